@@ -37,7 +37,7 @@ KERNEL_SOURCES = ("paper_2109_14403_amd/csrc/pipeline.h", "paper_2109_14403_amd/
 
 CALIB_FLOATS = 1 << 28
 NETWORK_PARAMS_MACS = 32 * 256 + 3 * 256 * 256 + 256 * 10   # multiply-adds per row of one network
-PMC_KINDS = {"xfwd": "k_xfwd", "ypass": "k_ypass", "zgreen": "k_zgreen", "xinv": "k_xinv", "eval": "k_eval",
+PMC_KINDS = {"xmid": "k_xmid", "ypass": "k_ypass", "zgreen": "k_zgreen", "eval": "k_eval",
              "commit": "k_commit_vox", "history": "k_history", "init": "k_init"}
 
 
@@ -66,6 +66,12 @@ def algorithmic_bytes(kind, n, fp_bytes, matrix_fraction):
         return field + spec, 2 * field + tang + spec, 5 * field + tang + spec
     if kind == "xinv":   # eval: read spectra and stress, write r; CG: read spectra and r, write r
         return spec + 2 * field, spec + 2 * field, spec + 2 * field
+    if kind == "xmid":
+        # the x pass of a Newton-CG iteration. Evaluation: read stress, write
+        # spectra. CG: read and write spectra, write r and p (read them, and
+        # read and write x, after the first), read tangent factors and phase
+        tang = 2 * fp_bytes * v + v
+        return field + spec, 2 * field + tang + 2 * spec, 6 * field + tang + 2 * spec
     if kind == "eval":   # read strain, phase, PA66 eps_p, eps_vp and history sums; write stress, tangent factors
         return 2 * field + v + matrix_fraction * v * 14 * 8 + 2 * fp_bytes * v, 0.0, 0.0
     return None
@@ -85,6 +91,8 @@ def solve_bytes(n, fp_bytes, matrix_fraction, n_state, n_eval, n_cg, n_first, in
     field = 6 * fp_bytes * v
     launches = n_eval + n_cg
     xf = algorithmic_bytes("xfwd", n, fp_bytes, matrix_fraction)
+    # "xfwd" and "xinv": a forward and an inverse x pass with the reduction of
+    # the residual between them; newton_solve_bytes has the single x pass
     ev = algorithmic_bytes("eval", n, fp_bytes, matrix_fraction)[0]
     out = {
         "xfwd": n_eval * xf[0] + n_first * xf[1] + (n_cg - n_first) * xf[2],
@@ -104,12 +112,22 @@ def solve_bytes(n, fp_bytes, matrix_fraction, n_state, n_eval, n_cg, n_first, in
     }
     spec3 = n * n * (n // 2 + 1) * 3 * 2 * fp_bytes
     f3 = 3 * fp_bytes * v
-    th = (thermal.get("xfwd", 0) * (f3 + spec3) + thermal.get("yfwd", 0) * 2 * spec3
+    th = ((thermal.get("xfwd", 0) + thermal.get("xmid", 0)) * (f3 + spec3) + thermal.get("yfwd", 0) * 2 * spec3
           + thermal.get("yinv", 0) * 2 * spec3 + thermal.get("zgreen", 0) * 2 * spec3
           + thermal.get("xinv", 0) * (spec3 + 2 * f3) + thermal.get("init", 0) * 2 * f3
           + thermal.get("commit", 0) * (f3 + v))
     out["conduction"] = th
     return {k: val / 1e9 for k, val in out.items()}
+
+
+def newton_solve_bytes(n, fp_bytes, matrix_fraction, n_state, n_eval, n_cg, n_first, increments, thermal):
+    """solve_bytes of the Newton-CG pipeline: one x pass an iteration in the
+    place of the forward and the inverse one."""
+    out = solve_bytes(n, fp_bytes, matrix_fraction, n_state, n_eval, n_cg, n_first, increments, thermal)
+    del out["xfwd"], out["xinv"]
+    xm = algorithmic_bytes("xmid", n, fp_bytes, matrix_fraction)
+    out["xmid"] = (n_eval * xm[0] + n_first * xm[1] + (n_cg - n_first) * xm[2]) / 1e9
+    return out
 
 
 def _host_info():
@@ -132,7 +150,7 @@ def counter_solve_bytes(n, n_eval, n_cg, increments):
     evaluations, n_cg CG iterations; the evaluation launches of CG iterations
     return at once). None if one is missing."""
     it = n_eval + n_cg
-    launches = {"xfwd": it, "ypass": 2 * it, "zgreen": it, "xinv": it, "eval": n_eval, "commit": increments,
+    launches = {"xmid": it, "ypass": 2 * it, "zgreen": it, "eval": n_eval, "commit": increments,
                 "history": increments, "init": increments}
     h = kernel_source_hash()
     tot = 0.0
@@ -488,7 +506,7 @@ def trace_summary(folder, log_path, n, command):
         d = json.loads([l for l in f if l.startswith("{") and '"metric"' in l][-1])
     roof = d["roofline"]
     kind = roof["kernel"]
-    name_part = {"xfwd": "k_xfwd", "xinv": "k_xinv", "zgreen": "k_zgreen", "eval": "k_eval",
+    name_part = {"xmid": "k_xmid", "xfwd": "k_xfwd", "xinv": "k_xinv", "zgreen": "k_zgreen", "eval": "k_eval",
                  "yfwd": "k_ypass", "yinv": "k_ypass"}[kind]
     bench_launches = d["kernel_ms"][kind][0]
     rows = [r for r in trace if name_part in r["Kernel_Name"] and "hom::" in r["Kernel_Name"]]
@@ -618,7 +636,7 @@ def pass_counter_summary(folder, command, out_path=None):
              "| kernel | launches | LDS instructions | LdsBankConflict | LdsUtil % | VALUBusy % | LDS wait % | "
              "GUI cycles per XCD |", "|---|---|---|---|---|---|---|---|"]
     names = [k for k in per["GRBM_GUI_ACTIVE"]
-             if any(p in k for p in ("k_xfwd<float, 6", "k_ypass<float, 6", "k_zgreen<float, 6", "k_xinv<float, 6"))]
+             if any(p in k for p in ("k_xmid<float, 6", "k_xfwd<float, 6", "k_ypass<float, 6", "k_zgreen<float, 6", "k_xinv<float, 6"))]
     for k in sorted(names):
         if any(k not in per[c] for c in PASS_COUNTERS):
             continue
@@ -977,7 +995,7 @@ def main():
             # timed increments over their wall time (graph replay, not the
             # per-kernel replay)
             thermal = {k[2:]: kstats[k][0] for k in kstats if k.startswith("t.")}
-            sb = solve_bytes(n, 4, matrix_fraction, 79, n_eval, n_cg, n_first, args.steps, thermal)
+            sb = newton_solve_bytes(n, 4, matrix_fraction, 79, n_eval, n_cg, n_first, args.steps, thermal)
             tot = sum(sb.values())
             roof["solve_frac"] = round(tot / elapsed / HBM_PEAK_GBS, 4)
             roof["solve_gbs"] = round(tot / elapsed, 1)

@@ -41,7 +41,7 @@ struct Ctl {
   int mode;
   int newton_it;    // residual evaluations done (Newton) / iterations (basic)
   int cg_it;        // CG iterations in the current Newton step
-  int cg_ready;     // A p of the current CG iteration is available
+  int cg_bad;       // p . C p of the current CG iteration is not positive and finite
   int pending;      // x += dx before the next evaluation
   int status;       // 0 running, 1 converged, <0 failure code
   int pipelines;    // FFT pipeline applications so far
@@ -87,6 +87,14 @@ struct ProbInc {
   double hk, nh, mexp, beta1, alpha0, dth;
 };
 
+// Limits of the solver's state machine.
+struct Limits {
+  double tol;
+  int max_newton;   // Newton: residual evaluations; basic: iterations
+  int max_krylov;
+  int linear;       // 1: CG solves to the tolerance at once
+};
+
 // Arguments shared by the pipeline kernels of one group.
 template <typename T>
 struct Pipe {
@@ -115,8 +123,10 @@ struct Pipe {
   double len[3];
   double ilen[3];           // 1 / len
   int green;                // Green enum
-  int alpha_blocks;         // > 0: the z pass forms the CG step length from the first
-                            // alpha_blocks partial sums of the x-forward pass
+  int xblocks;              // > 0: Newton-CG iteration; the x pass left xblocks partial sums a
+                            // problem, and the passes below drive the solver's state
+  int zblocks;              // work-groups a problem of the pass that applies the Green operator
+  Limits lim;
 };
 
 __device__ __forceinline__ bool pipeline_mode(int m) { return m == M_EVAL || m == M_CG || m == M_BASIC; }

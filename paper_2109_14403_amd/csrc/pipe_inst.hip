@@ -13,7 +13,7 @@ namespace {
 template <typename T, int C, int N, int NL>
 LaunchInfo xfwd_c(const Pipe<T>& a, hipStream_t s, bool dry) {
   LaunchInfo li;
-  li.threads = xfwd_threads<N, NL, C>();
+  li.threads = x_threads<N, NL, C>();
   li.blocks = a.nprob * ((a.ny * a.nz + NL - 1) / NL);
   li.lds = (size_t)xfwd_lds_elems<N, NL, C>() * sizeof(c2<T>);
   {
@@ -33,11 +33,8 @@ LaunchInfo xfwd_c(const Pipe<T>& a, hipStream_t s, bool dry) {
 
 template <typename T, int C, int N, int NL>
 LaunchInfo xinv_c(const Pipe<T>& a, hipStream_t s, bool dry) {
-  constexpr int G = N / Plan<N>::M;
-  constexpr int NP = (C + 1) / 2;
-  constexpr int L = NL * NP;
   LaunchInfo li;
-  li.threads = G * L;
+  li.threads = x_threads<N, NL, C>();
   li.blocks = a.nprob * ((a.ny * a.nz + NL - 1) / NL);
   li.lds = (size_t)xinv_lds_elems<N, NL, C>() * sizeof(c2<T>);
   {
@@ -51,6 +48,27 @@ LaunchInfo xinv_c(const Pipe<T>& a, hipStream_t s, bool dry) {
   }
   if (!dry) {
     hipLaunchKernelGGL((k_xinv<T, C, N, NL>), dim3(li.blocks), dim3(li.threads), li.lds, s, a);
+  }
+  return li;
+}
+
+template <typename T, int C, int N, int NL>
+LaunchInfo xmid_c(const Pipe<T>& a, hipStream_t s, bool dry) {
+  LaunchInfo li;
+  li.threads = x_threads<N, NL, C>();
+  li.blocks = a.nprob * ((a.ny * a.nz + NL - 1) / NL);
+  li.lds = (size_t)xmid_lds_elems<N, NL, C>() * sizeof(c2<T>);
+  {
+    static bool attr = false;
+    if (!attr && li.lds > 65536) {
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_xmid<T, C, N, NL>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      (void)hipGetLastError();
+      attr = true;
+    }
+  }
+  if (!dry) {
+    hipLaunchKernelGGL((k_xmid<T, C, N, NL>), dim3(li.blocks), dim3(li.threads), li.lds, s, a);
   }
   return li;
 }
@@ -118,7 +136,7 @@ LaunchInfo zgreen_v(const Pipe<T>& a, int tx, hipStream_t s, bool dry) {
 template <typename T, int N>
 LaunchInfo xfwd_launch(const Pipe<T>& a, hipStream_t s, bool dry) {
   static_assert(plan_m(N) == Plan<N>::M, "launch plan and transform plan disagree");
-  constexpr int NL = x_lines(N, sizeof(T) == 8, true);
+  constexpr int NL = x_lines(N, sizeof(T) == 8, false);
   return a.C == 6 ? xfwd_c<T, 6, N, NL>(a, s, dry) : xfwd_c<T, 3, N, NL>(a, s, dry);
 }
 
@@ -126,6 +144,12 @@ template <typename T, int N>
 LaunchInfo xinv_launch(const Pipe<T>& a, hipStream_t s, bool dry) {
   constexpr int NL = x_lines(N, sizeof(T) == 8, false);
   return a.C == 6 ? xinv_c<T, 6, N, NL>(a, s, dry) : xinv_c<T, 3, N, NL>(a, s, dry);
+}
+
+template <typename T, int N>
+LaunchInfo xmid_launch(const Pipe<T>& a, hipStream_t s, bool dry) {
+  constexpr int NL = x_lines(N, sizeof(T) == 8, true);
+  return a.C == 6 ? xmid_c<T, 6, N, NL>(a, s, dry) : xmid_c<T, 3, N, NL>(a, s, dry);
 }
 
 template <typename T, int N>
@@ -147,6 +171,7 @@ LaunchInfo zgreen_launch(const Pipe<T>& a, int sched, hipStream_t s, bool dry) {
 #define HOM_INST(T)                                                                         \
   template LaunchInfo xfwd_launch<T, HOM_N>(const Pipe<T>&, hipStream_t, bool);             \
   template LaunchInfo xinv_launch<T, HOM_N>(const Pipe<T>&, hipStream_t, bool);             \
+  template LaunchInfo xmid_launch<T, HOM_N>(const Pipe<T>&, hipStream_t, bool);             \
   template LaunchInfo ypass_launch<T, HOM_N>(const Pipe<T>&, int, int, hipStream_t, bool);  \
   template LaunchInfo zgreen_launch<T, HOM_N>(const Pipe<T>&, int, hipStream_t, bool);
 HOM_INST(float)

@@ -31,12 +31,12 @@ constexpr int plan_m(int n) {
   return 0;
 }
 
-// x-pass lines per work-group. The FP32 forward pass holds the three CG
+// x-pass lines per work-group. The FP32 middle pass holds the three CG
 // fields of its voxels in registers, which allows fewer of its work-groups per
-// CU: it takes half as many lines, so more, smaller work-groups overlap their
-// load and transform phases.
-constexpr int x_lines(int n, bool fp64, bool fwd) {
-  const int nl = ((fp64 ? 64 : 128) / (n / plan_m(n))) / (fwd && !fp64 ? 2 : 1);
+// CU: it takes half as many lines as the inverse pass, so more, smaller
+// work-groups overlap their load and transform phases.
+constexpr int x_lines(int n, bool fp64, bool mid) {
+  const int nl = ((fp64 ? 64 : 128) / (n / plan_m(n))) / (mid && !fp64 ? 2 : 1);
   return nl < 1 ? 1 : nl;
 }
 
@@ -60,6 +60,8 @@ LaunchInfo xfwd_launch(const Pipe<T>& a, hipStream_t s, bool dry);
 template <typename T, int N>
 LaunchInfo xinv_launch(const Pipe<T>& a, hipStream_t s, bool dry);
 template <typename T, int N>
+LaunchInfo xmid_launch(const Pipe<T>& a, hipStream_t s, bool dry);
+template <typename T, int N>
 LaunchInfo ypass_launch(const Pipe<T>& a, int sched, int inverse, hipStream_t s, bool dry);
 template <typename T, int N>
 LaunchInfo zgreen_launch(const Pipe<T>& a, int sched, hipStream_t s, bool dry);
@@ -68,6 +70,8 @@ template <typename T>
 LaunchInfo run_xfwd(const Pipe<T>& a, hipStream_t s, bool dry = false);
 template <typename T>
 LaunchInfo run_xinv(const Pipe<T>& a, hipStream_t s, bool dry = false);
+template <typename T>
+LaunchInfo run_xmid(const Pipe<T>& a, hipStream_t s, bool dry = false);
 template <typename T>
 LaunchInfo run_ypass(const Pipe<T>& a, int sched, int inverse, hipStream_t s, bool dry = false);
 template <typename T>

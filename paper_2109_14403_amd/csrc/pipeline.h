@@ -1,20 +1,38 @@
-// The five-pass FFT / Green-operator pipeline of one solver iteration.
+// The FFT / Green-operator pipeline of one solver iteration.
 //
-//   xfwd   pre-operation per voxel (copy of the stress / flux field, or the
-//          algorithmic tangent applied to the CG direction), then real-to-
-//          complex transforms along x (two real components packed into one
-//          complex line), written as the half spectrum kx = 0..nx/2.
+//   xmid   (Newton-CG) inverse transforms along x of the last application of
+//          the operator, the CG updates of r, p and x per voxel, the
+//          algorithmic tangent applied to the new direction, and its forward
+//          transforms along x: the half spectrum kx = 0..nx/2 is replaced in
+//          place (two real components packed into one complex line). A
+//          residual evaluation only transforms the stress / flux field.
 //   ypass  complex transforms along y on tiles of TX contiguous kx columns.
 //   zgreen forward transform along z, Green operator per frequency on all
 //          components, inverse transform along z.
 //   ypass  inverse along y.
-//   xinv   complex-to-real inverse along x, scaled by 1/(nx ny nz), then the
-//          post-operation per voxel (residual / CG residual update / basic-
-//          scheme update) with FP64 partial sums for the reductions.
+//
+// The CG scalars are known before a pass needs them: alpha = r.r / p.C p from
+// the partial sums of the x pass (p is compatible and the projector
+// orthogonal, so p.A p = p.C p); the norm of A p by Parseval's theorem from
+// the spectrum the Green operator leaves; then
+//   |r - alpha A p|^2 = alpha^2 |A p|^2 - r.r,
+// because r.A p = p.A p for conjugate directions. So beta and the stopping
+// test are there when the x pass starts, and one pass over the fields does
+// what an inverse and a forward pass with a reduction between them did. r.r
+// itself is summed from the updated residual in every x pass: the estimate
+// decides beta and the end of the solve, and never accumulates. The end of a
+// Newton step is decided by the true residual of its evaluation (|r| by
+// Parseval's theorem, |sigma| from the x pass).
+//
+// The fixed-point scheme has no such recurrence and takes
+//   xfwd   forward transforms along x of the stress / flux field,
+//   xinv   complex-to-real inverse along x, scaled by 1/(nx ny nz), the
+//          update of the strain and FP64 partial sums for the reductions,
+// around the same y and z passes.
 //
 // CG keeps three fields (x, r, p): the step x += alpha p of iteration k is
-// deferred to the x-forward pass of iteration k + 1 (or to the next
-// constitutive evaluation), which reads the old p anyway.
+// deferred to the x pass of iteration k + 1 (or to the next constitutive
+// evaluation), which reads the old p anyway.
 //
 // Every kernel serves all problems of a group in one launch: blockIdx.x runs
 // over (problem, tile), and a block whose problem is not iterating exits at
@@ -256,188 +274,36 @@ constexpr int tile_lds_elems() {
 // ---------------------------------------------------------------------------
 // x forward: pre-operation + packed real-to-complex transforms
 // ---------------------------------------------------------------------------
-// Threads of an x-forward work-group: the G * L of the line transforms, or
-// one per four-voxel work item of the per-voxel phase if that is more (the
-// extra threads idle through the transforms), so that the per-voxel phase,
-// whose loads dominate, takes one memory round trip
+// Threads of an x work-group: the G * L of the line transforms, or one per
+// four-voxel work item of the per-voxel phase if that is more (the extra
+// threads idle through the transforms), so that the per-voxel phase, whose
+// loads dominate, takes one memory round trip; whole waves
 template <int N, int NL, int C>
-constexpr int xfwd_threads() {
+constexpr int x_threads() {
   constexpr int ft = (N / Plan<N>::M) * NL * ((C + 1) / 2);
   constexpr int items = NL * N / 4;
-  return items > ft ? items : ft;
+  return ((items > ft ? items : ft) + 63) / 64 * 64;
 }
 
-// FP32: at most 128 VGPRs, four waves per SIMD (a few spilled values are
-// cheaper than the third of the occupancy the unbounded build gives up)
+// Forward transforms of the staged lines (rows of SP complex values in buf,
+// two real components each) and the unpacked half spectra [line][kx][comp],
+// rows PS * C apart in memory, with 16-byte stores. Starts and ends inside one
+// work-group; the caller has synchronized after its last write to buf.
 template <typename T, int C, int N, int NL>
-__global__ void __launch_bounds__((xfwd_threads<N, NL, C>()))
-    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) k_xfwd(Pipe<T> a) {
+__device__ __forceinline__ void x_forward_lines(const Pipe<T>& a, int prob, int line0, int nvl, const c2<T>* tw,
+                                                c2<T>* buf) {
   constexpr int M = Plan<N>::M;
   constexpr int G = N / M;
   constexpr int NP = (C + 1) / 2;
   constexpr int L = NL * NP;
   constexpr int H = N / 2 + 1;
   constexpr int SP = xstage_pitch(N);
-  static_assert(xfwd_lds_elems<N, NL, C>() - N >= L * SP && L * SP >= N * L, "x-forward LDS buffer too small");
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  c2<T>* tw = reinterpret_cast<c2<T>*>(smem_raw);
-  c2<T>* buf = tw + N;
-
-  __shared__ double red[16];
-  const int nlines = a.ny * a.nz;
-  const int bpp = (nlines + NL - 1) / NL;
-  const int prob = blockIdx.x / bpp;
-  const int blk = blockIdx.x % bpp;
-  const int line0 = blk * NL;
-  const Ctl& ctl = a.ctl[prob];
-  const int mode = ctl.mode;
-  if (!pipeline_mode(mode)) return;
   const int tid = threadIdx.x;
   const int nth = blockDim.x;
-  for (int i = tid; i < N; i += nth) tw[i] = a.twx[i];
-  double pcp = 0.0;  // CG: partial sum of p . C p  (= p . A p, p being compatible)
-
-  const long long nv = a.vs;  // stride of the per-voxel arrays (component, problem)
-  const long long fo = (long long)prob * C * nv;
-  const uint8_t* phase = a.phase + (long long)prob * nv;
-  const ProbInc& inc = a.inc[prob];
-  const bool cg = (mode == M_CG);
-  const bool first = (ctl.cg_it == 0);
-  const T beta = T(ctl.beta);
-  const T alpha_prev = T(ctl.alpha);  // step length of the previous CG iteration
-  __shared__ T ptab[MAX_PHASES];  // 3K (mechanics) or kappa (conduction) per phase
-  if (tid < MAX_PHASES) ptab[tid] = T(C == 6 ? inc.ph[tid].K3 : inc.ph[tid].kappa);
-  __syncthreads();
-
-  // four consecutive voxels of one line per work item, 16-byte accesses
-  const int nvl = min(NL, nlines - line0);
-  // uniform per-component bases and a 32-bit voxel offset: loads and stores
-  // take the scalar-base + 32-bit-offset form
-  const unsigned v0 = (unsigned)(line0 * N);
-  const T* fb = a.f + fo;
-  const T* rb = a.r + fo;
-  T* pb = a.p + fo;
-  T* xb = a.x + fo;
-  const T* tb = a.tab + (long long)prob * 2 * nv;
-  const T* nb = a.tn + (long long)prob * 6 * nv;
-  for (int w = tid; w < NL * N / 4; w += nth) {
-    const int e = 4 * w;
-    const int li = e / N;
-    const int xv = e - li * N;
-    T out[4][2 * NP];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int c = 0; c < 2 * NP; ++c) out[j][c] = T(0);
-    if (li < nvl) {
-      const unsigned v = v0 + (unsigned)e;
-      if (!cg) {
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-          const Q4<T> q = ld4(at(fb + c * nv, v));
-#pragma unroll
-          for (int j = 0; j < 4; ++j) out[j][c] = q.v[j];
-        }
-      } else {
-        // p = r + beta p; the step x += alpha p of the previous iteration is
-        // applied here, where the old direction is read anyway. Every load of
-        // the work item is issued before the first store (one memory round
-        // trip instead of one per component).
-        Q4<T> rq[C], pq[C], xq[C];
-#pragma unroll
-        for (int c = 0; c < C; ++c) rq[c] = ld4(at(rb + c * nv, v));
-        if (!first) {  // uniform over the block
-#pragma unroll
-          for (int c = 0; c < C; ++c) {
-            pq[c] = ld4(at(pb + c * nv, v));
-            xq[c] = ld4(at(xb + c * nv, v));
-          }
-        }
-        Q4<T> ca, cb;
-        if constexpr (C == 6) {
-          ca = ld4(at(tb, v));
-          cb = ld4(at(tb + nv, v));
-        }
-        const uchar4 ph = *reinterpret_cast<const uchar4*>(at(phase, v));
-        T pv[C][4];
-        if (first) {
-#pragma unroll
-          for (int c = 0; c < C; ++c)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) pv[c][j] = rq[c].v[j];
-        } else {
-#pragma unroll
-          for (int c = 0; c < C; ++c) {
-            T xn[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              pv[c][j] = rq[c].v[j] + beta * pq[c].v[j];
-              xn[j] = xq[c].v[j] + alpha_prev * pq[c].v[j];
-            }
-            st4(at(xb + c * nv, v), xn);
-          }
-        }
-#pragma unroll
-        for (int c = 0; c < C; ++c) st4(at(pb + c * nv, v), pv[c]);
-        const int phs[4] = {ph.x, ph.y, ph.z, ph.w};
-        if constexpr (C == 6) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const T tr3 = (pv[0][j] + pv[1][j] + pv[2][j]) * T(1.0 / 3.0);
-            const T sph = (ptab[phs[j]] - ca.v[j]) * tr3;
-#pragma unroll
-            for (int c = 0; c < 6; ++c) out[j][c] = ca.v[j] * pv[c][j];
-            out[j][0] += sph;
-            out[j][1] += sph;
-            out[j][2] += sph;
-          }
-          if (cb.v[0] != T(0) || cb.v[1] != T(0) || cb.v[2] != T(0) || cb.v[3] != T(0)) {
-            T nd[6][4];
-#pragma unroll
-            for (int c = 0; c < 6; ++c) {
-              const Q4<T> q = ld4(at(nb + c * nv, v));
-#pragma unroll
-              for (int j = 0; j < 4; ++j) nd[c][j] = q.v[j];
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              if (cb.v[j] == T(0)) continue;
-              T dot = T(0);
-#pragma unroll
-              for (int c = 0; c < 6; ++c) dot += nd[c][j] * pv[c][j];
-#pragma unroll
-              for (int c = 0; c < 6; ++c) out[j][c] += cb.v[j] * dot * nd[c][j];
-            }
-          }
-        } else {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const T kap = ptab[phs[j]];
-#pragma unroll
-            for (int c = 0; c < C; ++c) out[j][c] = kap * pv[c][j];
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int c = 0; c < C; ++c) pcp += (double)pv[c][j] * (double)out[j][c];
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < NP; ++q)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) buf[(li * NP + q) * SP + xv + j] = mk(out[j][2 * q], out[j][2 * q + 1]);
-  }
-  if (cg) {  // uniform per block
-    double s[1] = {pcp};
-    block_sum<1>(s, red);
-    if (tid == 0) a.part[part_index(prob, 0, blk, a.maxblk)] = s[0];
-  }
-  __syncthreads();
-
   const bool fw = tid < G * L;  // a thread of the line transforms
   const int l = tid % L;
   const int t = fw ? tid / L : 0;
+  __builtin_assume(t < G);
   c2<T> r[M];
 #pragma unroll
   for (int m = 0; m < M; ++m) r[m] = fw ? buf[l * SP + t + G * m] : mk(T(0), T(0));
@@ -485,6 +351,60 @@ __global__ void __launch_bounds__((xfwd_threads<N, NL, C>()))
   }
 }
 
+// Partial sums of an EVAL pass: |f|^2 of the field that is transformed.
+template <typename T, int C>
+__device__ __forceinline__ double x_load_field(const T* fb, long long nv, unsigned v, T (&out)[4][2 * ((C + 1) / 2)]) {
+  double ff = 0.0;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const Q4<T> q = ld4(at(fb + c * nv, v));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      out[j][c] = q.v[j];
+      ff += (double)q.v[j] * (double)q.v[j];
+    }
+  }
+  return ff;
+}
+
+// Fixed-point scheme (and single applications of the operator): the stress /
+// flux field as it is.
+template <typename T, int C, int N, int NL>
+__global__ void __launch_bounds__((x_threads<N, NL, C>())) k_xfwd(Pipe<T> a) {
+  constexpr int NP = (C + 1) / 2;
+  constexpr int SP = xstage_pitch(N);
+  static_assert(xfwd_lds_elems<N, NL, C>() - N >= NL * NP * SP, "x-forward LDS buffer too small");
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  c2<T>* tw = reinterpret_cast<c2<T>*>(smem_raw);
+  c2<T>* buf = tw + N;
+  const int nlines = a.ny * a.nz;
+  const int bpp = (nlines + NL - 1) / NL;
+  const int prob = blockIdx.x / bpp;
+  const int line0 = (blockIdx.x % bpp) * NL;
+  if (!pipeline_mode(a.ctl[prob].mode)) return;
+  const int tid = threadIdx.x;
+  for (int i = tid; i < N; i += blockDim.x) tw[i] = a.twx[i];
+  const int nvl = min(NL, nlines - line0);
+  const T* fb = a.f + (long long)prob * C * a.vs;
+  for (int w = tid; w < NL * N / 4; w += blockDim.x) {
+    const int e = 4 * w;
+    const int li = e / N;
+    const int xv = e - li * N;
+    T out[4][2 * NP];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int c = 0; c < 2 * NP; ++c) out[j][c] = T(0);
+    if (li < nvl) (void)x_load_field<T, C>(fb, a.vs, (unsigned)(line0 * N + e), out);
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) buf[(li * NP + q) * SP + xv + j] = mk(out[j][2 * q], out[j][2 * q + 1]);
+  }
+  __syncthreads();
+  x_forward_lines<T, C, N, NL>(a, prob, line0, nvl, tw, buf);
+}
+
 // Work-groups are dispatched to the 8 XCDs round-robin (work-group i to XCD
 // i mod 8), each XCD with its own L2. This bijection of [0, n) gives every XCD
 // a contiguous range of tiles, so neighbouring kx tiles, which share 128-byte
@@ -493,6 +413,96 @@ __device__ __forceinline__ int xcd_remap(int i, int n) {
   const int q = n >> 3, rem = n & 7;
   const int x = i & 7, k = i >> 3;
   return x * q + min(x, rem) + k;
+}
+
+// ---------------------------------------------------------------------------
+// the Newton-CG state of a problem, driven by the first work-group of its y
+// and z passes while the others transform. A work-group that starts late may
+// already see the new mode: it skips a transform only where the problem has
+// ended and nothing reads the spectrum any more.
+// ---------------------------------------------------------------------------
+// Sums of the first n partials of K quantities q0, q0 + 1, ...; in thread 0.
+template <typename T, int K>
+__device__ __forceinline__ void block_parts(const Pipe<T>& a, int prob, int q0, int n, double (&s)[K], double* red) {
+#pragma unroll
+  for (int k = 0; k < K; ++k) s[k] = 0.0;
+  const double* pp = a.part + part_index(prob, q0, 0, a.maxblk);
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) s[k] += pp[(long long)k * a.maxblk + i];
+  }
+  block_sum<K>(s, red);
+}
+
+// CG step length alpha = r.r / p.C p, or |f| of a residual evaluation, from
+// the partial sums of the x pass.
+template <typename T>
+__device__ __forceinline__ void cg_step_length(const Pipe<T>& a, int prob) {
+  __shared__ double red[2 * 16];
+  Ctl& c = a.ctl[prob];
+  double s[2];
+  block_parts<T, 2>(a, prob, 0, a.xblocks, s, red);
+  if (threadIdx.x != 0) return;
+  if (c.mode == M_CG) {
+    const double pap = s[0];
+    c.rr = s[1];
+    c.cg_bad = !(pap > 0.0) || !isfinite(pap);
+    c.alpha = c.cg_bad ? 0.0 : c.rr / pap;
+  } else {
+    c.fnorm = sqrt(s[0]);
+  }
+}
+
+// End of an application of the operator, |v|^2 (Parseval sum s of the
+// spectrum) being the squared norm of the residual or of A p: transitions of
+// the state machine. Called by one thread.
+__device__ __forceinline__ void newton_cg_transition(Ctl& c, double vv, const Limits& lim) {
+  c.pipelines += 1;
+  if (c.mode == M_CG) {
+    // |r - alpha A p|^2; rounding may leave a vanishing residual below zero
+    const double rn = fmax(c.alpha * c.alpha * vv - c.rr, 0.0);
+    c.beta = c.rr > 0.0 ? rn / c.rr : 0.0;
+    c.cg_it += 1;
+    c.krylov += 1;
+    if (c.cg_bad || !isfinite(vv) || !isfinite(c.rr)) {
+      c.mode = M_FAIL;
+      c.status = -4;
+    } else if (rn <= c.cg_target || c.cg_it >= lim.max_krylov) {
+      c.mode = M_EVAL;
+      c.pending = 1;
+    }
+  } else {
+    const double res = c.fnorm > 0.0 ? sqrt(vv) / c.fnorm : 0.0;
+    c.res = res;
+    c.newton_it += 1;
+    c.pending = 0;
+    if (!isfinite(res)) {
+      c.mode = M_FAIL;
+      c.status = -4;
+    } else if (res <= lim.tol) {
+      c.mode = M_DONE;
+      c.status = 1;
+    } else if (c.newton_it > lim.max_newton) {
+      c.mode = M_FAIL;
+      c.status = -3;
+    } else {
+      const double eta = lim.linear ? 0.0 : fmin(0.1, res);
+      const double tgt = fmax(eta * sqrt(vv), 0.5 * lim.tol * c.fnorm);
+      c.cg_target = tgt * tgt;
+      c.cg_it = 0;
+      c.beta = 0.0;
+      c.mode = M_CG;
+    }
+  }
+}
+
+template <typename T>
+__device__ __forceinline__ void newton_cg_step(const Pipe<T>& a, int prob, double* red /* >= 16 doubles of LDS */) {
+  double s[1];
+  block_parts<T, 1>(a, prob, 2, a.zblocks, s, red);
+  if (threadIdx.x == 0)
+    newton_cg_transition(a.ctl[prob], s[0] / ((double)a.nx * a.ny * a.nz), a.lim);
 }
 
 // ---------------------------------------------------------------------------
@@ -514,12 +524,17 @@ __global__ void __launch_bounds__((N / Plan<N, V>::M) * TX * C) k_ypass(Pipe<T> 
   const int prob = bid / bpp;
   const int b = bid % bpp;
   if (!pipeline_mode(a.ctl[prob].mode)) return;
+  // the exchange buffer is free until the first transform pass writes it
+  if (inverse && a.xblocks > 0 && b == 0) newton_cg_step(a, prob, reinterpret_cast<double*>(buf));
   const int z = b / nkb;
   const int kb = b % nkb;
   const int tid = threadIdx.x;
   for (int i = tid; i < N; i += blockDim.x) tw[i] = a.twy[i];
   const int l = tid % L;
   const int t = tid / L;
+  // the launch has G * L threads: the twiddle indices below need no wrap (with
+  // the range lost, one instantiation mixed up two twiddle loads)
+  __builtin_assume(t < G);
   const int kx = kb * TX + l / C;
   const int c = l % C;
   const bool active = kx < P;
@@ -563,33 +578,13 @@ __global__ void __launch_bounds__((N / Plan<N, V>::M) * TX * C)
   const int kb = b % nkb;
   const int tid = threadIdx.x;
   const int nth = blockDim.x;
-  if (a.alpha_blocks > 0 && b == 0) {
-    // CG step length alpha = r.r / p.C p from the x-forward pass's partials of
-    // p.C p (= p.A p: p is compatible and the projector orthogonal). Formed
-    // by the first work-group of the problem while the others transform; the
-    // x-inverse pass applies it.
-    Ctl& cw = a.ctl[prob];
-    if (cw.mode == M_CG && !cw.cg_ready) {  // uniform over the work-group
-      __shared__ double red[16];
-      double s[1] = {0.0};
-      const double* pp = a.part + part_index(prob, 0, 0, a.maxblk);
-      for (int i = tid; i < a.alpha_blocks; i += nth) s[0] += pp[i];
-      block_sum<1>(s, red);
-      if (tid == 0) {
-        const double pap = s[0];
-        if (!(pap > 0.0) || !isfinite(pap)) {
-          cw.mode = M_FAIL;
-          cw.status = -4;
-        } else {
-          cw.alpha = cw.rr / pap;
-          cw.cg_ready = 1;
-        }
-      }
-    }
-  }
+  if (a.xblocks > 0 && b == 0) cg_step_length(a, prob);
   for (int i = tid; i < N; i += nth) tw[i] = a.twz[i];
   const int l = tid % L;
   const int t = tid / L;
+  // the launch has G * L threads: the twiddle indices below need no wrap (with
+  // the range lost, one instantiation mixed up two twiddle loads)
+  __builtin_assume(t < G);
   const int kx = kb * TX + l / C;
   const int c = l % C;
   const bool active = kx < P;
@@ -622,6 +617,10 @@ __global__ void __launch_bounds__((N / Plan<N, V>::M) * TX * C)
   const T fab2 = fa * fa + fb * fb;
   const T il2 = T(a.ilen[2]);
   static_assert(((N / Plan<N, V>::M) * TX * C) % TX == 0, "thread count must be a multiple of TX");
+  // Parseval sum of the operator's result; a half spectrum stands for its
+  // mirror image too, except at kx = 0 and the Nyquist index
+  const double pw = (kxx == 0 || 2 * kxx == a.nx) ? 1.0 : 2.0;
+  double norm = 0.0;
   for (int idx = tid; idx < N * TX; idx += nth) {
     const int kz = idx / TX;
     const int kxi = idx - kz * TX;
@@ -670,7 +669,16 @@ __global__ void __launch_bounds__((N / Plan<N, V>::M) * TX * C)
         green_grad<T>(v, n0, n1, n2, cs);
     }
 #pragma unroll
-    for (int cc = 0; cc < C; ++cc) buf[kz * L + kxi * C + cc] = v[cc];
+    for (int cc = 0; cc < C; ++cc) {
+      buf[kz * L + kxi * C + cc] = v[cc];
+      norm += (double)v[cc].x * (double)v[cc].x + (double)v[cc].y * (double)v[cc].y;
+    }
+  }
+  if (a.xblocks > 0) {
+    __shared__ double nred[16];
+    double s[1] = {pw * norm};
+    block_sum<1>(s, nred);
+    if (tid == 0) a.part[part_index(prob, 2, b, a.maxblk)] = s[0];
   }
   __syncthreads();
 #pragma unroll
@@ -683,10 +691,14 @@ __global__ void __launch_bounds__((N / Plan<N, V>::M) * TX * C)
 }
 
 // ---------------------------------------------------------------------------
-// x inverse: packed complex-to-real transforms + post-operation + partial sums
+// x inverse: packed complex-to-real transforms (+ post-operation + partial sums)
 // ---------------------------------------------------------------------------
-template <typename T, int C, int N, int NL>
-__global__ void __launch_bounds__((N / Plan<N>::M) * NL * ((C + 1) / 2)) k_xinv(Pipe<T> a) {
+// The half spectra of a work-group's lines, transformed back: rows of SP
+// complex values in buf (unscaled), two real components each. The launch has
+// NTH threads. Ends synchronized.
+template <typename T, int C, int N, int NL, int NTH>
+__device__ __forceinline__ void x_inverse_lines(const Pipe<T>& a, int prob, int line0, int nvl, const c2<T>* tw,
+                                                c2<T>* buf) {
   constexpr int M = Plan<N>::M;
   constexpr int G = N / M;
   constexpr int NP = (C + 1) / 2;
@@ -696,31 +708,12 @@ __global__ void __launch_bounds__((N / Plan<N>::M) * NL * ((C + 1) / 2)) k_xinv(
   static_assert(xinv_lds_elems<N, NL, C>() - N >= L * SP && xinv_lds_elems<N, NL, C>() - N >= NL * H * C &&
                     L * SP >= N * L,
                 "x-inverse LDS buffer too small");
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  c2<T>* tw = reinterpret_cast<c2<T>*>(smem_raw);
-  c2<T>* buf = tw + N;  // holds the staged half spectra first, then the line FFTs
-  __shared__ double red[2 * 16];
-
-  const int nlines = a.ny * a.nz;
-  const int bpp = (nlines + NL - 1) / NL;
-  const int prob = blockIdx.x / bpp;
-  const int blk = blockIdx.x % bpp;
-  const int line0 = blk * NL;
-  const Ctl& ctl = a.ctl[prob];
-  const int mode = ctl.mode;
-  if (!pipeline_mode(mode)) return;
-  const T alpha = T(ctl.alpha);
   const int tid = threadIdx.x;
-  const int nth = blockDim.x;
-  for (int i = tid; i < N; i += nth) tw[i] = a.twx[i];
   // stage the block's half spectra [line][kx][comp] (rows rowp apart in
   // memory, packed in LDS)
-  const int nvl = min(NL, nlines - line0);
   const int rowp = a.PS * C;
   const c2<T>* spec = a.spec + (long long)prob * a.nz * a.ny * rowp + (long long)line0 * rowp;
-  // all of a thread's loads are issued before the LDS writes (the launch has
-  // exactly NTH threads)
-  constexpr int NTH = G * L;
+  // all of a thread's loads are issued before the LDS writes
   if constexpr (sizeof(c2<T>) == 8 && C % 2 == 0) {
     constexpr int K = (NL * H * C / 2 + NTH - 1) / NTH;
     const int tot = nvl * H * C / 2;
@@ -750,10 +743,12 @@ __global__ void __launch_bounds__((N / Plan<N>::M) * NL * ((C + 1) / 2)) k_xinv(
 #pragma unroll
     for (int k = 0; k < K; ++k) buf[min(tid + k * NTH, tot - 1)] = t2[k];
   }
-  for (int e = nvl * H * C + tid; e < NL * H * C; e += nth) buf[e] = mk(T(0), T(0));
+  for (int e = nvl * H * C + tid; e < NL * H * C; e += NTH) buf[e] = mk(T(0), T(0));
   __syncthreads();
+  const bool fw = NTH == G * L || tid < G * L;  // a thread of the line transforms
   const int l = tid % L;
-  const int t = tid / L;
+  const int t = fw ? tid / L : 0;
+  __builtin_assume(t < G);
   const int li = l / NP;
   const int q = l - li * NP;
   c2<T> r[M];
@@ -771,18 +766,43 @@ __global__ void __launch_bounds__((N / Plan<N>::M) * NL * ((C + 1) / 2)) k_xinv(
     // Z = A + i B, transformed as conj(DFT(conj(Z)))
     r[m] = mk(A.x - B.y, -(A.y + B.x));
   }
-  Plan<N>::run(r, t, tw, buf, L, l, true);
+  Plan<N>::run(r, t, tw, buf, L, l, fw);
   __syncthreads();
+  if (fw) {
 #pragma unroll
-  for (int m = 0; m < M; ++m) buf[l * SP + t + G * m] = conjg(r[m]);
+    for (int m = 0; m < M; ++m) buf[l * SP + t + G * m] = conjg(r[m]);
+  }
   __syncthreads();
+}
+
+template <typename T, int C, int N, int NL>
+__global__ void __launch_bounds__((x_threads<N, NL, C>())) k_xinv(Pipe<T> a) {
+  constexpr int NP = (C + 1) / 2;
+  constexpr int SP = xstage_pitch(N);
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  c2<T>* tw = reinterpret_cast<c2<T>*>(smem_raw);
+  c2<T>* buf = tw + N;  // holds the staged half spectra first, then the line FFTs
+  __shared__ double red[2 * 16];
+
+  const int nlines = a.ny * a.nz;
+  const int bpp = (nlines + NL - 1) / NL;
+  const int prob = blockIdx.x / bpp;
+  const int blk = blockIdx.x % bpp;
+  const int line0 = blk * NL;
+  const int mode = a.ctl[prob].mode;
+  if (!pipeline_mode(mode)) return;
+  const int tid = threadIdx.x;
+  const int nth = blockDim.x;
+  for (int i = tid; i < N; i += nth) tw[i] = a.twx[i];
+  const int nvl = min(NL, nlines - line0);
+  x_inverse_lines<T, C, N, NL, x_threads<N, NL, C>()>(a, prob, line0, nvl, tw, buf);
 
   const long long nv = a.vs;  // stride of the per-voxel arrays (component, problem)
   const long long fo = (long long)prob * C * nv;
   const T scale = T(1.0 / ((double)a.nx * a.ny * a.nz));
   double s0 = 0.0, s1 = 0.0;
   const unsigned v0 = (unsigned)(line0 * N);
-  const T* sb = (mode == M_EVAL ? a.f : (mode == M_CG ? a.r : a.x)) + fo;  // uniform bases
+  const T* sb = (mode == M_EVAL ? a.f : a.x) + fo;  // uniform bases
   T* db = (mode == M_BASIC ? a.x : a.r) + fo;
   for (int w = tid; w < nvl * N / 4; w += nth) {
     const int e = 4 * w;
@@ -812,15 +832,6 @@ __global__ void __launch_bounds__((N / Plan<N>::M) * NL * ((C + 1) / 2)) k_xinv(
           s1 += (double)q[c].v[j] * (double)q[c].v[j];
         }
         st4(o, out);
-      } else if (mode == M_CG) {
-        // residual update with alpha = r.r / p.C p: r -= alpha A p (the step
-        // x += alpha p follows in the next x-forward pass or evaluation)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          out[j] = q[c].v[j] - alpha * g[j];
-          s0 += (double)out[j] * (double)out[j];
-        }
-        st4(o, out);
       } else {  // basic scheme: x -= Gamma0 sigma
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -838,6 +849,189 @@ __global__ void __launch_bounds__((N / Plan<N>::M) * NL * ((C + 1) / 2)) k_xinv(
     a.part[part_index(prob, 0, blk, a.maxblk)] = s[0];
     a.part[part_index(prob, 1, blk, a.maxblk)] = s[1];
   }
+}
+
+// ---------------------------------------------------------------------------
+// x middle: one pass of a Newton-CG iteration over the fields
+// ---------------------------------------------------------------------------
+template <int N, int NL, int C>
+constexpr int xmid_lds_elems() {
+  return xinv_lds_elems<N, NL, C>() > xfwd_lds_elems<N, NL, C>() ? xinv_lds_elems<N, NL, C>()
+                                                                  : xfwd_lds_elems<N, NL, C>();
+}
+
+// Bound by HBM at 128^3 and above (two spectra and six field accesses, 207
+// bytes a voxel in FP32), by the latency of its chain of loads, exchanges and
+// stores below. In the place of a forward pass, an inverse pass and a
+// reduction kernel, which moved the residual twice more and stood one behind
+// the other: an increment of the 256^3 fibre composite 140.4 -> 134.8 ms, of
+// a 64^3 cell 6.72 -> 5.77 ms, a 32^3 cell with its four tangents 28.0 ->
+// 22.7 ms, 96 x 24 x 48 in FP64 19.7 -> 17.5 ms.
+// FP32: at most 128 VGPRs, four waves per SIMD (it takes 107)
+template <typename T, int C, int N, int NL>
+__global__ void __launch_bounds__((x_threads<N, NL, C>()))
+    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) k_xmid(Pipe<T> a) {
+  constexpr int NP = (C + 1) / 2;
+  constexpr int SP = xstage_pitch(N);
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  c2<T>* tw = reinterpret_cast<c2<T>*>(smem_raw);
+  c2<T>* buf = tw + N;
+  __shared__ double red[2 * 16];
+  const int nlines = a.ny * a.nz;
+  const int bpp = (nlines + NL - 1) / NL;
+  const int prob = blockIdx.x / bpp;
+  const int blk = blockIdx.x % bpp;
+  const int line0 = blk * NL;
+  const Ctl& ctl = a.ctl[prob];
+  const int mode = ctl.mode;
+  if (mode != M_EVAL && mode != M_CG) return;
+  const int tid = threadIdx.x;
+  const int nth = blockDim.x;
+  for (int i = tid; i < N; i += nth) tw[i] = a.twx[i];
+  const long long nv = a.vs;  // stride of the per-voxel arrays (component, problem)
+  const long long fo = (long long)prob * C * nv;
+  const uint8_t* phase = a.phase + (long long)prob * nv;
+  const ProbInc& inc = a.inc[prob];
+  const bool cg = (mode == M_CG);
+  const bool first = (ctl.cg_it == 0);
+  const T beta = T(ctl.beta);
+  const T alpha = T(ctl.alpha);  // step length of the direction p in memory
+  __shared__ T ptab[MAX_PHASES];  // 3K (mechanics) or kappa (conduction) per phase
+  if (tid < MAX_PHASES) ptab[tid] = T(C == 6 ? inc.ph[tid].K3 : inc.ph[tid].kappa);
+  const int nvl = min(NL, nlines - line0);
+  if (cg)  // uniform over the work-group
+    x_inverse_lines<T, C, N, NL, x_threads<N, NL, C>()>(a, prob, line0, nvl, tw, buf);
+
+  // four consecutive voxels of one line per work item, 16-byte accesses;
+  // uniform per-component bases and a 32-bit voxel offset: loads and stores
+  // take the scalar-base + 32-bit-offset form
+  const unsigned v0 = (unsigned)(line0 * N);
+  const T scale = T(1.0 / ((double)a.nx * a.ny * a.nz));
+  T* rb = a.r + fo;
+  T* pb = a.p + fo;
+  T* xb = a.x + fo;
+  const T* tb = a.tab + (long long)prob * 2 * nv;
+  const T* nb = a.tn + (long long)prob * 6 * nv;
+  double s0 = 0.0, s1 = 0.0;  // CG: p . C p and r . r; evaluation: f . f
+  const int w = tid;
+  if (w < NL * N / 4) {
+    const int e = 4 * w;
+    const int li = e / N;
+    const int xv = e - li * N;
+    T out[4][2 * NP];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int c = 0; c < 2 * NP; ++c) out[j][c] = T(0);
+    if (li < nvl) {
+      const unsigned v = v0 + (unsigned)e;
+      if (!cg) {
+        s0 = x_load_field<T, C>(a.f + fo, nv, v, out);
+      } else {
+        // r -= alpha A p, p = r + beta p, and the deferred step x += alpha p.
+        // Every load of the work item is issued before the first store (one
+        // memory round trip instead of one per component).
+        Q4<T> rq[C], pq[C], xq[C];
+        if (!first) {  // uniform over the block
+#pragma unroll
+          for (int c = 0; c < C; ++c) {
+            rq[c] = ld4(at(rb + c * nv, v));
+            pq[c] = ld4(at(pb + c * nv, v));
+            xq[c] = ld4(at(xb + c * nv, v));
+          }
+        }
+        Q4<T> ca, cb;
+        if constexpr (C == 6) {
+          ca = ld4(at(tb, v));
+          cb = ld4(at(tb + nv, v));
+        }
+        const uchar4 ph = *reinterpret_cast<const uchar4*>(at(phase, v));
+        T pv[C][4];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          T g[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const c2<T> z = buf[(li * NP + (c >> 1)) * SP + xv + j];
+            g[j] = ((c & 1) ? z.y : z.x) * scale;
+          }
+          T rn[4];
+          if (first) {  // g is the projected residual stress
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pv[c][j] = rn[j] = -g[j];
+          } else {
+            T xn[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              rn[j] = rq[c].v[j] - alpha * g[j];
+              pv[c][j] = rn[j] + beta * pq[c].v[j];
+              xn[j] = xq[c].v[j] + alpha * pq[c].v[j];
+            }
+            st4(at(xb + c * nv, v), xn);
+          }
+          st4(at(rb + c * nv, v), rn);
+          st4(at(pb + c * nv, v), pv[c]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) s1 += (double)rn[j] * (double)rn[j];
+        }
+        const int phs[4] = {ph.x, ph.y, ph.z, ph.w};
+        if constexpr (C == 6) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const T tr3 = (pv[0][j] + pv[1][j] + pv[2][j]) * T(1.0 / 3.0);
+            const T sph = (ptab[phs[j]] - ca.v[j]) * tr3;
+#pragma unroll
+            for (int c = 0; c < 6; ++c) out[j][c] = ca.v[j] * pv[c][j];
+            out[j][0] += sph;
+            out[j][1] += sph;
+            out[j][2] += sph;
+          }
+          if (cb.v[0] != T(0) || cb.v[1] != T(0) || cb.v[2] != T(0) || cb.v[3] != T(0)) {
+            T nd[6][4];
+#pragma unroll
+            for (int c = 0; c < 6; ++c) {
+              const Q4<T> q = ld4(at(nb + c * nv, v));
+#pragma unroll
+              for (int j = 0; j < 4; ++j) nd[c][j] = q.v[j];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              if (cb.v[j] == T(0)) continue;
+              T dot = T(0);
+#pragma unroll
+              for (int c = 0; c < 6; ++c) dot += nd[c][j] * pv[c][j];
+#pragma unroll
+              for (int c = 0; c < 6; ++c) out[j][c] += cb.v[j] * dot * nd[c][j];
+            }
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const T kap = ptab[phs[j]];
+#pragma unroll
+            for (int c = 0; c < C; ++c) out[j][c] = kap * pv[c][j];
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int c = 0; c < C; ++c) s0 += (double)pv[c][j] * (double)out[j][c];
+      }
+    }
+    // each work item overwrites the staged values that it alone has read
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) buf[(li * NP + q) * SP + xv + j] = mk(out[j][2 * q], out[j][2 * q + 1]);
+  }
+  double s[2] = {s0, s1};
+  block_sum<2>(s, red);
+  if (tid == 0) {
+    a.part[part_index(prob, 0, blk, a.maxblk)] = s[0];
+    a.part[part_index(prob, 1, blk, a.maxblk)] = s[1];
+  }
+  __syncthreads();
+  x_forward_lines<T, C, N, NL>(a, prob, line0, nvl, tw, buf);
 }
 
 }  // namespace hom

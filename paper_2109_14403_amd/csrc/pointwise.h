@@ -64,13 +64,6 @@ constexpr int MECH_SUMS = 14;
 constexpr double FD_H_EPS = 1e-6;
 constexpr double FD_H_THETA = 1e-3;
 
-struct Limits {
-  double tol;
-  int max_newton;   // Newton: residual evaluations; basic: iterations
-  int max_krylov;
-  int linear;       // 1: CG solves to the tolerance at once
-};
-
 }  // namespace hom
 
 // host launchers (pointwise.hip)

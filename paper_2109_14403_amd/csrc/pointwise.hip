@@ -34,7 +34,7 @@ __global__ void __launch_bounds__(PT_THREADS) k_init(Pt<T> a, int basic, int kee
     c.mode = basic ? M_BASIC : M_EVAL;
     c.newton_it = 0;
     c.cg_it = 0;
-    c.cg_ready = 0;
+    c.cg_bad = 0;
     c.pending = 0;
     c.status = 0;
     c.pipelines = 0;
@@ -402,7 +402,7 @@ __global__ void __launch_bounds__(PT_THREADS) k_init_linear(Pt<T> a) {
   if (blk == 0 && threadIdx.x == 0) {
     Ctl& c = a.ctl[prob];
     c.mode = M_EVAL;
-    c.newton_it = c.cg_it = c.cg_ready = c.pending = c.status = c.pipelines = c.krylov = 0;
+    c.newton_it = c.cg_it = c.cg_bad = c.pending = c.status = c.pipelines = c.krylov = 0;
     c.rr = c.alpha = c.beta = c.res = c.fnorm = c.cg_target = 0.0;
   }
   const long long nv = a.nvox;
@@ -607,73 +607,31 @@ __device__ __forceinline__ void sum_parts(const double* part, int maxblk, int nb
   __syncthreads();
 }
 
+// End of a fixed-point iteration (the Newton-CG state moves in the y and z
+// passes).
 __global__ void __launch_bounds__(RED_THREADS) k_reduce_a(Ctl* ctl, const double* part, int maxblk, int nblk,
                                                            Limits lim) {
   __shared__ double red[2 * 16];
   __shared__ double s[2];
   const int prob = blockIdx.x;
   Ctl& c = ctl[prob];
-  const int mode = c.mode;
-  if (!(mode == M_EVAL || mode == M_BASIC || (mode == M_CG && c.cg_ready))) return;
+  if (c.mode != M_BASIC) return;
   sum_parts<2>(part, maxblk, nblk, prob, s, red);
   if (threadIdx.x != 0) return;
   c.pipelines += 1;
-  if (mode == M_CG) {
-    // after the CG update of the x-inverse pass: s[0] = r.r of the new residual
-    const double rn = s[0];
-    c.beta = c.rr > 0.0 ? rn / c.rr : 0.0;
-    c.rr = rn;
-    c.cg_it += 1;
-    c.krylov += 1;
-    c.cg_ready = 0;
-    if (!isfinite(rn)) {
-      c.mode = M_FAIL;
-      c.status = -4;
-    } else if (rn <= c.cg_target || c.cg_it >= lim.max_krylov) {
-      c.mode = M_EVAL;
-      c.pending = 1;
-    }
-  } else if (mode == M_EVAL) {
-    const double rr = s[0], ff = s[1];
-    const double res = ff > 0.0 ? sqrt(rr / ff) : 0.0;
-    c.res = res;
-    c.fnorm = sqrt(ff);
-    c.newton_it += 1;
-    c.pending = 0;
-    if (!isfinite(res)) {
-      c.mode = M_FAIL;
-      c.status = -4;
-    } else if (res <= lim.tol) {
-      c.mode = M_DONE;
-      c.status = 1;
-    } else if (c.newton_it > lim.max_newton) {
-      c.mode = M_FAIL;
-      c.status = -3;
-    } else {
-      const double eta = lim.linear ? 0.0 : fmin(0.1, res);
-      const double tgt = fmax(eta * sqrt(rr), 0.5 * lim.tol * sqrt(ff));
-      c.cg_target = tgt * tgt;
-      c.rr = rr;
-      c.cg_it = 0;
-      c.cg_ready = 0;
-      c.beta = 0.0;
-      c.mode = M_CG;
-    }
-  } else {  // basic scheme
-    const double dd = s[0], xx = s[1];
-    const double err = xx > 0.0 ? sqrt(dd / xx) : 0.0;
-    c.res = err;
-    c.newton_it += 1;
-    if (!isfinite(err)) {
-      c.mode = M_FAIL;
-      c.status = -4;
-    } else if (err <= lim.tol) {
-      c.mode = M_DONE;
-      c.status = 1;
-    } else if (c.newton_it >= lim.max_newton) {
-      c.mode = M_FAIL;
-      c.status = -3;
-    }
+  const double dd = s[0], xx = s[1];
+  const double err = xx > 0.0 ? sqrt(dd / xx) : 0.0;
+  c.res = err;
+  c.newton_it += 1;
+  if (!isfinite(err)) {
+    c.mode = M_FAIL;
+    c.status = -4;
+  } else if (err <= lim.tol) {
+    c.mode = M_DONE;
+    c.status = 1;
+  } else if (c.newton_it >= lim.max_newton) {
+    c.mode = M_FAIL;
+    c.status = -3;
   }
 }
 

@@ -35,6 +35,7 @@ enum KernelKind {
   K_HIST,
   K_COMMIT,
   K_REDOUT,
+  K_XMID,
   K_COUNT
 };
 extern const char* const kKernelNames[2 * K_COUNT];

@@ -13,9 +13,10 @@
 namespace hom {
 
 const char* const kKernelNames[2 * K_COUNT] = {
-    "init",     "eval",   "xfwd",   "yfwd",       "zgreen",   "yinv",    "xinv",   "reduce_a", "history",
-    "commit",   "reduce_out", "t.init", "t.eval",  "t.xfwd",   "t.yfwd",  "t.zgreen", "t.yinv", "t.xinv",
-    "t.reduce_a", "t.history", "t.commit", "t.reduce_out"};
+    "init",     "eval",   "xfwd",   "yfwd",   "zgreen",   "yinv",   "xinv",   "reduce_a",   "history",
+    "commit",   "reduce_out", "xmid",
+    "t.init",   "t.eval", "t.xfwd", "t.yfwd", "t.zgreen", "t.yinv", "t.xinv", "t.reduce_a", "t.history",
+    "t.commit", "t.reduce_out", "t.xmid"};
 
 void fail(int code, const std::string& msg) { throw Error{code, msg}; }
 
@@ -223,6 +224,10 @@ LaunchInfo run_xinv(const Pipe<T>& a, hipStream_t s, bool dry) {
   HOM_DISPATCH(a.nx, (xinv_launch<T, NN>(a, s, dry)))
 }
 template <typename T>
+LaunchInfo run_xmid(const Pipe<T>& a, hipStream_t s, bool dry) {
+  HOM_DISPATCH(a.nx, (xmid_launch<T, NN>(a, s, dry)))
+}
+template <typename T>
 LaunchInfo run_ypass(const Pipe<T>& a, int sched, int inverse, hipStream_t s, bool dry) {
   HOM_DISPATCH(a.ny, (ypass_launch<T, NN>(a, sched, inverse, s, dry)))
 }
@@ -281,7 +286,7 @@ struct Group {
   int* cbase = nullptr;
   int* npa_d = nullptr;
   std::vector<int> npa;
-  int xfblocks = 1, xiblocks = 1;  // x-forward / x-inverse work-groups per problem
+  int xmblocks = 1, xiblocks = 1;  // x-middle / x-inverse work-groups per problem
   // captured chunks: [0] mechanics, [1] conduction, [2] linearized mechanics
   // (tangent strain columns), [3] linearized mechanics with a source (tangent
   // temperature column)
@@ -382,10 +387,11 @@ struct Group {
     // (many short work-groups) up to 65536 groups.
     cm_bpp = (int)std::min<long long>((nvox + 255) / 256, std::max<long long>(1, 65536 / nprob));
     cm_bpp = std::max(cm_bpp, pt_bpp);
-    const int nlf = x_lines(nx, sizeof(T) == 8, true), nli = x_lines(nx, sizeof(T) == 8, false);
-    xfblocks = (ny * nz + nlf - 1) / nlf;
+    const int nlm = x_lines(nx, sizeof(T) == 8, true), nli = x_lines(nx, sizeof(T) == 8, false);
+    xmblocks = (ny * nz + nlm - 1) / nlm;
     xiblocks = (ny * nz + nli - 1) / nli;
-    maxblk = std::max(pt_bpp, std::max(xfblocks, xiblocks));
+    // the z pass: one partial a work-group, most with the narrowest tile
+    maxblk = std::max(std::max(pt_bpp, ny * ((P + 1) / 2)), std::max(xmblocks, xiblocks));
     // the commit of the internal variables: one partial a block of 256 voxels
     if (with_state && nstate > 0) maxblk = std::max(maxblk, commit_voxel_blocks(nvox));
     part = dalloc<double>((size_t)nprob * maxblk * NPART);
@@ -442,7 +448,9 @@ struct Group {
       a.ilen[d] = 1.0 / len[d];
     }
     a.green = green;
-    a.alpha_blocks = 0;
+    a.xblocks = 0;
+    a.zblocks = 0;
+    a.lim = Limits{};
     return a;
   }
 
@@ -715,7 +723,8 @@ class BatchT : public BatchImpl {
     }
     LaunchInfo lx = run_xfwd<T>(a, stream, true);
     LaunchInfo li = run_xinv<T>(a, stream, true);
-    if (!launch_ok(lx) || !launch_ok(li)) fail(HOM_E_UNSUPPORTED, "x-pass does not fit the work-group limits");
+    LaunchInfo lm = run_xmid<T>(a, stream, true);
+    if (!launch_ok(lx) || !launch_ok(li) || !launch_ok(lm)) fail(HOM_E_UNSUPPORTED, "x-pass does not fit the work-group limits");
   }
 
   Limits limits(int phys) const {
@@ -738,11 +747,16 @@ class BatchT : public BatchImpl {
     const int green = phys == 0 ? (basic ? G_GAMMA0 : (rot ? G_PROJ_ROT : G_PROJ))
                                 : (basic ? G_GAMMA_TH : (rot ? G_GRADPROJ_ROT : G_GRADPROJ));
     Pipe<T> a = G.pipe(phys, green);
-    if (!basic) a.alpha_blocks = G.xfblocks;  // the z pass forms the CG step length
     Pt<T> q = G.pt(phys);
     const int C = phys == 0 ? 6 : 3;
     Limits lim = limits(phys);
     if (variant >= 2) lim.linear = 1;
+    if (!basic) {  // the y and z passes drive the Newton-CG state
+      a.xblocks = G.xmblocks;
+      const int tx = schedule_tile(G.txz[phys]);
+      a.zblocks = G.ny * ((G.P + tx - 1) / tx);
+      a.lim = lim;
+    }
     Ctl* ctl = phys == 0 ? G.ctl_m : G.ctl_t;
     prof.begin(K_EVAL, stream);
     if (variant >= 2) {
@@ -752,8 +766,11 @@ class BatchT : public BatchImpl {
       launch_eval<T>(q, C, stream);
     }
     prof.end(stream);
-    prof.begin(K_XFWD, stream);
-    run_xfwd<T>(a, stream);
+    prof.begin(basic ? K_XFWD : K_XMID, stream);
+    if (basic)
+      run_xfwd<T>(a, stream);
+    else
+      run_xmid<T>(a, stream);
     prof.end(stream);
     prof.begin(K_YFWD, stream);
     run_ypass<T>(a, G.txy[phys], 0, stream);
@@ -764,6 +781,7 @@ class BatchT : public BatchImpl {
     prof.begin(K_YINV, stream);
     run_ypass<T>(a, G.txy[phys], 1, stream);
     prof.end(stream);
+    if (!basic) return;
     prof.begin(K_XINV, stream);
     run_xinv<T>(a, stream);
     prof.end(stream);
