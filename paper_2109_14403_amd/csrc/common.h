@@ -5,7 +5,9 @@
 //   spectra          [prob][kz][ky][kx][comp]         complex, kx = 0..nx/2,
 //                                                     components interleaved so
 //                                                     that a tile of kx columns
-//                                                     is one contiguous segment
+//                                                     is one contiguous segment;
+//                    [prob][kx][kz][ky][comp]         where whole planes of one kx
+//                                                     are transformed in LDS
 //   PA66 state       [prob][var][voxel]               FP64, var = eps_p, eps_vp(6),
 //                                                     eps_v_i(6) for i = 1..N
 // Strains and stresses are Mandel vectors (11, 22, 33, sqrt2 23, sqrt2 13, sqrt2 12).
@@ -46,6 +48,8 @@ struct Ctl {
   int status;       // 0 running, 1 converged, <0 failure code
   int pipelines;    // FFT pipeline applications so far
   int krylov;       // total CG iterations
+  int ticket;       // work-groups of a plane pass that have left their partial sums
+  int pad;
   double rr;        // r.r of the current CG residual
   double alpha, beta;
   double res;       // relative residual of the last evaluation
@@ -112,7 +116,9 @@ struct Pipe {
   T* p;
   const T* tab;             // tangent factors [prob][2][nvox] (mechanics)
   const T* tn;              // tangent direction [prob][6][nvox] (mechanics)
-  c2<T>* spec;              // [prob][nz][ny][PS][C], kx < P used
+  c2<T>* spec;              // [prob][nz][ny][PS][C], kx < P used; with planes set
+                            // [prob][P][nz][ny][C]
+  int planes;               // 1: kx-major spectra, transformed plane by plane (k_yzplane)
   Ctl* ctl;
   const ProbInc* inc;
   double* part;             // [prob][NPART][maxblk]

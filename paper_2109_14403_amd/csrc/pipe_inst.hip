@@ -131,7 +131,49 @@ LaunchInfo zgreen_v(const Pipe<T>& a, int tx, hipStream_t s, bool dry) {
   return zgreen_c<T, C, N, 4, V>(a, s, dry);
 }
 
+template <typename T, int C, int NY, int NZ>
+LaunchInfo yzplane_c(const Pipe<T>& a, hipStream_t s, bool dry) {
+  LaunchInfo li;
+  li.threads = PlaneCfg<T, C, NY, NZ>::THREADS;
+  li.blocks = a.nprob * (a.xblocks > 0 ? a.P + 1 : a.P);
+  li.lds = plane_lds(NY, NZ, C, sizeof(T) == 8);
+  {
+    static bool attr = false;
+    if (!attr && li.lds > 65536) {
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_yzplane<T, C, NY, NZ>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      (void)hipGetLastError();
+      attr = true;
+    }
+  }
+  if (!dry) {
+    hipLaunchKernelGGL((k_yzplane<T, C, NY, NZ>), dim3(li.blocks), dim3(li.threads), li.lds, s, a);
+  }
+  return li;
+}
+// the plane sizes ny x N that fit
+template <typename T, int N, int NY>
+bool yzplane_try(const Pipe<T>& a, hipStream_t s, bool dry, LaunchInfo& li) {
+  if constexpr (plane_fits(NY, N, sizeof(T) == 8)) {
+    if (a.ny == NY) {
+      li = a.C == 6 ? yzplane_c<T, 6, NY, N>(a, s, dry) : yzplane_c<T, 3, NY, N>(a, s, dry);
+      return true;
+    }
+  }
+  return false;
+}
+
 }  // namespace
+
+template <typename T, int N>
+LaunchInfo yzplane_launch(const Pipe<T>& a, hipStream_t s, bool dry) {
+  LaunchInfo li{0, 1 << 20, 0};  // no such launch
+  (void)(yzplane_try<T, N, 16>(a, s, dry, li) || yzplane_try<T, N, 24>(a, s, dry, li) ||
+         yzplane_try<T, N, 32>(a, s, dry, li) || yzplane_try<T, N, 48>(a, s, dry, li) ||
+         yzplane_try<T, N, 64>(a, s, dry, li) || yzplane_try<T, N, 96>(a, s, dry, li) ||
+         yzplane_try<T, N, 128>(a, s, dry, li));
+  return li;
+}
 
 template <typename T, int N>
 LaunchInfo xfwd_launch(const Pipe<T>& a, hipStream_t s, bool dry) {
@@ -172,6 +214,7 @@ LaunchInfo zgreen_launch(const Pipe<T>& a, int sched, hipStream_t s, bool dry) {
   template LaunchInfo xfwd_launch<T, HOM_N>(const Pipe<T>&, hipStream_t, bool);             \
   template LaunchInfo xinv_launch<T, HOM_N>(const Pipe<T>&, hipStream_t, bool);             \
   template LaunchInfo xmid_launch<T, HOM_N>(const Pipe<T>&, hipStream_t, bool);             \
+  template LaunchInfo yzplane_launch<T, HOM_N>(const Pipe<T>&, hipStream_t, bool);          \
   template LaunchInfo ypass_launch<T, HOM_N>(const Pipe<T>&, int, int, hipStream_t, bool);  \
   template LaunchInfo zgreen_launch<T, HOM_N>(const Pipe<T>&, int, hipStream_t, bool);
 HOM_INST(float)

@@ -49,6 +49,27 @@ constexpr int schedule_plan(int s) { return s >> 4; }
 constexpr int kScheduleChoices[] = {schedule(2, 0), schedule(4, 0), schedule(8, 0),
                                     schedule(2, 1), schedule(4, 1), schedule(8, 1)};
 
+// The plane pass holds a whole ny x nz plane of one kx, all components, in LDS
+// (rows of plane_row complex values: padding spreads the rows of a y transform
+// over the banks), and the twiddles of both axes.
+constexpr int plane_row(int ny, int C) { return (ny + 1) * C; }
+constexpr size_t plane_lds(int ny, int nz, int C, bool fp64) {
+  return ((size_t)nz * plane_row(ny, C) + ny + nz) * (fp64 ? 16 : 8);
+}
+constexpr bool plane_fits(int ny, int nz, bool fp64) { return plane_lds(ny, nz, 6, fp64) <= 120 * 1024; }
+// The plane pass puts a plane on one CU, the three separate passes spread it
+// over the chip but make three trips and two more launches. Measured:
+// single cells (increments of 32 x ny x nz, 17 planes on 256 CUs) in FP32 16^2
+// 1.33, 24^2 1.26, 32^2 1.19, 24 x 48 1.16, 64 x 24 1.05, 96 x 16 1.11, 64 x 32
+// (98 KB) 1.04 times as fast, 48^2 (113 KB) 0.93; in FP64 16^2 1.22, 24^2
+// (58 KB) 1.15, 32^2 (101 KB) 0.98, 24 x 48 0.90. Batches, FP32: 8 and 64
+// problems of 24^3 1.18 and 1.05, of 32^3 1.13 and 1.14, 8 and 32 of 48^3 (200
+// and 800 planes) 1.12 and 1.10. So large planes need enough of them.
+inline bool plane_pass(int ny, int nz, bool fp64, long long planes) {
+  return plane_fits(ny, nz, fp64) &&
+         (plane_lds(ny, nz, 6, fp64) <= (size_t)(fp64 ? 64 : 104) * 1024 || planes >= 128);
+}
+
 struct LaunchInfo {
   int blocks;
   int threads;
@@ -65,6 +86,8 @@ template <typename T, int N>
 LaunchInfo ypass_launch(const Pipe<T>& a, int sched, int inverse, hipStream_t s, bool dry);
 template <typename T, int N>
 LaunchInfo zgreen_launch(const Pipe<T>& a, int sched, hipStream_t s, bool dry);
+template <typename T, int N>  // N = nz; a.ny one that fits
+LaunchInfo yzplane_launch(const Pipe<T>& a, hipStream_t s, bool dry);
 
 template <typename T>
 LaunchInfo run_xfwd(const Pipe<T>& a, hipStream_t s, bool dry = false);
@@ -76,5 +99,7 @@ template <typename T>
 LaunchInfo run_ypass(const Pipe<T>& a, int sched, int inverse, hipStream_t s, bool dry = false);
 template <typename T>
 LaunchInfo run_zgreen(const Pipe<T>& a, int sched, hipStream_t s, bool dry = false);
+template <typename T>
+LaunchInfo run_yzplane(const Pipe<T>& a, hipStream_t s, bool dry = false);
 
 }  // namespace hom

@@ -10,6 +10,8 @@
 //   zgreen forward transform along z, Green operator per frequency on all
 //          components, inverse transform along z.
 //   ypass  inverse along y.
+// or, where a plane of one kx fits into LDS,
+//   yzplane  the y and z transforms both ways with the Green operator between.
 //
 // The CG scalars are known before a pass needs them: alpha = r.r / p.C p from
 // the partial sums of the x pass (p is compatible and the projector
@@ -39,6 +41,7 @@
 // once.
 #pragma once
 #include "common.h"
+#include "pipe_launch.h"
 
 namespace hom {
 
@@ -286,9 +289,9 @@ constexpr int x_threads() {
 }
 
 // Forward transforms of the staged lines (rows of SP complex values in buf,
-// two real components each) and the unpacked half spectra [line][kx][comp],
-// rows PS * C apart in memory, with 16-byte stores. Starts and ends inside one
-// work-group; the caller has synchronized after its last write to buf.
+// two real components each) and the unpacked half spectra, [line][kx][comp]
+// with rows PS * C apart or [kx][line][comp] (a.planes). The caller has
+// synchronized after its last write to buf.
 template <typename T, int C, int N, int NL>
 __device__ __forceinline__ void x_forward_lines(const Pipe<T>& a, int prob, int line0, int nvl, const c2<T>* tw,
                                                 c2<T>* buf) {
@@ -316,22 +319,43 @@ __device__ __forceinline__ void x_forward_lines(const Pipe<T>& a, int prob, int 
   __syncthreads();
 
   // unpack the two real transforms of each complex line and write the block's
-  // contiguous run of half spectra [line][kx][comp] with 16-byte stores
-  const int rowp = a.PS * C;
-  c2<T>* spec = a.spec + (long long)prob * a.nz * a.ny * rowp + (long long)line0 * rowp;
+  // half spectra with 16-byte stores
   constexpr int V = 16 / sizeof(c2<T>);
-  const int total = nvl * H * C;
-  auto value = [&](int e) -> c2<T> {
-    const int c = e % C;
-    const int rest = e / C;
-    const int k = rest % H;
-    const int li = rest / H;
+  auto value = [&](int li, int k, int c) -> c2<T> {
     const int q = c >> 1;
     const c2<T> zk = buf[k * L + li * NP + q];
     const c2<T> zm = conjg(buf[((N - k) % N) * L + li * NP + q]);
     const c2<T> val = (c & 1) ? mul_mi(zk - zm) : (zk + zm);
     return cscale(val, T(0.5));
   };
+  if (a.planes) {
+    // the block's lines are contiguous in every plane of one kx
+    const long long plane = (long long)a.ny * a.nz * C;
+    c2<T>* spec = a.spec + (long long)prob * a.P * plane + (long long)line0 * C;
+    for (int i = tid; i < H * NL * C / V; i += nth) {
+      const int e = V * i;
+      const int k = e / (NL * C);
+      const int rest = e - k * (NL * C);
+      const int li = rest / C;
+      const int c = rest - li * C;
+      if (li >= nvl) continue;
+      if constexpr (V == 2 && C % 2 == 0) {
+        const c2<T> u0 = value(li, k, c), u1 = value(li, k, c + 1);
+        const nt_f4 t = {u0.x, u0.y, u1.x, u1.y};
+        *reinterpret_cast<nt_f4*>(spec + k * plane + rest) = t;
+      } else {
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+          const int r1 = rest + j;
+          spec[k * plane + r1] = value(r1 / C, k, r1 % C);
+        }
+      }
+    }
+    return;
+  }
+  const int rowp = a.PS * C;
+  c2<T>* spec = a.spec + (long long)prob * a.nz * a.ny * rowp + (long long)line0 * rowp;
+  const int total = nvl * H * C;
   // rows are rowp apart; the (kx, comp) entries of one row are contiguous
   if constexpr (V == 2 && C % 2 == 0) {
     // pairs of components of one kx: 16-byte aligned stores (rowp * 8 is a
@@ -339,14 +363,18 @@ __device__ __forceinline__ void x_forward_lines(const Pipe<T>& a, int prob, int 
     for (int i = tid; i < total / 2; i += nth) {
       const int e = 2 * i;
       const int li = e / (H * C);
-      const c2<T> u0 = value(e), u1 = value(e + 1);
+      const int rest = e - li * H * C;
+      const int k = rest / C;
+      const c2<T> u0 = value(li, k, rest - k * C), u1 = value(li, k, rest - k * C + 1);
       const nt_f4 t = {u0.x, u0.y, u1.x, u1.y};
-      __builtin_nontemporal_store(t, reinterpret_cast<nt_f4*>(spec + li * rowp + (e - li * H * C)));
+      __builtin_nontemporal_store(t, reinterpret_cast<nt_f4*>(spec + li * rowp + rest));
     }
   } else {
     for (int e = tid; e < total; e += nth) {
       const int li = e / (H * C);
-      stc(spec + li * rowp + (e - li * H * C), value(e));
+      const int rest = e - li * H * C;
+      const int k = rest / C;
+      stc(spec + li * rowp + rest, value(li, k, rest - k * C));
     }
   }
 }
@@ -554,6 +582,70 @@ __global__ void __launch_bounds__((N / Plan<N, V>::M) * TX * C) k_ypass(Pipe<T> 
   }
 }
 
+// The Green operator of a pipeline at one frequency.
+template <typename T>
+struct GreenOp {
+  const ProbInc& inc;
+  T cs = T(1), hcn = T(0.5);
+  bool rot;
+  __device__ __forceinline__ GreenOp(const Pipe<T>& a, int prob) : inc(a.inc[prob]) {
+    if (a.green == G_GAMMA0) {
+      cs = T(1.0 / (2.0 * inc.mu0));
+      hcn = T(0.5 * (inc.lam0 + inc.mu0) / (inc.mu0 * (inc.lam0 + 2.0 * inc.mu0)));
+    } else if (a.green == G_GAMMA_TH) {
+      cs = T(1.0 / inc.kappa0);
+    }
+    rot = (a.green == G_PROJ_ROT || a.green == G_GRADPROJ_ROT);
+    eval = a.ctl[prob].mode == M_EVAL;
+  }
+  bool eval;
+  // v: the components at frequency (kx, ky, kz); fa, fb: the x and y parts of
+  // the frequency vector; twx, twy, twz: forward twiddles of the axes
+  template <int C>
+  __device__ __forceinline__ void apply(const Pipe<T>& a, c2<T>* v, int kx, int ky, int kz, T fa, T fb,
+                                        const c2<T>* twx, const c2<T>* twy, const c2<T>* twz) const {
+    T n0 = T(0), n1 = T(0), n2 = T(0);
+    c2<T> nc[3];
+    bool zero;
+    if (rot) {
+      rotated_direction<T>(twx[kx], twy[ky], twz[kz], a.nx, a.ny, a.nz, a.len, nc, zero);
+    } else {
+      const T fc = frequency_component<T>(kz, a.nz, T(a.ilen[2]));
+      const T m2 = fc * fc + (fa * fa + fb * fb);
+      zero = !(m2 > T(0));
+      const T inv = zero ? T(0) : inv_norm(m2);
+      n0 = fa * inv;
+      n1 = fb * inv;
+      n2 = fc * inv;
+    }
+    if (zero) {
+      // the mean: removed, except for the stress-controlled components of
+      // mixed conditions, whose mean strain is an unknown of the iteration
+      // (the projector's zero-frequency block is the mask). A residual
+      // evaluation compares the mean stress with the prescribed one (the
+      // spectrum is unnormalized: the mean mode holds nvox <sigma>).
+      const bool mean = (kx == 0 && ky == 0 && kz == 0);
+#pragma unroll
+      for (int cc = 0; cc < C; ++cc) {
+        if (C == 6 && mean && ((inc.smask >> cc) & 1))
+          v[cc] = mk(v[cc].x - (eval ? T((double)a.nvox * inc.S[cc]) : T(0)), T(0));
+        else
+          v[cc] = mk(T(0), T(0));
+      }
+    } else if (rot) {
+      if constexpr (C == 6)
+        green_mech_herm<T>(v, nc);
+      else
+        green_grad_herm<T>(v, nc);
+    } else {
+      if constexpr (C == 6)
+        green_mech<T>(v, n0, n1, n2, cs, hcn);
+      else
+        green_grad<T>(v, n0, n1, n2, cs);
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------
 // z forward + Green operator + z inverse on tiles of TX kx columns
 // ---------------------------------------------------------------------------
@@ -600,22 +692,12 @@ __global__ void __launch_bounds__((N / Plan<N, V>::M) * TX * C)
   for (int m = 0; m < M; ++m) buf[(t + G * m) * L + l] = r[m];
   __syncthreads();
 
-  const ProbInc& inc = a.inc[prob];
-  T cs = T(1), hcn = T(0.5);
-  if (a.green == G_GAMMA0) {
-    cs = T(1.0 / (2.0 * inc.mu0));
-    hcn = T(0.5 * (inc.lam0 + inc.mu0) / (inc.mu0 * (inc.lam0 + 2.0 * inc.mu0)));
-  } else if (a.green == G_GAMMA_TH) {
-    cs = T(1.0 / inc.kappa0);
-  }
-  const bool rot = (a.green == G_PROJ_ROT || a.green == G_GRADPROJ_ROT);
+  GreenOp<T> op(a, prob);
   // every index of this thread has the same kx (nth is a multiple of TX):
   // the x and y parts of the frequency are fixed, the z part varies
   const int kxx = kb * TX + tid % TX;
   const T fa = frequency_component<T>(kxx, a.nx, T(a.ilen[0]));
   const T fb = frequency_component<T>(ky, a.ny, T(a.ilen[1]));
-  const T fab2 = fa * fa + fb * fb;
-  const T il2 = T(a.ilen[2]);
   static_assert(((N / Plan<N, V>::M) * TX * C) % TX == 0, "thread count must be a multiple of TX");
   // Parseval sum of the operator's result; a half spectrum stands for its
   // mirror image too, except at kx = 0 and the Nyquist index
@@ -625,49 +707,10 @@ __global__ void __launch_bounds__((N / Plan<N, V>::M) * TX * C)
     const int kz = idx / TX;
     const int kxi = idx - kz * TX;
     if (kxx >= P) break;
-    T n0 = T(0), n1 = T(0), n2 = T(0);
-    c2<T> nc[3];
-    bool zero;
-    if (rot) {
-      rotated_direction<T>(a.twx[kxx], a.twy[ky], tw[kz], a.nx, a.ny, a.nz, a.len, nc, zero);
-    } else {
-      const T fc = frequency_component<T>(kz, a.nz, il2);
-      const T m2 = fc * fc + fab2;
-      zero = !(m2 > T(0));
-      const T inv = zero ? T(0) : inv_norm(m2);
-      n0 = fa * inv;
-      n1 = fb * inv;
-      n2 = fc * inv;
-    }
     c2<T> v[C];
 #pragma unroll
     for (int cc = 0; cc < C; ++cc) v[cc] = buf[kz * L + kxi * C + cc];
-    if (zero) {
-      // the mean: removed, except for the stress-controlled components of
-      // mixed conditions, whose mean strain is an unknown of the iteration
-      // (the projector's zero-frequency block is the mask). A residual
-      // evaluation compares the mean stress with the prescribed one (the
-      // spectrum is unnormalized: the mean mode holds nvox <sigma>).
-      const bool mean = (kxx == 0 && ky == 0 && kz == 0);
-      const bool eval = a.ctl[prob].mode == M_EVAL;
-#pragma unroll
-      for (int cc = 0; cc < C; ++cc) {
-        if (C == 6 && mean && ((inc.smask >> cc) & 1))
-          v[cc] = mk(v[cc].x - (eval ? T((double)a.nvox * inc.S[cc]) : T(0)), T(0));
-        else
-          v[cc] = mk(T(0), T(0));
-      }
-    } else if (rot) {
-      if constexpr (C == 6)
-        green_mech_herm<T>(v, nc);
-      else
-        green_grad_herm<T>(v, nc);
-    } else {
-      if constexpr (C == 6)
-        green_mech<T>(v, n0, n1, n2, cs, hcn);
-      else
-        green_grad<T>(v, n0, n1, n2, cs);
-    }
+    op.template apply<C>(a, v, kxx, ky, kz, fa, fb, a.twx, a.twy, tw);
 #pragma unroll
     for (int cc = 0; cc < C; ++cc) {
       buf[kz * L + kxi * C + cc] = v[cc];
@@ -691,8 +734,218 @@ __global__ void __launch_bounds__((N / Plan<N, V>::M) * TX * C)
 }
 
 // ---------------------------------------------------------------------------
+// y and z transforms, Green operator and back, on a whole plane of one kx
+// ---------------------------------------------------------------------------
+// Where a plane of all components fits into LDS, one work-group transforms it
+// along z (from and to memory, contiguous accesses) and along y (in LDS) both
+// ways, with the Green operator between: one pass over the spectra instead of
+// three. A line's exchange takes place in the line's own LDS elements.
+// The work-group's vector instructions bound it (no packed FP32; lines spread
+// over the four lanes of a quad with the exchange in registers and a sixth of
+// the barriers took 1.0 to 1.3 times as long, because they take more of them).
+template <int N>
+constexpr int plane_plan = N == 96 ? 1 : 0;  // 12 instead of 24 elements a thread
+template <typename T, int C, int NY, int NZ>
+struct PlaneCfg {
+  using PY = Plan<NY, plane_plan<NY>>;
+  using PZ = Plan<NZ, plane_plan<NZ>>;
+  static constexpr int GY = NY / PY::M, GZ = NZ / PZ::M;
+  static constexpr int LY = NZ * C, LZ = NY * C;  // lines along y and z
+  // threads: all lines at once if the registers of a thread's elements allow
+  // it, else in rounds of whole lines
+  static constexpr int MOST = sizeof(T) == 8 ? 512 : 1024;
+  static constexpr int rounds(int lines, int g, int threads) { return (lines + threads / g - 1) / (threads / g); }
+  static constexpr int need(int lines, int g) {
+    return g * ((lines + rounds(lines, g, MOST) - 1) / rounds(lines, g, MOST));
+  }
+  static constexpr int THREADS = ((need(LY, GY) > need(LZ, GZ) ? need(LY, GY) : need(LZ, GZ)) + 63) / 64 * 64;
+  static constexpr int RY = rounds(LY, GY, THREADS), RZ = rounds(LZ, GZ, THREADS);
+  static constexpr int NLY = (LY + RY - 1) / RY, NLZ = (LZ + RZ - 1) / RZ;  // lines of a round
+  static constexpr int SZ = plane_row(NY, C);                               // LDS row of one z
+  // thread tid's place in round i: line and position in it (off lines: idle)
+  static __device__ __forceinline__ bool y_line(int tid, int i, int& t, int& l) {
+    t = tid / NLY;
+    l = tid - t * NLY + i * NLY;
+    const bool on = t < GY && l < LY;
+    t = on ? t : 0;
+    l = on ? l : 0;
+    __builtin_assume(t < GY);
+    return on;
+  }
+  static __device__ __forceinline__ bool z_line(int tid, int i, int& t, int& l) {
+    t = tid / NLZ;
+    l = tid - t * NLZ + i * NLZ;
+    const bool on = t < GZ && l < LZ;
+    t = on ? t : 0;
+    l = on ? l : 0;
+    __builtin_assume(t < GZ);
+    return on;
+  }
+};
+
+template <typename T, int C, int NY, int NZ>
+__global__ void __launch_bounds__((PlaneCfg<T, C, NY, NZ>::THREADS)) k_yzplane(Pipe<T> a) {
+  using Cfg = PlaneCfg<T, C, NY, NZ>;
+  using PY = typename Cfg::PY;
+  using PZ = typename Cfg::PZ;
+  constexpr int GY = Cfg::GY, GZ = Cfg::GZ, SZ = Cfg::SZ, NTH = Cfg::THREADS, LZ = Cfg::LZ;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  c2<T>* twy = reinterpret_cast<c2<T>*>(smem_raw);
+  c2<T>* twz = twy + NY;
+  c2<T>* S = twz + NZ;
+  __shared__ double red[2 * 16];
+  __shared__ int last;
+  const int P = a.P;
+  const bool drive = a.xblocks > 0;  // Newton-CG: one more work-group a problem forms the step length
+  const int bpp = drive ? P + 1 : P;
+  const int prob = blockIdx.x / bpp;
+  const int kx = blockIdx.x - prob * bpp;
+  Ctl& ctl = a.ctl[prob];
+  if (!pipeline_mode(ctl.mode)) return;
+  const int tid = threadIdx.x;
+  double norm = 0.0;
+  c2<T>* base = a.spec + ((long long)prob * P + min(kx, P - 1)) * (NY * NZ * C);
+  if (kx < P) {
+    c2<T> rz[Cfg::RZ][PZ::M];
+#pragma unroll
+    for (int i = 0; i < Cfg::RZ; ++i) {
+      int t, l;
+      const bool on = Cfg::z_line(tid, i, t, l);
+#pragma unroll
+      for (int m = 0; m < PZ::M; ++m) rz[i][m] = on ? base[(t + GZ * m) * LZ + l] : mk(T(0), T(0));
+    }
+    for (int i = tid; i < NY; i += NTH) twy[i] = a.twy[i];
+    for (int i = tid; i < NZ; i += NTH) twz[i] = a.twz[i];
+    __syncthreads();
+    // z forward
+#pragma unroll
+    for (int i = 0; i < Cfg::RZ; ++i) {
+      int t, l;
+      const bool on = Cfg::z_line(tid, i, t, l);
+      PZ::run(rz[i], t, twz, S, SZ, l, on);
+      __syncthreads();
+      if (on) {
+#pragma unroll
+        for (int m = 0; m < PZ::M; ++m) S[(t + GZ * m) * SZ + l] = rz[i][m];
+      }
+    }
+    __syncthreads();
+    // y forward
+#pragma unroll
+    for (int i = 0; i < Cfg::RY; ++i) {
+      int t, l;
+      const bool on = Cfg::y_line(tid, i, t, l);
+      const int z = l / C, off = z * SZ + (l - z * C);
+      c2<T> r[PY::M];
+#pragma unroll
+      for (int m = 0; m < PY::M; ++m) r[m] = S[off + (t + GY * m) * C];
+      PY::run(r, t, twy, S, C, off, on);
+      __syncthreads();
+      if (on) {
+#pragma unroll
+        for (int m = 0; m < PY::M; ++m) S[off + (t + GY * m) * C] = r[m];
+      }
+    }
+    __syncthreads();
+    {
+      const GreenOp<T> op(a, prob);
+      const T fa = frequency_component<T>(kx, a.nx, T(a.ilen[0]));
+      for (int i = tid; i < NY * NZ; i += NTH) {
+        const int kz = i / NY, ky = i - kz * NY;
+        c2<T>* q = S + kz * SZ + ky * C;
+        c2<T> v[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) v[c] = q[c];
+        op.template apply<C>(a, v, kx, ky, kz, fa, frequency_component<T>(ky, NY, T(a.ilen[1])), a.twx, twy, twz);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          q[c] = v[c];
+          norm += (double)v[c].x * (double)v[c].x + (double)v[c].y * (double)v[c].y;
+        }
+      }
+      // Parseval weight: a half spectrum stands for its mirror image too
+      if (kx != 0 && 2 * kx != a.nx) norm *= 2.0;
+    }
+  }
+  if (drive) {
+    if (kx == P) cg_step_length(a, prob);
+    double s[1] = {norm};
+    block_sum<1>(s, red);
+    if (tid == 0) {
+      // the last work-group of the problem has every partial sum and the step
+      // length, and moves the solver's state while the others transform back
+      double* pp = a.part + part_index(prob, 2, 0, a.maxblk);
+      if (kx < P) __hip_atomic_store(pp + kx, s[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int before = __hip_atomic_fetch_add(&ctl.ticket, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+      last = before == P;
+    }
+    __syncthreads();
+    if (last && tid < 64) {
+      const double* pp = a.part + part_index(prob, 2, 0, a.maxblk);
+      double v = 0.0;
+      for (int i = tid; i < P; i += 64) v += __hip_atomic_load(pp + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+      if (tid == 0) {
+        ctl.ticket = 0;
+        newton_cg_transition(ctl, v / ((double)a.nx * a.ny * a.nz), a.lim);
+      }
+    }
+  }
+  if (kx >= P) return;
+  __syncthreads();
+  // y inverse
+#pragma unroll
+  for (int i = 0; i < Cfg::RY; ++i) {
+    int t, l;
+    const bool on = Cfg::y_line(tid, i, t, l);
+    const int z = l / C, off = z * SZ + (l - z * C);
+    c2<T> r[PY::M];
+#pragma unroll
+    for (int m = 0; m < PY::M; ++m) r[m] = conjg(S[off + (t + GY * m) * C]);
+    PY::run(r, t, twy, S, C, off, on);
+    __syncthreads();
+    if (on) {
+#pragma unroll
+      for (int m = 0; m < PY::M; ++m) S[off + (t + GY * m) * C] = conjg(r[m]);
+    }
+  }
+  __syncthreads();
+  // z inverse
+#pragma unroll
+  for (int i = 0; i < Cfg::RZ; ++i) {
+    int t, l;
+    const bool on = Cfg::z_line(tid, i, t, l);
+    c2<T> r[PZ::M];
+#pragma unroll
+    for (int m = 0; m < PZ::M; ++m) r[m] = conjg(S[(t + GZ * m) * SZ + l]);
+    PZ::run(r, t, twz, S, SZ, l, on);
+    if (on) {
+#pragma unroll
+      for (int m = 0; m < PZ::M; ++m) base[(t + GZ * m) * LZ + l] = conjg(r[m]);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // x inverse: packed complex-to-real transforms (+ post-operation + partial sums)
 // ---------------------------------------------------------------------------
+// Staging access of x_inverse_lines: a pair of FP32 complex values, else one
+// complex value.
+template <typename T, int V>
+struct x_access;
+template <>
+struct x_access<float, 2> {
+  using type = nt_f4;
+};
+template <>
+struct x_access<float, 1> {
+  using type = nt_f2;
+};
+template <>
+struct x_access<double, 1> {
+  using type = nt_d2;
+};
 // The half spectra of a work-group's lines, transformed back: rows of SP
 // complex values in buf (unscaled), two real components each. The launch has
 // NTH threads. Ends synchronized.
@@ -709,41 +962,46 @@ __device__ __forceinline__ void x_inverse_lines(const Pipe<T>& a, int prob, int 
                     L * SP >= N * L,
                 "x-inverse LDS buffer too small");
   const int tid = threadIdx.x;
-  // stage the block's half spectra [line][kx][comp] (rows rowp apart in
-  // memory, packed in LDS)
-  const int rowp = a.PS * C;
-  const c2<T>* spec = a.spec + (long long)prob * a.nz * a.ny * rowp + (long long)line0 * rowp;
-  // all of a thread's loads are issued before the LDS writes
-  if constexpr (sizeof(c2<T>) == 8 && C % 2 == 0) {
-    constexpr int K = (NL * H * C / 2 + NTH - 1) / NTH;
-    const int tot = nvl * H * C / 2;
-    const nt_f4* s4 = reinterpret_cast<const nt_f4*>(spec);
-    nt_f4* d4 = reinterpret_cast<nt_f4*>(buf);
-    nt_f4 t4[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {  // unconditional loads (index clamped in range), no branch between them
-      const int e = 2 * min(tid + k * NTH, tot - 1);
-      const int li = e / (H * C);
-      t4[k] = __builtin_nontemporal_load(s4 + (li * rowp + (e - li * H * C)) / 2);
-    }
-    // unconditional writes too (else the compiler sinks each load into its
-    // write's branch): a clamped thread rewrites the last element's own value
-#pragma unroll
-    for (int k = 0; k < K; ++k) d4[min(tid + k * NTH, tot - 1)] = t4[k];
-  } else {
-    constexpr int K = (NL * H * C + NTH - 1) / NTH;
-    const int tot = nvl * H * C;
-    c2<T> t2[K];
+  // stage the block's half spectra: [line][kx][comp], rows rowp apart in
+  // memory and packed in LDS, or [kx][line][comp] (a.planes). All of a
+  // thread's loads are issued before the LDS writes, with indices clamped in
+  // range and no branch between them; a clamped thread rewrites the last
+  // element's own value (else the compiler sinks each load into its write's
+  // branch).
+  constexpr int V = (sizeof(c2<T>) == 8 && C % 2 == 0) ? 2 : 1;
+  constexpr int K = (NL * H * C / V + NTH - 1) / NTH;
+  using acc_t = typename x_access<T, V>::type;
+  acc_t t4[K];
+  acc_t* d4 = reinterpret_cast<acc_t*>(buf);
+  int tot;
+  if (a.planes) {
+    const long long plane = (long long)a.ny * a.nz * C;
+    const c2<T>* spec = a.spec + (long long)prob * a.P * plane + (long long)line0 * C;
+    tot = NL * H * C / V;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int e = min(tid + k * NTH, tot - 1);
-      const int li = e / (H * C);
-      t2[k] = ldc(spec + li * rowp + (e - li * H * C));
+      const int e = V * min(tid + k * NTH, tot - 1);
+      const int kk = e / (NL * C);
+      const int rest = min(e - kk * (NL * C), nvl * C - V);
+      t4[k] = *reinterpret_cast<const acc_t*>(spec + kk * plane + rest);
     }
+  } else {
+    const int rowp = a.PS * C;
+    const c2<T>* spec = a.spec + (long long)prob * a.nz * a.ny * rowp + (long long)line0 * rowp;
+    tot = nvl * H * C / V;
 #pragma unroll
-    for (int k = 0; k < K; ++k) buf[min(tid + k * NTH, tot - 1)] = t2[k];
+    for (int k = 0; k < K; ++k) {
+      const int e = V * min(tid + k * NTH, tot - 1);
+      const int li = e / (H * C);
+      t4[k] = __builtin_nontemporal_load(reinterpret_cast<const acc_t*>(spec + li * rowp + (e - li * H * C)));
+    }
   }
-  for (int e = nvl * H * C + tid; e < NL * H * C; e += NTH) buf[e] = mk(T(0), T(0));
+#pragma unroll
+  for (int k = 0; k < K; ++k) d4[min(tid + k * NTH, tot - 1)] = t4[k];
+  const int sl = a.planes ? C : H * C;   // LDS strides of a line and of a kx
+  const int sk = a.planes ? NL * C : C;
+  if (!a.planes)
+    for (int e = nvl * H * C + tid; e < NL * H * C; e += NTH) buf[e] = mk(T(0), T(0));
   __syncthreads();
   const bool fw = NTH == G * L || tid < G * L;  // a thread of the line transforms
   const int l = tid % L;
@@ -757,8 +1015,8 @@ __device__ __forceinline__ void x_inverse_lines(const Pipe<T>& a, int prob, int 
     const int p = t + G * m;
     const bool lo = p <= N / 2;
     const int kk = lo ? p : N - p;
-    c2<T> A = buf[(li * H + kk) * C + 2 * q];
-    c2<T> B = (2 * q + 1 < C) ? buf[(li * H + kk) * C + 2 * q + 1] : mk(T(0), T(0));
+    c2<T> A = buf[li * sl + kk * sk + 2 * q];
+    c2<T> B = (2 * q + 1 < C) ? buf[li * sl + kk * sk + 2 * q + 1] : mk(T(0), T(0));
     if (!lo) {
       A = conjg(A);
       B = conjg(B);

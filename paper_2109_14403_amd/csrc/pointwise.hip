@@ -35,6 +35,7 @@ __global__ void __launch_bounds__(PT_THREADS) k_init(Pt<T> a, int basic, int kee
     c.newton_it = 0;
     c.cg_it = 0;
     c.cg_bad = 0;
+    c.ticket = 0;
     c.pending = 0;
     c.status = 0;
     c.pipelines = 0;
@@ -402,7 +403,7 @@ __global__ void __launch_bounds__(PT_THREADS) k_init_linear(Pt<T> a) {
   if (blk == 0 && threadIdx.x == 0) {
     Ctl& c = a.ctl[prob];
     c.mode = M_EVAL;
-    c.newton_it = c.cg_it = c.cg_bad = c.pending = c.status = c.pipelines = c.krylov = 0;
+    c.newton_it = c.cg_it = c.cg_bad = c.ticket = c.pending = c.status = c.pipelines = c.krylov = 0;
     c.rr = c.alpha = c.beta = c.res = c.fnorm = c.cg_target = 0.0;
   }
   const long long nv = a.nvox;

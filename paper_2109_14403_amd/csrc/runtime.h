@@ -36,6 +36,7 @@ enum KernelKind {
   K_COMMIT,
   K_REDOUT,
   K_XMID,
+  K_PLANE,
   K_COUNT
 };
 extern const char* const kKernelNames[2 * K_COUNT];

@@ -14,9 +14,9 @@ namespace hom {
 
 const char* const kKernelNames[2 * K_COUNT] = {
     "init",     "eval",   "xfwd",   "yfwd",   "zgreen",   "yinv",   "xinv",   "reduce_a",   "history",
-    "commit",   "reduce_out", "xmid",
+    "commit",   "reduce_out", "xmid",   "yzplane",
     "t.init",   "t.eval", "t.xfwd", "t.yfwd", "t.zgreen", "t.yinv", "t.xinv", "t.reduce_a", "t.history",
-    "t.commit", "t.reduce_out", "t.xmid"};
+    "t.commit", "t.reduce_out", "t.xmid", "t.yzplane"};
 
 void fail(int code, const std::string& msg) { throw Error{code, msg}; }
 
@@ -236,6 +236,11 @@ LaunchInfo run_zgreen(const Pipe<T>& a, int sched, hipStream_t s, bool dry) {
   HOM_DISPATCH(a.nz, (zgreen_launch<T, NN>(a, sched, s, dry)))
 }
 
+template <typename T>
+LaunchInfo run_yzplane(const Pipe<T>& a, hipStream_t s, bool dry) {
+  HOM_DISPATCH(a.nz, (yzplane_launch<T, NN>(a, s, dry)))
+}
+
 static bool launch_ok(const LaunchInfo& li) { return li.threads <= 1024 && li.lds <= 160 * 1024; }
 
 // ---------------------------------------------------------------------------
@@ -277,6 +282,7 @@ struct Group {
   // schedules of the y and z passes, [mech, thermal]: tile width + 16 x plan
   // variant (pipe_launch.h)
   int txy[2] = {schedule(4, 0), schedule(4, 0)}, txz[2] = {schedule(4, 0), schedule(4, 0)};
+  int planes = 0;  // 1: the y and z transforms in one pass, a plane of one kx at a time
   int pt_bpp = 1;
   int cm_bpp = 1;  // blocks per problem of the once-per-increment history sums
   // internal variables and increment slots of the PA66 voxels only, compacted
@@ -345,6 +351,7 @@ struct Group {
 
   void alloc(bool with_state, bool partials = false, bool predictor = false) {
     P = nx / 2 + 1;
+    planes = plane_pass(ny, nz, sizeof(T) == 8, (long long)nprob * P) ? 1 : 0;
     nvox = (long long)nx * ny * nz;
     vs = (nvox + 63) / 64 * 64 + 1024;
     const long long nm = (long long)nprob * vs;
@@ -391,7 +398,7 @@ struct Group {
     xmblocks = (ny * nz + nlm - 1) / nlm;
     xiblocks = (ny * nz + nli - 1) / nli;
     // the z pass: one partial a work-group, most with the narrowest tile
-    maxblk = std::max(std::max(pt_bpp, ny * ((P + 1) / 2)), std::max(xmblocks, xiblocks));
+    maxblk = std::max(std::max(pt_bpp, std::max(P, ny * ((P + 1) / 2))), std::max(xmblocks, xiblocks));
     // the commit of the internal variables: one partial a block of 256 voxels
     if (with_state && nstate > 0) maxblk = std::max(maxblk, commit_voxel_blocks(nvox));
     part = dalloc<double>((size_t)nprob * maxblk * NPART);
@@ -436,6 +443,7 @@ struct Group {
     a.tab = tab;
     a.tn = tn;
     a.spec = spec;
+    a.planes = planes;
     a.ctl = phys == 0 ? ctl_m : ctl_t;
     a.inc = inc_d;
     a.part = part;
@@ -649,7 +657,7 @@ class BatchT : public BatchImpl {
         HIPCHK(hipMemcpy(G.cbase, cbase.data(), cbase.size() * sizeof(int), hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(G.npa_d, G.npa.data(), G.nprob * sizeof(int), hipMemcpyHostToDevice));
       }
-      if (opts.autotune) autotune(G);
+      if (opts.autotune && !G.planes) autotune(G);
     }
     HIPCHK(hipDeviceSynchronize());
   }
@@ -714,6 +722,8 @@ class BatchT : public BatchImpl {
   void check_tiles(Group<T>& G, int phys) {
     hipStream_t stream = G.stream;  // this group's lane
     Pipe<T> a = G.pipe(phys, 0);
+    if (G.planes && !launch_ok(run_yzplane<T>(a, stream, true)))
+      fail(HOM_E_UNSUPPORTED, "the plane pass does not fit the work-group limits");
     for (int pass = 0; pass < 2; ++pass) {
       int& sc = (pass == 0 ? G.txy : G.txz)[phys];
       LaunchInfo li = pass == 0 ? run_ypass<T>(a, sc, 0, stream, true) : run_zgreen<T>(a, sc, stream, true);
@@ -772,15 +782,21 @@ class BatchT : public BatchImpl {
     else
       run_xmid<T>(a, stream);
     prof.end(stream);
-    prof.begin(K_YFWD, stream);
-    run_ypass<T>(a, G.txy[phys], 0, stream);
-    prof.end(stream);
-    prof.begin(K_ZGREEN, stream);
-    run_zgreen<T>(a, G.txz[phys], stream);
-    prof.end(stream);
-    prof.begin(K_YINV, stream);
-    run_ypass<T>(a, G.txy[phys], 1, stream);
-    prof.end(stream);
+    if (G.planes) {
+      prof.begin(K_PLANE, stream);
+      run_yzplane<T>(a, stream);
+      prof.end(stream);
+    } else {
+      prof.begin(K_YFWD, stream);
+      run_ypass<T>(a, G.txy[phys], 0, stream);
+      prof.end(stream);
+      prof.begin(K_ZGREEN, stream);
+      run_zgreen<T>(a, G.txz[phys], stream);
+      prof.end(stream);
+      prof.begin(K_YINV, stream);
+      run_ypass<T>(a, G.txy[phys], 1, stream);
+      prof.end(stream);
+    }
     if (!basic) return;
     prof.begin(K_XINV, stream);
     run_xinv<T>(a, stream);
@@ -1417,6 +1433,7 @@ static void apply_operator_t(const hom_grid& g, int ncomp, int op, double p0, do
   a.ctl = G.ctl_m;
   hipStream_t s = nullptr;
   int tx = sched;
+  if (sched >= 0) a.planes = 0;  // a schedule of the separate y and z passes
   if (sched < 0) {
     tx = schedule(4, 0);
     if (!launch_ok(run_zgreen<T>(a, tx, s, true))) tx = schedule(2, 0);
@@ -1426,11 +1443,16 @@ static void apply_operator_t(const hom_grid& g, int ncomp, int op, double p0, do
   (void)hipGetLastError();
   run_xfwd<T>(a, s);
   hip_check(hipGetLastError(), "xfwd launch");
-  run_ypass<T>(a, tx, 0, s);
-  hip_check(hipGetLastError(), "ypass launch");
-  run_zgreen<T>(a, tx, s);
-  hip_check(hipGetLastError(), "zgreen launch");
-  run_ypass<T>(a, tx, 1, s);
+  if (a.planes) {
+    run_yzplane<T>(a, s);
+    hip_check(hipGetLastError(), "yzplane launch");
+  } else {
+    run_ypass<T>(a, tx, 0, s);
+    hip_check(hipGetLastError(), "ypass launch");
+    run_zgreen<T>(a, tx, s);
+    hip_check(hipGetLastError(), "zgreen launch");
+    run_ypass<T>(a, tx, 1, s);
+  }
   run_xinv<T>(a, s);
   hip_check(hipGetLastError(), "xinv launch");
   HIPCHK(hipDeviceSynchronize());

@@ -34,3 +34,25 @@ def test_increment_matches_oracle(shape, precision):
                 err = np.abs(g[k] - o[k]).max() / np.abs(o[k]).max()
                 print(f"{shape} precision {precision} {k}: {err:.2e}", flush=True)
                 assert err <= TOL[precision]
+
+
+# planes of these sizes are transformed in LDS only when a launch has enough of
+# them: the batch takes the plane pass, a single cell the separate passes
+@pytest.mark.parametrize("shape,count,precision", [((48, 48, 16), 15, hom.FP32), ((32, 32, 16), 15, hom.FP64),
+                                                   ((24, 48, 32), 8, hom.FP64)])
+def test_batch_of_large_planes_equals_single_cells(shape, count, precision):
+    rng = np.random.default_rng(count)
+    imgs = [(rng.random(shape) < 0.3).astype(np.uint8) for _ in range(count)]
+    laws = [W.small_sphere_matrix(), W.small_sphere_inclusion()]
+    strains = rng.normal(size=(count, 6)) * 2e-3
+    grads = rng.normal(size=(count, 3))
+    opts = dict(precision=precision, tol=1e-10 if precision == hom.FP64 else 1e-6)
+    with hom.Batch(imgs, laws, **opts) as b:
+        r = b.solve_increment(strains, [323.0] * count, grads, [2.0] * count)
+    for i in (0, count // 2, count - 1):
+        with hom.Context(imgs[i], laws, **opts) as ctx:
+            g = ctx.solve_increment(strains[i], 323.0, grads[i], 2.0)
+        for k in ("stress", "heat_flux"):
+            err = np.abs(r[i][k] - g[k]).max() / np.abs(g[k]).max()
+            print(f"{shape} problem {i} precision {precision} {k}: {err:.2e}", flush=True)
+            assert err <= 2 * TOL[precision]
