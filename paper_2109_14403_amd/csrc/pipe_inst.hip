@@ -190,7 +190,9 @@ LaunchInfo xinv_launch(const Pipe<T>& a, hipStream_t s, bool dry) {
 
 template <typename T, int N>
 LaunchInfo xmid_launch(const Pipe<T>& a, hipStream_t s, bool dry) {
-  constexpr int NL = x_lines(N, sizeof(T) == 8, true);
+  constexpr int NL = x_lines(N, sizeof(T) == 8, true), FEW = xmid_lines_few(N, sizeof(T) == 8);
+  if (xmid_lines(N, sizeof(T) == 8, (long long)a.nprob * a.ny * a.nz) == FEW)
+    return a.C == 6 ? xmid_c<T, 6, N, FEW>(a, s, dry) : xmid_c<T, 3, N, FEW>(a, s, dry);
   return a.C == 6 ? xmid_c<T, 6, N, NL>(a, s, dry) : xmid_c<T, 3, N, NL>(a, s, dry);
 }
 

@@ -39,6 +39,19 @@ constexpr int x_lines(int n, bool fp64, bool mid) {
   const int nl = ((fp64 ? 64 : 128) / (n / plan_m(n))) / (mid && !fp64 ? 2 : 1);
   return nl < 1 ? 1 : nl;
 }
+// Launches of few lines take a quarter of that in the middle pass, so that the
+// lines spread over more of the chip. Measured on increments of single cells
+// (in brackets the work-groups they made before): FP64 32 x 16^2 (16) 1.12, 24^3
+// (36) 1.19, 32^3 (64) 1.06, 96 x 24 x 48 (72) 1.14, 128 x 32 x 32 (128) 1.08, 48^3
+// (144) 1.03 times as fast; FP32 24^3 (18) 1.06, 32^3 (64) 1.05, 96 x 24 x 48 (72)
+// 1.10, but 128 x 32 x 32 (128) 0.98 and 48^3 (144) 0.99. The forward and inverse
+// passes of the fixed-point scheme gain nothing (16^3: 0.97).
+constexpr int xmid_lines_few(int n, bool fp64) {
+  return x_lines(n, fp64, true) < 4 ? 1 : x_lines(n, fp64, true) / 4;
+}
+constexpr int xmid_lines(int n, bool fp64, long long lines) {
+  return lines < (fp64 ? 256LL : 112LL) * x_lines(n, fp64, true) ? xmid_lines_few(n, fp64) : x_lines(n, fp64, true);
+}
 
 // Schedules of the y and z passes: tile width (kx columns per work-group: 2,
 // 4 or 8) and FFT plan variant (0 or 1, Plan<N, V>), packed as width + 16 V.

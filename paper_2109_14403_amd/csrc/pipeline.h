@@ -332,23 +332,20 @@ __device__ __forceinline__ void x_forward_lines(const Pipe<T>& a, int prob, int 
     // the block's lines are contiguous in every plane of one kx
     const long long plane = (long long)a.ny * a.nz * C;
     c2<T>* spec = a.spec + (long long)prob * a.P * plane + (long long)line0 * C;
-    for (int i = tid; i < H * NL * C / V; i += nth) {
-      const int e = V * i;
+    constexpr int VP = C % 2 == 0 ? V : 1;  // pairs of components of one kx
+    for (int i = tid; i < H * NL * C / VP; i += nth) {
+      const int e = VP * i;
       const int k = e / (NL * C);
       const int rest = e - k * (NL * C);
       const int li = rest / C;
       const int c = rest - li * C;
       if (li >= nvl) continue;
-      if constexpr (V == 2 && C % 2 == 0) {
+      if constexpr (VP == 2) {
         const c2<T> u0 = value(li, k, c), u1 = value(li, k, c + 1);
         const nt_f4 t = {u0.x, u0.y, u1.x, u1.y};
         *reinterpret_cast<nt_f4*>(spec + k * plane + rest) = t;
       } else {
-#pragma unroll
-        for (int j = 0; j < V; ++j) {
-          const int r1 = rest + j;
-          spec[k * plane + r1] = value(r1 / C, k, r1 % C);
-        }
+        spec[k * plane + rest] = value(li, k, c);
       }
     }
     return;

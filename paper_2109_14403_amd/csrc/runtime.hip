@@ -394,7 +394,7 @@ struct Group {
     // (many short work-groups) up to 65536 groups.
     cm_bpp = (int)std::min<long long>((nvox + 255) / 256, std::max<long long>(1, 65536 / nprob));
     cm_bpp = std::max(cm_bpp, pt_bpp);
-    const int nlm = x_lines(nx, sizeof(T) == 8, true), nli = x_lines(nx, sizeof(T) == 8, false);
+    const int nlm = xmid_lines(nx, sizeof(T) == 8, (long long)nprob * ny * nz), nli = x_lines(nx, sizeof(T) == 8, false);
     xmblocks = (ny * nz + nlm - 1) / nlm;
     xiblocks = (ny * nz + nli - 1) / nli;
     // the z pass: one partial a work-group, most with the narrowest tile
