@@ -1145,7 +1145,8 @@ __global__ void __launch_bounds__((x_threads<N, NL, C>()))
   for (int i = tid; i < N; i += nth) tw[i] = a.twx[i];
   const long long nv = a.vs;  // stride of the per-voxel arrays (component, problem)
   const long long fo = (long long)prob * C * nv;
-  const uint8_t* phase = a.phase + (long long)prob * nv;
+  const int cell = prob / a.div;  // whose phases and tangents the problem has
+  const uint8_t* phase = a.phase + (long long)cell * nv;
   const ProbInc& inc = a.inc[prob];
   const bool cg = (mode == M_CG);
   const bool first = (ctl.cg_it == 0);
@@ -1165,8 +1166,8 @@ __global__ void __launch_bounds__((x_threads<N, NL, C>()))
   T* rb = a.r + fo;
   T* pb = a.p + fo;
   T* xb = a.x + fo;
-  const T* tb = a.tab + (long long)prob * 2 * nv;
-  const T* nb = a.tn + (long long)prob * 6 * nv;
+  const T* tb = a.tab + (long long)cell * 2 * nv;
+  const T* nb = a.tn + (long long)cell * 6 * nv;
   double s0 = 0.0, s1 = 0.0;  // CG: p . C p and r . r; evaluation: f . f
   const int w = tid;
   if (w < NL * N / 4) {

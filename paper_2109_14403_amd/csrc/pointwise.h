@@ -53,6 +53,12 @@ struct Pt {
                             // plastic increments are in the increment slots)
   T* dx;                    // strain change of the last committed increment [prob][6][nvox], or null
   const T* x0;              // start of a linearized solve [prob][6][nvox], or null (uniform dE)
+  // columns of a tangent call that are solved together: problem = cell * div +
+  // column; phases, tangents and partials are the cell's, columns from ncol on
+  // are idle, bit c of x0_ok says that column c starts from x0
+  int div;
+  int ncol;
+  int x0_ok;
 };
 
 // Effective sums of the commit kernel (mechanics): <sigma> (6), dissipation,

@@ -400,6 +400,12 @@ __global__ void __launch_bounds__(PT_THREADS) k_init_linear(Pt<T> a) {
   const int prob = blockIdx.x / a.bpp;
   const int blk = blockIdx.x % a.bpp;
   const ProbInc& in = a.inc[prob];
+  const int col = prob % a.div;
+  if (a.div > 1 && col >= a.ncol) {  // not solved by this call
+    if (blk == 0 && threadIdx.x == 0) a.ctl[prob].mode = M_DONE, a.ctl[prob].status = 0;
+    return;
+  }
+  const bool start = a.x0 && (a.div == 1 || ((a.x0_ok >> col) & 1));
   if (blk == 0 && threadIdx.x == 0) {
     Ctl& c = a.ctl[prob];
     c.mode = M_EVAL;
@@ -410,7 +416,7 @@ __global__ void __launch_bounds__(PT_THREADS) k_init_linear(Pt<T> a) {
   const long long vs = a.vs;  // stride of the per-voxel arrays (component, problem)
   const long long fo = (long long)prob * 6 * vs;
   for (long long v = (long long)blk * PT_THREADS + threadIdx.x; v < nv; v += (long long)a.bpp * PT_THREADS) {
-    if (a.x0) {  // an earlier solution of the same column: same mean, close fluctuation
+    if (start) {  // an earlier solution of the same column: same mean, close fluctuation
 #pragma unroll
       for (int c = 0; c < 6; ++c) stnt(a.x + fo + c * vs + v, ldnt(a.x0 + fo + c * vs + v));
     } else {
@@ -434,8 +440,10 @@ __global__ void __launch_bounds__(PT_THREADS) k_eval_linear(Pt<T> a) {
   const long long nv = a.nvox;
   const long long vs = a.vs;  // stride of the per-voxel arrays (component, problem)
   const long long fo = (long long)prob * 6 * vs;
-  const long long to = (long long)prob * 2 * vs;
-  const uint8_t* phase = a.phase + (long long)prob * vs;
+  const int cell = prob / a.div;
+  const long long to = (long long)cell * 2 * vs, co = (long long)cell * 6 * vs;
+  const uint8_t* phase = a.phase + (long long)cell * vs;
+  const bool source = a.s0 && (a.div == 1 || prob - cell * a.div == 6);
   for (long long v = (long long)blk * PT_THREADS + threadIdx.x; v < nv; v += (long long)a.bpp * PT_THREADS) {
     double e[6];
 #pragma unroll
@@ -459,15 +467,15 @@ __global__ void __launch_bounds__(PT_THREADS) k_eval_linear(Pt<T> a) {
       double nd[6], dot = 0.0;
 #pragma unroll
       for (int c = 0; c < 6; ++c) {
-        nd[c] = (double)ldnt(a.tn + fo + c * vs + v);
+        nd[c] = (double)ldnt(a.tn + co + c * vs + v);
         dot += nd[c] * e[c];
       }
 #pragma unroll
       for (int c = 0; c < 6; ++c) sg[c] += cb * dot * nd[c];
     }
-    if (a.s0) {
+    if (source) {
 #pragma unroll
-      for (int c = 0; c < 6; ++c) sg[c] += (double)ldnt(a.s0 + fo + c * vs + v);
+      for (int c = 0; c < 6; ++c) sg[c] += (double)ldnt(a.s0 + co + c * vs + v);
     }
 #pragma unroll
     for (int c = 0; c < 6; ++c) stnt(a.f + fo + c * vs + v, T(sg[c]));
@@ -560,6 +568,7 @@ __global__ void __launch_bounds__(PT_THREADS) k_tangent_sum(Pt<T> a) {
   const long long nv = a.nvox;
   const long long vs = a.vs;  // stride of the per-voxel arrays (component, problem)
   const long long fo = (long long)prob * 6 * vs;
+  const long long cell = prob / a.div, co = cell * 6 * vs;
   double acc[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) acc[k] = 0.0;
@@ -569,8 +578,8 @@ __global__ void __launch_bounds__(PT_THREADS) k_tangent_sum(Pt<T> a) {
     if (a.dDde) {
 #pragma unroll
       for (int c = 0; c < 6; ++c)
-        acc[6] += (double)ldnt(a.dDde + fo + c * vs + v) * (double)ldnt(a.x + fo + c * vs + v);
-      acc[7] += (double)ldnt(a.dDdt + (long long)prob * vs + v);
+        acc[6] += (double)ldnt(a.dDde + co + c * vs + v) * (double)ldnt(a.x + fo + c * vs + v);
+      acc[7] += (double)ldnt(a.dDdt + cell * vs + v);
     }
   }
   block_sum<8>(acc, red);

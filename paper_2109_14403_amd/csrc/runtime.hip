@@ -311,6 +311,13 @@ struct Group {
   // which start the next call's linearized solves
   T* tcol = nullptr;
   bool tcol_ok[7] = {false, false, false, false, false, false, false};
+  // the columns of a tangent call solved together (small groups): a group of
+  // nprob * div problems with its own iteration fields and the cells' phases,
+  // tangents and partials
+  std::unique_ptr<Group<T>> columns;
+  bool columns_failed = false;  // no memory for it: one column after the other
+  const Group<T>* base = nullptr;
+  int div = 1;
   ProbInc* inc_pm_d = nullptr;
   ProbInc* inc_pm_h = nullptr;
   bool tan_ok = false;
@@ -386,23 +393,12 @@ struct Group {
     HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&inc_h), sizeof(ProbInc) * nprob));
     HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&ctl_h), sizeof(Ctl) * nprob));
     std::memset(inc_h, 0, sizeof(ProbInc) * nprob);
-    // blocks per problem of the pointwise kernels
-    pt_bpp = (int)std::min<long long>((nvox + 255) / 256, std::max<long long>(1, 8192 / nprob));
-    pt_bpp = std::max(pt_bpp, 1);
+    alloc_partials(with_state && nstate > 0);
     // the history sums stream the branch strains of the compacted PA66 voxels
     // once per increment and write no partial sums: one voxel per thread
     // (many short work-groups) up to 65536 groups.
     cm_bpp = (int)std::min<long long>((nvox + 255) / 256, std::max<long long>(1, 65536 / nprob));
     cm_bpp = std::max(cm_bpp, pt_bpp);
-    const int nlm = xmid_lines(nx, sizeof(T) == 8, (long long)nprob * ny * nz), nli = x_lines(nx, sizeof(T) == 8, false);
-    xmblocks = (ny * nz + nlm - 1) / nlm;
-    xiblocks = (ny * nz + nli - 1) / nli;
-    // the z pass: one partial a work-group, most with the narrowest tile
-    maxblk = std::max(std::max(pt_bpp, std::max(P, ny * ((P + 1) / 2))), std::max(xmblocks, xiblocks));
-    // the commit of the internal variables: one partial a block of 256 voxels
-    if (with_state && nstate > 0) maxblk = std::max(maxblk, commit_voxel_blocks(nvox));
-    part = dalloc<double>((size_t)nprob * maxblk * NPART);
-    part2 = dalloc<double>((size_t)nprob * ((maxblk + RED_CHUNK - 1) / RED_CHUNK) * NPART);
     for (int d = 0; d < 3; ++d) {
       const int n = d == 0 ? nx : (d == 1 ? ny : nz);
       auto w = twiddles<T>(n);
@@ -422,6 +418,65 @@ struct Group {
       HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&inc_pm_h), sizeof(ProbInc) * 2 * nprob));
       std::memset(inc_pm_h, 0, sizeof(ProbInc) * 2 * nprob);
     }
+  }
+
+  // Iteration fields for ncol linearized solves a problem of b, with b's
+  // grid, phases, tangents and schedules.
+  void alloc_columns(const Group<T>& b, int ncol) {
+    base = &b;
+    div = ncol;
+    nx = b.nx;
+    ny = b.ny;
+    nz = b.nz;
+    P = b.P;
+    nvox = b.nvox;
+    vs = b.vs;
+    nprob = b.nprob * ncol;
+    stream = b.stream;
+    phase = b.phase;
+    tab = b.tab;
+    tn = b.tn;
+    dsdt = b.dsdt;
+    dDde = b.dDde;
+    dDdt = b.dDdt;
+    for (int d = 0; d < 3; ++d) {
+      len[d] = b.len[d];
+      tw[d] = b.tw[d];
+    }
+    for (int i = 0; i < 2; ++i) {
+      ps[i] = b.ps[i];
+      txy[i] = b.txy[i];
+      txz[i] = b.txz[i];
+    }
+    planes = plane_pass(ny, nz, sizeof(T) == 8, (long long)nprob * P) ? 1 : 0;
+    const long long nm = (long long)nprob * vs;
+    xm = dalloc<T>(6 * nm);
+    f = dalloc<T>(6 * nm);
+    r = dalloc<T>(6 * nm);
+    p = dalloc<T>(6 * nm);
+    spec_count = (size_t)nprob * nz * ny * ps[0] * 6;
+    spec = dalloc<c2<T>>(spec_count);
+    ctl_m = dalloc<Ctl>(nprob);
+    inc_d = dalloc<ProbInc>(nprob);
+    HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&inc_h), sizeof(ProbInc) * nprob));
+    HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&ctl_h), sizeof(Ctl) * nprob));
+    alloc_partials(false);
+  }
+
+  // Work-groups of the passes and their partial sums.
+  void alloc_partials(bool voxel_commit) {
+    // blocks per problem of the pointwise kernels
+    pt_bpp = (int)std::min<long long>((nvox + 255) / 256, std::max<long long>(1, 8192 / nprob));
+    pt_bpp = std::max(pt_bpp, 1);
+    const int nlm = xmid_lines(nx, sizeof(T) == 8, (long long)nprob * ny * nz), nli = x_lines(nx, sizeof(T) == 8, false);
+    xmblocks = (ny * nz + nlm - 1) / nlm;
+    xiblocks = (ny * nz + nli - 1) / nli;
+    // the z pass: one partial a work-group, most with the narrowest tile
+    maxblk = std::max(std::max(pt_bpp, std::max(P, ny * ((P + 1) / 2))), std::max(xmblocks, xiblocks));
+    // the commit of the internal variables: one partial a block of 256 voxels
+    if (voxel_commit) maxblk = std::max(maxblk, commit_voxel_blocks(nvox));
+    part = dalloc<double>((size_t)nprob * maxblk * NPART);
+    part2 = dalloc<double>((size_t)nprob * ((maxblk + RED_CHUNK - 1) / RED_CHUNK) * NPART);
   }
 
   Pipe<T> pipe(int phys, int green) const {
@@ -456,6 +511,7 @@ struct Group {
       a.ilen[d] = 1.0 / len[d];
     }
     a.green = green;
+    a.div = div;
     a.xblocks = 0;
     a.zblocks = 0;
     a.lim = Limits{};
@@ -497,6 +553,9 @@ struct Group {
     a.dp_known = 0;
     a.dx = dx;
     a.x0 = nullptr;
+    a.div = div;
+    a.ncol = div;
+    a.x0_ok = 0;
     return a;
   }
 };
@@ -552,7 +611,7 @@ class BatchT : public BatchImpl {
 
   size_t device_bytes() const override {
     size_t b = 0;
-    for (auto& g : groups) b += g->bytes;
+    for (auto& g : groups) b += g->bytes + (g->columns ? g->columns->bytes : 0);
     return b;
   }
 
@@ -770,7 +829,7 @@ class BatchT : public BatchImpl {
     Ctl* ctl = phys == 0 ? G.ctl_m : G.ctl_t;
     prof.begin(K_EVAL, stream);
     if (variant >= 2) {
-      q.s0 = variant == 3 ? G.dsdt : nullptr;
+      q.s0 = variant == 3 || G.div > 1 ? G.dsdt : nullptr;  // columns solved together: of the last one
       launch_eval_linear<T>(q, stream);
     } else {
       launch_eval<T>(q, C, stream);
@@ -1162,6 +1221,104 @@ class BatchT : public BatchImpl {
     }
   }
 
+  // ---- the columns of a tangent call solved together --------------------
+  // One linearized solve of a small group is bound by the latency of its
+  // passes and launches: its columns run as that many problems at once, with
+  // the cell's phases and tangents read by all of them. Measured, one column
+  // after the other against all together (an increment and its tangents,
+  // 7 columns; a stiffness sample, 6): 16^3 FP32 12.0 -> 3.6 ms, 32^3 18.8 -> 6.0,
+  // 48^3 24.5 -> 10.5, 64^3 37.0 -> 21.1, 24^3 FP64 23.2 -> 6.2; sample at 32^3
+  // 12.6 -> 3.1, 64^3 23.2 -> 13.3, 96^3 57.7 -> 40.1, 128^3 112 -> 103 ms. Above
+  // that the passes fill the memory system by themselves, and seven sets of
+  // iteration fields (0.8 KB a voxel in FP32) are not worth it.
+  static constexpr int kColumns = 7;
+  static constexpr long long kColumnVoxels = 1LL << 21;  // of a group, up to which they do
+  bool columns_together(Group<T>& G) {
+    if (G.columns) return true;
+    if (G.columns_failed || G.nvox * G.nprob > kColumnVoxels) return false;
+    try {
+      G.columns.reset(new Group<T>());
+      G.columns->alloc_columns(G, kColumns);
+      check_tiles(*G.columns, 0);
+      HIPCHK(hipStreamSynchronize(nullptr));  // the clears, which the lane's stream does not wait for
+    } catch (const Error& e) {
+      G.columns.reset();
+      if (e.code != HOM_E_OOM) throw;
+      (void)hipGetLastError();
+      G.columns_failed = true;
+      return false;
+    }
+    return true;
+  }
+
+  void tangent_columns(Group<T>& G, int what, hom_tangent* out) {
+    hipStream_t stream = G.stream;  // this group's lane
+    const double sq2 = std::sqrt(2.0);
+    const double w[6] = {1, 1, 1, sq2, sq2, sq2};
+    Group<T>& L = *G.columns;
+    const size_t field = 6 * (size_t)G.vs;  // one problem's
+    const int ncol = what == 1 ? 7 : 6;
+    Limits lim = limits(0);
+    lim.linear = 1;
+    Pt<T> q = L.pt(0);
+    q.ncol = ncol;
+    if (G.dx && !G.tcol) {  // predictor: warm starts
+      G.tcol = G.template dalloc<T>(kColumns * field * G.nprob);
+      HIPCHK(hipStreamSynchronize(nullptr));
+    }
+    q.x0 = G.tcol;
+    for (int c = 0; c < ncol; ++c) q.x0_ok |= G.tcol && G.tcol_ok[c] ? 1 << c : 0;
+    for (int j = 0; j < G.nprob; ++j) {
+      hom_tangent& t = out[G.members[j]];
+      std::memset(&t, 0, sizeof(t));
+      if (what == 0) {
+        for (int c = 0; c < 6; ++c) t.dsdt[c] = t.dDde[c] = NAN;
+        t.dDdt = NAN;
+      }
+      G.inc_h[j].smask = 0;  // the tangents are derivatives at prescribed strain
+      for (int col = 0; col < kColumns; ++col) {
+        ProbInc& in = L.inc_h[j * kColumns + col];
+        in = G.inc_h[j];
+        for (int c = 0; c < 6; ++c) in.dE[c] = (c == col) ? 1.0 : 0.0;
+      }
+    }
+    HIPCHK(hipMemcpyAsync(L.inc_d, L.inc_h, sizeof(ProbInc) * L.nprob, hipMemcpyHostToDevice, stream));
+    launch_init_linear<T>(q, stream);
+    iterate(L, 2, false, iteration_cap(lim, false));
+    launch_tangent_sum<T>(q, stream);
+    launch_reduce_out(L.ctl_m, L.part, L.maxblk, L.pt_bpp, L.nprob, 8, 1.0 / (double)L.nvox, stream);
+    HIPCHK(hipMemcpyAsync(L.ctl_h, L.ctl_m, sizeof(Ctl) * L.nprob, hipMemcpyDeviceToHost, stream));
+    // the strain field is the committed one after a tangent call
+    HIPCHK(hipMemcpyAsync(G.xm, G.xnm, field * G.nprob * sizeof(T), hipMemcpyDeviceToDevice, stream));
+    HIPCHK(hipStreamSynchronize(stream));
+    for (int col = 0; col < ncol; ++col)
+      for (int j = 0; j < G.nprob; ++j) {
+        const Ctl& c = L.ctl_h[j * kColumns + col];
+        if (c.status != 1)
+          fail(c.status < 0 ? c.status : HOM_E_NOT_CONVERGED,
+               "linearized solve " + std::to_string(col) + " of problem " + std::to_string(G.members[j]) +
+                   " did not converge");
+        hom_tangent& t = out[G.members[j]];
+        if (col < 6) {
+          for (int I = 0; I < 6; ++I) t.dsde[6 * I + col] = c.out[I] * w[col] / w[I];
+          if (what == 1) t.dDde[col] = c.out[6] * w[col];
+        } else {
+          for (int I = 0; I < 6; ++I) t.dsdt[I] = c.out[I] / w[I];
+          t.dDdt = c.out[6] + c.out[7];
+        }
+        t.solves += 1;
+        t.krylov_iters += c.krylov;
+        t.pipelines += c.pipelines;
+      }
+    if (G.tcol) {  // converged everywhere: the next call starts from these solutions
+      const size_t row = ncol * field * sizeof(T), pitch = kColumns * field * sizeof(T);
+      HIPCHK(hipMemcpy2DAsync(G.tcol, pitch, L.xm, pitch, row, G.nprob, hipMemcpyDeviceToDevice, stream));
+      for (int c = 0; c < ncol; ++c) G.tcol_ok[c] = true;
+      HIPCHK(hipStreamSynchronize(stream));
+    }
+    HIPCHK(hipGetLastError());
+  }
+
   // ---- effective algorithmic tangents of the last increment ---------------
   // Linearized solves with the algorithmic tangent of the converged Newton
   // evaluation: one per unit macro strain (Mandel), and for what = 1 one with
@@ -1184,6 +1341,15 @@ class BatchT : public BatchImpl {
     for (auto& gp : groups) {
       Group<T>& G = *gp;
       hipStream_t stream = G.stream;  // this group's lane
+      if (columns_together(G)) {
+        try {
+          tangent_columns(G, what, out);
+        } catch (...) {
+          prof.on = prof_on;
+          throw;
+        }
+        continue;
+      }
       const size_t nm = (size_t)G.nprob * G.vs;
       if (!G.fsave) G.fsave = G.template dalloc<T>(6 * nm);
       HIPCHK(hipMemcpyAsync(G.fsave, G.f, 6 * nm * sizeof(T), hipMemcpyDeviceToDevice, stream));

@@ -193,3 +193,25 @@ def test_set_laws_reuses_a_context():
     assert e.value.code == hom.HOM_E_ARG
     ctx.close()
     fresh.close()
+
+
+@pytest.mark.parametrize("shape,predictor", [((128, 128, 256), 0), ((128, 128, 256), 1), ((64, 64, 16), 1)])
+def test_laminate_tangent_at_any_size(shape, predictor):
+    """d<sigma>/dE of a laminate does not depend on how finely its plane is
+    resolved: a grid whose columns are solved one after the other and one whose
+    columns are solved together against a small cell in FP64, twice (with the
+    predictor the second call starts from the first one's solutions)."""
+    nz, ny, nx = shape
+    laws = [W.small_sphere_matrix(), W.small_sphere_inclusion()]
+
+    def tangents(n, precision, tol, calls, pred=0):
+        img = W.laminate(n, [n[0] // 4, 5 * n[0] // 8], axis=0)
+        with hom.Context(img, laws, precision=precision, tol=tol, predictor=pred) as ctx:
+            ctx.solve_increment([1e-3, 0, 0, 0, 5e-4, 0], 310.0, [0, 0, 0], 1.0)
+            return [ctx.algorithmic_tangent(what=0)["dsde"] for _ in range(calls)]
+
+    ref = tangents((16, 16, 16), hom.FP64, 1e-10, 1)[0]
+    for t in tangents((nx, ny, nz), hom.FP32, 1e-6, 2, predictor):
+        err = rel(t, ref)
+        print(f"laminate {shape} predictor {predictor}: {err:.2e}", flush=True)
+        assert err <= 2e-6      # the stated FP32 bound
