@@ -96,203 +96,208 @@ __device__ __forceinline__ int param_of(int h, int nleaf) {
 }
 
 // ---------------------------------------------------------------------------
-// offline: laminate forward and backward
+// offline: laminate forward and backward, eight lanes a laminate
 // ---------------------------------------------------------------------------
-__device__ void lam_fwd(const double* C1, const double* C2, double c1, const double* n, double* C) {
-  const double c2 = 1.0 - c1;
-  double N[6][3];
-  nmat(n, N);
-  double G[6][3], HN[6][3];
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      double g = 0.0, h = 0.0;
-#pragma unroll
-      for (int j = 0; j < 6; ++j) {
-        const double a = C1[6 * i + j], b = C2[6 * i + j];
-        g += (a - b) * N[j][k];
-        h += (c2 * a + c1 * b) * N[j][k];
-      }
-      G[i][k] = g;
-      HN[i][k] = h;
-    }
-  double M[3][3], Mi[3][3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-#pragma unroll
-    for (int l = 0; l < 3; ++l) {
-      double s = 0.0;
-#pragma unroll
-      for (int i = 0; i < 6; ++i) s += N[i][k] * HN[i][l];
-      M[k][l] = s;
-    }
-  if (!inv3(M, Mi)) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-      for (int l = 0; l < 3; ++l) Mi[k][l] = 0.0;
-  }
-  double GM[6][3];
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) GM[i][k] = G[i][0] * Mi[0][k] + G[i][1] * Mi[1][k] + G[i][2] * Mi[2][k];
-  const double cc = c1 * c2;
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int j = 0; j < 6; ++j)
-      C[6 * i + j] = c1 * C1[6 * i + j] + c2 * C2[6 * i + j] -
-                     cc * (GM[i][0] * G[j][0] + GM[i][1] * G[j][1] + GM[i][2] * G[j][2]);
+// Lane r < 6 of a group of eight owns row r of the 6 x 6 matrices (lanes 6 and
+// 7 repeat row 5 and add nothing to sums). With one thread a laminate a tree of
+// depth 8 was a chain of sixteen levels of 7 to 20 us each (1500 FP64
+// operations, uncoalesced rows, spills): 60 us forward and 180 us backward for
+// 32 samples, now 49 us for both; the update 25 -> 13 us. What is left is the
+// latency of the levels, of which the upper ones hold few laminates.
+
+// sum over the eight lanes of a group, in all of them
+__device__ __forceinline__ double dpp_add(double v, int lo, int hi) { return v + __hiloint2double(hi, lo); }
+#define HOM_DPP_ADD(v, ctrl)                                                                       \
+  dpp_add(v, __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xf, 0xf, true),                    \
+          __builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xf, 0xf, true))
+__device__ __forceinline__ double sum8(double v) {
+  v = HOM_DPP_ADD(v, 0xB1);   // quad_perm [1,0,3,2]
+  v = HOM_DPP_ADD(v, 0x4E);   // quad_perm [2,3,0,1]
+  return HOM_DPP_ADD(v, 0x141);  // row_half_mirror: the other quad of the eight
+}
+#undef HOM_DPP_ADD
+
+// d^T N and x . N_j of N (6 x 3, Mandel, a -> sym(a (x) n)), without its zeros
+__device__ __forceinline__ void row_times_n(const double* d, const double* n, double* g) {
+  g[0] = d[0] * n[0] + SQ2H * (d[4] * n[2] + d[5] * n[1]);
+  g[1] = d[1] * n[1] + SQ2H * (d[3] * n[2] + d[5] * n[0]);
+  g[2] = d[2] * n[2] + SQ2H * (d[3] * n[1] + d[4] * n[0]);
+}
+__device__ __forceinline__ void n_rows_dot(const double* x, const double* n, double* y) {
+  y[0] = x[0] * n[0];
+  y[1] = x[1] * n[1];
+  y[2] = x[2] * n[2];
+  y[3] = SQ2H * (x[1] * n[2] + x[2] * n[1]);
+  y[4] = SQ2H * (x[0] * n[2] + x[2] * n[0]);
+  y[5] = SQ2H * (x[0] * n[1] + x[1] * n[0]);
+}
+// row r of N
+__device__ __forceinline__ void n_row(int r, const double* n, double* nr) {
+  const double s0 = SQ2H * n[0], s1 = SQ2H * n[1], s2 = SQ2H * n[2];
+  nr[0] = r == 0 ? n[0] : (r == 4 ? s2 : (r == 5 ? s1 : 0.0));
+  nr[1] = r == 1 ? n[1] : (r == 3 ? s2 : (r == 5 ? s0 : 0.0));
+  nr[2] = r == 2 ? n[2] : (r == 3 ? s1 : (r == 4 ? s0 : 0.0));
 }
 
-// Reverse mode of lam_fwd: given Cb = dJ/dC, writes dJ/dC1, dJ/dC2 (if the
-// pointers are non-null), dJ/dc1 and dJ/dn.
-__device__ void lam_bwd(const double* C1, const double* C2, double c1, const double* n, const double* Cb,
-                        double* C1b, double* C2b, double& c1b, double* nb) {
-  const double c2 = 1.0 - c1;
-  const double cc = c1 * c2;
-  double N[6][3];
-  nmat(n, N);
-  double G[6][3], HN[6][3];
+// What both directions form first: row r of C1, C2, of G = (C1 - C2) N and of
+// HN = (c2 C1 + c1 C2) N, and M^-1 of M = N^T HN.
+struct Lam8 {
+  double a[6], b[6], G[3], HN[3], nr[3], Mi[3][3];
+  __device__ __forceinline__ void form(const double* C1, const double* C2, double c1, const double* n, int row,
+                                       bool own) {
+    const double c2 = 1.0 - c1;
+    double d[6], e[6];
 #pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      double g = 0.0, h = 0.0;
-#pragma unroll
-      for (int j = 0; j < 6; ++j) {
-        const double a = C1[6 * i + j], b = C2[6 * i + j];
-        g += (a - b) * N[j][k];
-        h += (c2 * a + c1 * b) * N[j][k];
-      }
-      G[i][k] = g;
-      HN[i][k] = h;
+    for (int j = 0; j < 6; ++j) {
+      a[j] = C1[6 * row + j];
+      b[j] = C2[6 * row + j];
+      d[j] = a[j] - b[j];
+      e[j] = c2 * a[j] + c1 * b[j];
     }
-  double M[3][3], Mi[3][3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-#pragma unroll
-    for (int l = 0; l < 3; ++l) {
-      double s = 0.0;
-#pragma unroll
-      for (int i = 0; i < 6; ++i) s += N[i][k] * HN[i][l];
-      M[k][l] = s;
-    }
-  if (!inv3(M, Mi)) {
+    row_times_n(d, n, G);
+    row_times_n(e, n, HN);
+    n_row(row, n, nr);
+    double M[3][3];
 #pragma unroll
     for (int k = 0; k < 3; ++k)
 #pragma unroll
-      for (int l = 0; l < 3; ++l) Mi[k][l] = 0.0;
+      for (int l = 0; l < 3; ++l) M[k][l] = sum8(own ? nr[k] * HN[l] : 0.0);
+    if (!inv3(M, Mi)) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int l = 0; l < 3; ++l) Mi[k][l] = 0.0;
+    }
   }
-  double GM[6][3];
+};
+
+__device__ __forceinline__ void times_mi(const double* g, const double Mi[3][3], double* gm) {
 #pragma unroll
-  for (int i = 0; i < 6; ++i)
+  for (int k = 0; k < 3; ++k) gm[k] = g[0] * Mi[0][k] + g[1] * Mi[1][k] + g[2] * Mi[2][k];
+}
+
+// the rows v (3 values) of the six lanes, through the group's scratch in LDS;
+// the lanes are in one wave, whose LDS accesses are in order
+__device__ __forceinline__ void share_rows(const double* v, double* scr, int row, double (&all)[6][3]) {
+  __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int k = 0; k < 3; ++k) GM[i][k] = G[i][0] * Mi[0][k] + G[i][1] * Mi[1][k] + G[i][2] * Mi[2][k];
+  for (int k = 0; k < 3; ++k) scr[3 * row + k] = v[k];
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int j = 0; j < 6; ++j)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) all[j][k] = scr[3 * j + k];
+  __builtin_amdgcn_wave_barrier();
+}
+
+constexpr int SCR8 = 18;  // scratch of a group
+
+__device__ __forceinline__ void lam_fwd8(const double* C1, const double* C2, double c1, const double* n, double* C,
+                                         int row, bool own, double* scr) {
+  const double c2 = 1.0 - c1;
+  Lam8 m;
+  m.form(C1, C2, c1, n, row, own);
+  double GM[3], G[6][3];
+  times_mi(m.G, m.Mi, GM);
+  share_rows(m.G, scr, row, G);
+  const double cc = c1 * c2;
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    const double v = c1 * m.a[j] + c2 * m.b[j] - cc * (GM[0] * G[j][0] + GM[1] * G[j][1] + GM[2] * G[j][2]);
+    if (own) C[6 * row + j] = v;
+  }
+}
+
+// Reverse mode of lam_fwd8: given Cb = dJ/dC, writes dJ/dC1, dJ/dC2 (if the
+// pointers are non-null; they may be C1 and C2), dJ/dc1 and dJ/dn.
+__device__ __forceinline__ void lam_bwd8(const double* C1, const double* C2, double c1, const double* n,
+                                         const double* Cb, double* C1b, double* C2b, double& c1b, double* nb, int row,
+                                         bool own, double* scr) {
+  const double c2 = 1.0 - c1;
+  const double cc = c1 * c2;
+  Lam8 m;
+  m.form(C1, C2, c1, n, row, own);
+  double cr[6], ck[6], dk[6];  // row and column of Cb, column of C1 - C2
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    cr[j] = Cb[6 * row + j];
+    ck[j] = Cb[6 * j + row];
+    dk[j] = C1[6 * j + row] - C2[6 * j + row];
+  }
   // C = c1 C1 + c2 C2 - cc X, X = G Mi G^T = GM G^T. With T = Cb G:
-  //   <Cb, X> = <GM, T>, dJ/dMi = -cc G^T T, dJ/dG = -cc (Cb + Cb^T) GM,
-  // one row of Cb at a time
-  double dx = 0.0, dd = 0.0;  // <Cb, X>, <Cb, C1 - C2>
-  double Gb[6][3], T[6][3];
+  //   <Cb, X> = <GM, T>, dJ/dMi = -cc G^T T, dJ/dG = -cc (Cb + Cb^T) GM
+  double GM[3], T[3], Gb[3], all[6][3];
+  times_mi(m.G, m.Mi, GM);
+  share_rows(m.G, scr, row, all);
 #pragma unroll
-  for (int i = 0; i < 6; ++i)
+  for (int k = 0; k < 3; ++k) {
+    double t = 0.0;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) Gb[i][k] = 0.0;
-#pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    double cr[6];
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      cr[j] = Cb[6 * i + j];
-      dd += cr[j] * (C1[6 * i + j] - C2[6 * i + j]);
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      double t = 0.0, u = 0.0;
-#pragma unroll
-      for (int j = 0; j < 6; ++j) {
-        t += cr[j] * G[j][k];
-        u += cr[j] * GM[j][k];
-        Gb[j][k] -= cc * cr[j] * GM[i][k];  // (Cb^T GM)[j][k]
-      }
-      T[i][k] = t;
-      Gb[i][k] -= cc * u;  // (Cb GM)[i][k]
-      dx += GM[i][k] * t;
-    }
+    for (int j = 0; j < 6; ++j) t += cr[j] * all[j][k];
+    T[k] = t;
   }
+  share_rows(GM, scr, row, all);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    double u = 0.0;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) u += (cr[j] + ck[j]) * all[j][k];
+    Gb[k] = -cc * u;
+  }
+  double dd = 0.0;
+#pragma unroll
+  for (int j = 0; j < 6; ++j) dd += cr[j] * (m.a[j] - m.b[j]);
+  dd = sum8(own ? dd : 0.0);                                                   // <Cb, C1 - C2>
+  const double dx = sum8(own ? GM[0] * T[0] + GM[1] * T[1] + GM[2] * T[2] : 0.0);  // <Cb, X>
   double Mib[3][3];
 #pragma unroll
   for (int k = 0; k < 3; ++k)
 #pragma unroll
-    for (int l = 0; l < 3; ++l) {
-      double m = 0.0;
-#pragma unroll
-      for (int i = 0; i < 6; ++i) m += G[i][k] * T[i][l];
-      Mib[k][l] = -cc * m;
-    }
+    for (int l = 0; l < 3; ++l) Mib[k][l] = -cc * sum8(own ? m.G[k] * T[l] : 0.0);
   // Mi = M^-1: Mb = -Mi Mib Mi (Mi symmetric)
   double W[3][3], Mb[3][3];
 #pragma unroll
-  for (int k = 0; k < 3; ++k)
-#pragma unroll
-    for (int l = 0; l < 3; ++l) W[k][l] = Mib[k][0] * Mi[0][l] + Mib[k][1] * Mi[1][l] + Mib[k][2] * Mi[2][l];
+  for (int k = 0; k < 3; ++k) times_mi(Mib[k], m.Mi, W[k]);
 #pragma unroll
   for (int k = 0; k < 3; ++k)
 #pragma unroll
-    for (int l = 0; l < 3; ++l) Mb[k][l] = -(Mi[k][0] * W[0][l] + Mi[k][1] * W[1][l] + Mi[k][2] * W[2][l]);
-  // M = N^T H N, H = c2 C1 + c1 C2: Hb = N Mb N^T, Nb = HN (Mb + Mb^T)
-  double Nb[6][3];
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      double s = 0.0;
-#pragma unroll
-      for (int l = 0; l < 3; ++l) s += HN[i][l] * (Mb[k][l] + Mb[l][k]);
-      Nb[i][k] = s;
-    }
+    for (int l = 0; l < 3; ++l)
+      Mb[k][l] = -(m.Mi[k][0] * W[0][l] + m.Mi[k][1] * W[1][l] + m.Mi[k][2] * W[2][l]);
+  // M = N^T H N, H = c2 C1 + c1 C2: Hb = N Mb N^T, Nb = HN (Mb + Mb^T);
   // G = (C1 - C2) N: Nb += (C1 - C2)^T Gb, (C1 - C2)b = Gb N^T
+  share_rows(Gb, scr, row, all);
+  double Nb[3], NM[3];
 #pragma unroll
-  for (int j = 0; j < 6; ++j)
+  for (int k = 0; k < 3; ++k) {
+    double s = 0.0;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      double s = 0.0;
+    for (int l = 0; l < 3; ++l) s += m.HN[l] * (Mb[k][l] + Mb[l][k]);
 #pragma unroll
-      for (int i = 0; i < 6; ++i) s += (C1[6 * i + j] - C2[6 * i + j]) * Gb[i][k];
-      Nb[j][k] += s;
+    for (int i = 0; i < 6; ++i) s += dk[i] * all[i][k];
+    Nb[k] = s;
+    NM[k] = m.nr[0] * Mb[0][k] + m.nr[1] * Mb[1][k] + m.nr[2] * Mb[2][k];
+  }
+  double hb[6], db[6], dh = 0.0;  // <Hb, C2 - C1>
+  n_rows_dot(NM, n, hb);
+  n_rows_dot(Gb, n, db);
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    dh += hb[j] * (m.b[j] - m.a[j]);
+    if (own) {
+      if (C1b) C1b[6 * row + j] = c1 * cr[j] + c2 * hb[j] + db[j];
+      if (C2b) C2b[6 * row + j] = c2 * cr[j] + c1 * hb[j] - db[j];
     }
-  // Hb = N Mb N^T = NM N^T
-  double NM[6][3];
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int l = 0; l < 3; ++l) NM[i][l] = N[i][0] * Mb[0][l] + N[i][1] * Mb[1][l] + N[i][2] * Mb[2][l];
-  double dh = 0.0;  // <Hb, C2 - C1>
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      double hb = 0.0, db = 0.0;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        db += Gb[i][k] * N[j][k];
-        hb += NM[i][k] * N[j][k];
-      }
-      dh += hb * (C2[6 * i + j] - C1[6 * i + j]);
-      const double cb = Cb[6 * i + j];
-      if (C1b) C1b[6 * i + j] = c1 * cb + c2 * hb + db;
-      if (C2b) C2b[6 * i + j] = c2 * cb + c1 * hb - db;
-    }
-  c1b = dd - (1.0 - 2.0 * c1) * dx + dh;
-  nmat_adj(Nb, nb);
+  }
+  c1b = dd - (1.0 - 2.0 * c1) * dx + sum8(own ? dh : 0.0);
+  // adjoint of N with respect to n: every row adds where n enters it
+  nb[0] = sum8(!own ? 0.0 : (row == 0 ? Nb[0] : (row == 4 ? SQ2H * Nb[2] : (row == 5 ? SQ2H * Nb[1] : 0.0))));
+  nb[1] = sum8(!own ? 0.0 : (row == 1 ? Nb[1] : (row == 3 ? SQ2H * Nb[2] : (row == 5 ? SQ2H * Nb[0] : 0.0))));
+  nb[2] = sum8(!own ? 0.0 : (row == 2 ? Nb[2] : (row == 3 ? SQ2H * Nb[1] : (row == 4 ? SQ2H * Nb[0] : 0.0))));
 }
 
-// threads of an offline work-group (one sample): the bottom level of a depth-8
-// tree has 128 laminates; deeper trees loop. Small groups leave the reverse
-// mode of a laminate its full register budget.
-constexpr int OFF_THREADS = 128;
+// threads of an offline work-group (one sample): 64 laminates at a time, half
+// the bottom level of a depth-8 tree
+constexpr int OFF_THREADS = 512;
 
 struct OffArgs {
   int K, nleaf;
@@ -301,170 +306,161 @@ struct OffArgs {
   const double* C2;
   const double* Cb;    // [S][36] targets, or null
   const int* idx;      // [B] sample of each block, or null (block = sample)
-  double* Cnode;       // [B][nleaf][36] (heap index 1 .. nleaf - 1)
+  double* Cnode;       // [B][nleaf][36] (heap index 1 .. nleaf - 1) of trees that do not fit into LDS
   double* D;           // [B][36] prediction, or null
   double* err;         // [B] relative l1 errors, or null
-  double* Cadj;        // [B][nleaf][36] adjoints (backward)
-  double* grad;        // [B][nparam] per-sample gradients (backward)
-  int B;
-  double q;
+  double* grad;        // [B][nparam] gradients of every sample's error, or null (forward only)
 };
 
-// subtree weights, heap order, in LDS
-__device__ void subtree_weights(const OffArgs& a, double* wsub) {
+// Trees up to this depth keep their nodes' stiffnesses in LDS (72 KB at 8).
+constexpr int OFF_LDS_K = 8;
+constexpr size_t off_lds(int nleaf, bool nodes) {
+  return sizeof(double) * ((size_t)4 * nleaf + (OFF_THREADS / 8) * SCR8 + (nodes ? (size_t)nleaf * 36 : 0));
+}
+
+// Forward and, with a.grad, reverse mode of one sample: the effective
+// stiffness and its error e_s = |T - C|_1 / |T|_1, then de_s / dparameters
+// (the batch's loss weighs them by dJ/de_s, which needs all errors, in the
+// update kernel). A node's adjoint takes the place of its stiffness, which its
+// parent's reverse step is the last to read.
+template <bool NODES>
+__global__ void __launch_bounds__(OFF_THREADS) k_dmn_sample(OffArgs a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double* wsub = reinterpret_cast<double*>(smem_raw);  // subtree weights, heap order
+  double* wbar = wsub + 2 * a.nleaf;
+  double* scr = wbar + 2 * a.nleaf + (threadIdx.x >> 3) * SCR8;
+  double* node = NODES ? wbar + 2 * a.nleaf + (OFF_THREADS / 8) * SCR8 : a.Cnode + (long long)blockIdx.x * a.nleaf * 36;
+  __shared__ double den_s;
+  const int s = blockIdx.x;
+  const int sample = a.idx ? a.idx[s] : s;
   const int nleaf = a.nleaf;
+  const int tid = threadIdx.x, nth = blockDim.x;
+  const int row = min(tid & 7, 5);
+  const bool own = (tid & 7) < 6;
   const double* v = a.p + 3 * (nleaf - 1);
-  for (int l = threadIdx.x; l < nleaf; l += blockDim.x) wsub[nleaf + l] = fmax(v[l], 0.0);
+  for (int l = tid; l < nleaf; l += nth) wsub[nleaf + l] = fmax(v[l], 0.0);
   __syncthreads();
   for (int cnt = nleaf >> 1; cnt >= 1; cnt >>= 1) {
-    for (int j = threadIdx.x; j < cnt; j += blockDim.x) wsub[cnt + j] = wsub[2 * (cnt + j)] + wsub[2 * (cnt + j) + 1];
+    for (int j = tid; j < cnt; j += nth) wsub[cnt + j] = wsub[2 * (cnt + j)] + wsub[2 * (cnt + j) + 1];
     __syncthreads();
   }
-}
-
-__device__ __forceinline__ const double* child_C(const OffArgs& a, int s, int sample, int h) {
-  if (h >= a.nleaf) {
-    const int l = h - a.nleaf;
-    return ((l & 1) ? a.C2 : a.C1) + (long long)sample * 36;
-  }
-  return a.Cnode + ((long long)s * a.nleaf + h) * 36;
-}
-
-__global__ void __launch_bounds__(OFF_THREADS) k_dmn_fwd(OffArgs a) {
-  __shared__ double wsub[2 * (1 << DMN_MAX_K)];
-  const int s = blockIdx.x;
-  const int sample = a.idx ? a.idx[s] : s;
-  subtree_weights(a, wsub);
-  for (int cnt = a.nleaf >> 1; cnt >= 1; cnt >>= 1) {
-    for (int j = threadIdx.x; j < cnt; j += blockDim.x) {
+  const auto child = [&](int h) -> const double* {
+    if (h >= nleaf) return (((h - nleaf) & 1) ? a.C2 : a.C1) + (long long)sample * 36;
+    return node + h * 36;
+  };
+  const auto fraction = [&](int h) {
+    const double wl = wsub[2 * h], sw = wl + wsub[2 * h + 1];
+    return sw > 0.0 ? wl / sw : 0.5;
+  };
+  for (int cnt = nleaf >> 1; cnt >= 1; cnt >>= 1) {
+    for (int j = tid >> 3; j < cnt; j += nth >> 3) {
       const int h = cnt + j;
-      const double wl = wsub[2 * h], wr = wsub[2 * h + 1], sw = wl + wr;
-      const double c1 = sw > 0.0 ? wl / sw : 0.5;
       double n[3], len;
-      unit(a.p + 3 * param_of(h, a.nleaf), n, len);
-      lam_fwd(child_C(a, s, sample, 2 * h), child_C(a, s, sample, 2 * h + 1), c1, n,
-              a.Cnode + ((long long)s * a.nleaf + h) * 36);
+      unit(a.p + 3 * param_of(h, nleaf), n, len);
+      lam_fwd8(child(2 * h), child(2 * h + 1), fraction(h), n, node + h * 36, row, own, scr);
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    const double* C = a.Cnode + ((long long)s * a.nleaf + 1) * 36;
-    if (a.D)
-      for (int i = 0; i < 36; ++i) a.D[(long long)s * 36 + i] = C[i];
-    if (a.err && a.Cb) {
-      const double* T = a.Cb + (long long)sample * 36;
-      double num = 0.0, den = 0.0;
-      for (int i = 0; i < 36; ++i) {
-        num += fabs(T[i] - C[i]);
-        den += fabs(T[i]);
-      }
-      a.err[s] = num / den;
-    }
-  }
-}
-
-// per-sample gradient of J1 = (1/B) (sum_s e_s^q)^(1/q) with respect to all parameters
-__global__ void __launch_bounds__(OFF_THREADS) k_dmn_bwd(OffArgs a) {
-  __shared__ double wsub[2 * (1 << DMN_MAX_K)];
-  __shared__ double wbar[2 * (1 << DMN_MAX_K)];
-  const int s = blockIdx.x;
-  const int sample = a.idx ? a.idx[s] : s;
-  const int nleaf = a.nleaf;
-  subtree_weights(a, wsub);
-  double* grad = a.grad + (long long)s * (3 * (nleaf - 1) + nleaf);
-  if (threadIdx.x == 0) {
-    double sq = 0.0;
-    for (int b = 0; b < a.B; ++b) sq += pow(a.err[b], a.q);
-    const double e = a.err[s];
-    // dJ1/de_s = (1/B) (sum e^q)^(1/q - 1) e_s^(q - 1)
-    const double f = sq > 0.0 ? pow(sq, 1.0 / a.q - 1.0) * pow(e, a.q - 1.0) / a.B : 0.0;
-    const double* T = a.Cb + (long long)sample * 36;
-    const double* C = a.Cnode + ((long long)s * nleaf + 1) * 36;
-    double den = 0.0;
-    for (int i = 0; i < 36; ++i) den += fabs(T[i]);
-    double* R = a.Cadj + ((long long)s * nleaf + 1) * 36;
+  double* root = node + 36;
+  if (a.D && tid < 36) a.D[(long long)s * 36 + tid] = root[tid];
+  const double* Tg = a.Cb ? a.Cb + (long long)sample * 36 : nullptr;
+  if (Tg && tid == 0) {
+    double num = 0.0, den = 0.0;
     for (int i = 0; i < 36; ++i) {
-      const double d = T[i] - C[i];
-      R[i] = d > 0.0 ? -f / den : (d < 0.0 ? f / den : 0.0);
+      num += fabs(Tg[i] - root[i]);
+      den += fabs(Tg[i]);
     }
+    a.err[s] = num / den;
+    den_s = den;
     wbar[1] = 0.0;  // the mixing penalty is added once per batch by the update kernel
   }
+  if (!a.grad) return;
   __syncthreads();
+  if (tid < 36) {
+    const double d = Tg[tid] - root[tid];
+    root[tid] = d > 0.0 ? -1.0 / den_s : (d < 0.0 ? 1.0 / den_s : 0.0);
+  }
+  __syncthreads();
+  double* grad = a.grad + (long long)s * (3 * (nleaf - 1) + nleaf);
   for (int cnt = 1; cnt < nleaf; cnt <<= 1) {
-    for (int j = threadIdx.x; j < cnt; j += blockDim.x) {
+    for (int j = tid >> 3; j < cnt; j += nth >> 3) {
       const int h = cnt + j;
-      const double wl = wsub[2 * h], wr = wsub[2 * h + 1], sw = wl + wr;
-      const double c1 = sw > 0.0 ? wl / sw : 0.5;
       const int pi = param_of(h, nleaf);
       double n[3], len;
       unit(a.p + 3 * pi, n, len);
       const bool inner = 2 * h < nleaf;
       double c1b, nb[3];
-      lam_bwd(child_C(a, s, sample, 2 * h), child_C(a, s, sample, 2 * h + 1), c1, n,
-              a.Cadj + ((long long)s * nleaf + h) * 36,
-              inner ? a.Cadj + ((long long)s * nleaf + 2 * h) * 36 : nullptr,
-              inner ? a.Cadj + ((long long)s * nleaf + 2 * h + 1) * 36 : nullptr, c1b, nb);
-      // n = m / |m|
-      const double dn = nb[0] * n[0] + nb[1] * n[1] + nb[2] * n[2];
-      const double il = len > 0.0 ? 1.0 / len : 0.0;
+      lam_bwd8(child(2 * h), child(2 * h + 1), fraction(h), n, node + h * 36, inner ? node + 2 * h * 36 : nullptr,
+               inner ? node + (2 * h + 1) * 36 : nullptr, c1b, nb, row, own, scr);
+      if ((tid & 7) == 0) {
+        // n = m / |m|
+        const double dn = nb[0] * n[0] + nb[1] * n[1] + nb[2] * n[2];
+        const double il = len > 0.0 ? 1.0 / len : 0.0;
 #pragma unroll
-      for (int k = 0; k < 3; ++k) grad[3 * pi + k] = (nb[k] - dn * n[k]) * il;
-      // c1 = wl / (wl + wr); the node weight wl + wr passes its adjoint down
-      double gl = wbar[h], gr = wbar[h];
-      if (sw > 0.0) {
-        gl += c1b * wr / (sw * sw);
-        gr -= c1b * wl / (sw * sw);
+        for (int k = 0; k < 3; ++k) grad[3 * pi + k] = (nb[k] - dn * n[k]) * il;
+        // c1 = wl / (wl + wr); the node weight wl + wr passes its adjoint down
+        const double wl = wsub[2 * h], wr = wsub[2 * h + 1], sw = wl + wr;
+        double gl = wbar[h], gr = wbar[h];
+        if (sw > 0.0) {
+          gl += c1b * wr / (sw * sw);
+          gr -= c1b * wl / (sw * sw);
+        }
+        wbar[2 * h] = gl;
+        wbar[2 * h + 1] = gr;
       }
-      wbar[2 * h] = gl;
-      wbar[2 * h + 1] = gr;
     }
     __syncthreads();
   }
-  const double* v = a.p + 3 * (nleaf - 1);
-  for (int l = threadIdx.x; l < nleaf; l += blockDim.x)
-    grad[3 * (nleaf - 1) + l] = v[l] > 0.0 ? wbar[nleaf + l] : 0.0;
+  for (int l = tid; l < nleaf; l += nth) grad[3 * (nleaf - 1) + l] = v[l] > 0.0 ? wbar[nleaf + l] : 0.0;
 }
 
 struct StepArgs {
   int nparam, nnode, nleaf, B;
   double* p;
   double *a1, *a2, *a2max;
-  const double* grad;   // [B][nparam]
-  const double* err;    // [B]
+  const double* grad;   // [B][nparam] of the samples' errors
+  double* err;          // [B] errors; their dJ/de_s afterwards
   double* gout;         // [nparam] summed gradient (or null)
   double* loss;         // loss of this batch (or null)
   double* loss_acc;     // accumulated batch losses (or null)
   double lr, q, penalty, beta1, beta2, eps;
-  long long t;          // step number (1-based), for the bias corrections
+  double bc1, bc2;      // bias corrections of this step
   int update;
 };
 
-// sum of the per-sample gradients (fixed order) plus the mixing penalty,
-// loss value, AMSGrad update
-__global__ void __launch_bounds__(1024) k_dmn_step(StepArgs a) {
-  __shared__ double red[32];
-  __shared__ double wsum;
+// loss value J = (1/B) (sum_s e_s^q)^(1/q) + penalty (sum w - 1)^2, its gradient
+// (the per-sample gradients weighed by dJ/de_s and summed in a fixed order,
+// plus the mixing penalty) and the AMSGrad update. Latency-bound: the powers of
+// the errors are formed in parallel and the sum over the samples is unrolled.
+constexpr int STEP_THREADS = 1024;
+__global__ void __launch_bounds__(STEP_THREADS) k_dmn_step(StepArgs a) {
+  __shared__ double red[2 * 16];
+  __shared__ double tot[2];
   const double* v = a.p + 3 * a.nnode;
-  double part = 0.0;
-  for (int l = threadIdx.x; l < a.nleaf; l += blockDim.x) part += fmax(v[l], 0.0);
-  double r[1] = {part};
-  block_sum<1>(r, red);
+  double r[2] = {0.0, 0.0};
+  for (int l = threadIdx.x; l < a.nleaf; l += blockDim.x) r[0] += fmax(v[l], 0.0);
+  for (int b = threadIdx.x; b < a.B; b += blockDim.x) r[1] += pow(a.err[b], a.q);
+  block_sum<2>(r, red);
   if (threadIdx.x == 0) {
-    wsum = r[0];
+    tot[0] = r[0];
+    tot[1] = r[1];
     if (a.loss || a.loss_acc) {
-      double sq = 0.0;
-      for (int b = 0; b < a.B; ++b) sq += pow(a.err[b], a.q);
-      const double J = pow(sq, 1.0 / a.q) / a.B + a.penalty * (r[0] - 1.0) * (r[0] - 1.0);
+      const double J = pow(r[1], 1.0 / a.q) / a.B + a.penalty * (r[0] - 1.0) * (r[0] - 1.0);
       if (a.loss) *a.loss = J;
       if (a.loss_acc) *a.loss_acc += J;
     }
   }
   __syncthreads();
-  const double pen = 2.0 * a.penalty * (wsum - 1.0);
-  const double bc1 = 1.0 - pow(a.beta1, (double)a.t), bc2 = 1.0 - pow(a.beta2, (double)a.t);
+  // dJ/de_s = (1/B) (sum e^q)^(1/q - 1) e_s^(q - 1)
+  const double sq = tot[1];
+  for (int b = threadIdx.x; b < a.B; b += blockDim.x)
+    a.err[b] = sq > 0.0 ? pow(sq, 1.0 / a.q - 1.0) * pow(a.err[b], a.q - 1.0) / a.B : 0.0;
+  __syncthreads();
+  const double pen = 2.0 * a.penalty * (tot[0] - 1.0);
   for (int i = threadIdx.x; i < a.nparam; i += blockDim.x) {
     double g = 0.0;
-    for (int b = 0; b < a.B; ++b) g += a.grad[(long long)b * a.nparam + i];
+#pragma unroll 8
+    for (int b = 0; b < a.B; ++b) g += a.err[b] * a.grad[(long long)b * a.nparam + i];
     if (i >= 3 * a.nnode && v[i - 3 * a.nnode] > 0.0) g += pen;
     if (a.gout) a.gout[i] = g;
     if (!a.update) continue;
@@ -474,7 +470,7 @@ __global__ void __launch_bounds__(1024) k_dmn_step(StepArgs a) {
     a.a1[i] = m1;
     a.a2[i] = m2;
     a.a2max[i] = mx;
-    a.p[i] -= a.lr * (m1 / bc1) / (sqrt(mx / bc2) + a.eps);
+    a.p[i] -= a.lr * (m1 / a.bc1) / (sqrt(mx / a.bc2) + a.eps);
   }
 }
 
@@ -487,7 +483,27 @@ U* dalloc_into(std::vector<void*>& allocs, size_t count) {
   return static_cast<U*>(ptr);
 }
 
-int threads_for(int nleaf) { return std::min(OFF_THREADS, std::max(64, nleaf / 2)); }
+void launch_samples(const OffArgs& a, int B, hipStream_t stream) {
+  const int threads = std::min(OFF_THREADS, std::max(64, 4 * a.nleaf));  // eight lanes a laminate
+  const bool nodes = a.K <= OFF_LDS_K;
+  const size_t lds = off_lds(a.nleaf, nodes);
+  if (nodes) {
+    if (lds > 65536)
+      hip_check(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dmn_sample<true>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
+                "hipFuncSetAttribute");
+    hipLaunchKernelGGL(k_dmn_sample<true>, dim3(B), dim3(threads), lds, stream, a);
+  } else {
+    hipLaunchKernelGGL(k_dmn_sample<false>, dim3(B), dim3(threads), lds, stream, a);
+  }
+  hip_check(hipGetLastError(), "k_dmn_sample");
+}
+// node stiffnesses in memory, for the trees that do not fit into LDS
+size_t node_doubles(int K, long long B) { return K <= OFF_LDS_K ? 1 : (size_t)B * ((size_t)1 << K) * 36; }
+void launch_step(const StepArgs& s, hipStream_t stream) {
+  hipLaunchKernelGGL(k_dmn_step, dim3(1), dim3(STEP_THREADS), 0, stream, s);
+  hip_check(hipGetLastError(), "k_dmn_step");
+}
 
 }  // namespace
 
@@ -593,11 +609,9 @@ void Dmn::homogenize(long long n, const double* C1, const double* C2, double* Co
   a.p = p;
   a.C1 = d.C1;
   a.C2 = d.C2;
-  a.Cnode = dalloc_into<double>(tmp, (size_t)n * nleaf * 36);
+  a.Cnode = dalloc_into<double>(tmp, node_doubles(K, n));
   a.D = dalloc_into<double>(tmp, (size_t)n * 36);
-  a.B = (int)n;
-  hipLaunchKernelGGL(k_dmn_fwd, dim3((unsigned)n), dim3(threads_for(nleaf)), 0, nullptr, a);
-  hip_check(hipGetLastError(), "k_dmn_fwd");
+  launch_samples(a, (int)n, nullptr);
   hip_check(hipMemcpy(Cout, a.D, 36 * n * sizeof(double), hipMemcpyDeviceToHost), "hipMemcpy");
   for (void* ptr : tmp) (void)hipFree(ptr);
 }
@@ -615,14 +629,10 @@ double Dmn::loss_grad(long long n, const double* C1, const double* C2, const dou
   a.C1 = d.C1;
   a.C2 = d.C2;
   a.Cb = d.Cb;
-  a.Cnode = dalloc_into<double>(tmp, (size_t)n * nleaf * 36);
-  a.Cadj = dalloc_into<double>(tmp, (size_t)n * nleaf * 36);
+  a.Cnode = dalloc_into<double>(tmp, node_doubles(K, n));
   a.err = dalloc_into<double>(tmp, n);
   a.grad = dalloc_into<double>(tmp, (size_t)n * nparam);
-  a.B = (int)n;
-  a.q = sc.q;
-  hipLaunchKernelGGL(k_dmn_fwd, dim3((unsigned)n), dim3(threads_for(nleaf)), 0, nullptr, a);
-  hipLaunchKernelGGL(k_dmn_bwd, dim3((unsigned)n), dim3(threads_for(nleaf)), 0, nullptr, a);
+  launch_samples(a, (int)n, nullptr);
   StepArgs s{};
   s.nparam = nparam;
   s.nnode = nnode;
@@ -635,12 +645,10 @@ double Dmn::loss_grad(long long n, const double* C1, const double* C2, const dou
   s.loss = dalloc_into<double>(tmp, 1);
   s.q = sc.q;
   s.penalty = sc.penalty;
-  s.t = 1;
   s.update = 0;
   s.beta1 = sc.beta1;
   s.beta2 = sc.beta2;
-  hipLaunchKernelGGL(k_dmn_step, dim3(1), dim3(1024), 0, nullptr, s);
-  hip_check(hipGetLastError(), "dmn kernels");
+  launch_step(s, nullptr);
   std::vector<double> g(nparam);
   double J = 0.0;
   hip_check(hipMemcpy(g.data(), s.gout, nparam * sizeof(double), hipMemcpyDeviceToHost), "hipMemcpy");
@@ -666,12 +674,9 @@ void Dmn::train(long long n, const double* C1, const double* C2, const double* C
   a.C1 = d.C1;
   a.C2 = d.C2;
   a.Cb = d.Cb;
-  a.Cnode = dalloc_into<double>(tmp, (size_t)batch * nleaf * 36);
-  a.Cadj = dalloc_into<double>(tmp, (size_t)batch * nleaf * 36);
+  a.Cnode = dalloc_into<double>(tmp, node_doubles(K, batch));
   a.err = dalloc_into<double>(tmp, batch);
   a.grad = dalloc_into<double>(tmp, (size_t)batch * nparam);
-  a.B = batch;
-  a.q = sc.q;
   const long long nb = n / batch;  // incomplete batches are dropped
   int* idx = dalloc_into<int>(tmp, (size_t)nb * batch);
   double* lacc = dalloc_into<double>(tmp, std::max(epochs, 1));
@@ -705,12 +710,12 @@ void Dmn::train(long long n, const double* C1, const double* C2, const double* C
     s.loss_acc = lacc + e;
     for (long long b = 0; b < nb; ++b) {
       a.idx = idx + b * batch;
-      hipLaunchKernelGGL(k_dmn_fwd, dim3(batch), dim3(threads_for(nleaf)), 0, nullptr, a);
-      hipLaunchKernelGGL(k_dmn_bwd, dim3(batch), dim3(threads_for(nleaf)), 0, nullptr, a);
-      s.t = ++steps;
-      hipLaunchKernelGGL(k_dmn_step, dim3(1), dim3(1024), 0, nullptr, s);
+      launch_samples(a, batch, nullptr);
+      ++steps;
+      s.bc1 = 1.0 - std::pow(sc.beta1, (double)steps);
+      s.bc2 = 1.0 - std::pow(sc.beta2, (double)steps);
+      launch_step(s, nullptr);
     }
-    hip_check(hipGetLastError(), "dmn training kernels");
   }
   hip_check(hipDeviceSynchronize(), "dmn training");
   if (loss_hist && epochs > 0) {

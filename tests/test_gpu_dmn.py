@@ -325,3 +325,26 @@ def test_online_predictor_switched_off_and_on_again_starts_over():
     a.close()
     b.close()
     net.close()
+
+
+@pytest.mark.parametrize("K,count", [(1, 3), (2, 7), (8, 2), (9, 2)])
+def test_gradients_at_the_depth_limits(K, count):
+    """One laminate, fewer laminates than a wave holds, the deepest tree whose
+    nodes stay in LDS and the first that does not: prediction, loss and
+    gradients against the oracle, at the tolerances of the tests above."""
+    rng = np.random.default_rng(80 + K)
+    m, v = random_params(K, rng)
+    C1, C2 = samples(count, rng)
+    ref = dmn.homogenize_np(C1, C2, m, v)
+    Ceff = ref * rng.uniform(0.9, 1.1, (count, 6, 6))
+    J, gm, gv = dmn.loss_and_grad(C1, C2, Ceff, m, v)
+    with hom.Dmn(K) as net:
+        net.set_params(m, v)
+        D = net.homogenize(C1, C2)
+        Jg, gmg, gvg = net.loss_grad(C1, C2, Ceff)
+    em = np.abs(gmg - gm).max() / np.abs(gm).max()
+    ev = np.abs(gvg - gv).max() / np.abs(gv).max()
+    print(f"K={K}: loss {abs(Jg - J) / J:.2e} grad m {em:.2e} grad v {ev:.2e}", flush=True)
+    assert np.abs(D - ref).max() <= 1e-10 * np.abs(ref).max()
+    assert abs(Jg - J) <= 1e-10 * J
+    assert em <= 1e-7 and ev <= 1e-7
