@@ -44,10 +44,10 @@ struct Mlp {
   long long work_rows = 0;
   std::vector<void*> work;
   float *xs = nullptr, *zs[MLP_LAYERS - 1] = {}, *as[MLP_LAYERS - 1] = {}, *yhat = nullptr, *dy = nullptr;
-  float *da = nullptr, *dz = nullptr, *xb = nullptr, *tb = nullptr, *rwb = nullptr, *lpart = nullptr;
-  // split-K partials of the weight-gradient products and FP64 column-sum
-  // partials of the bias gradients (grown on demand, one set per network so
-  // that networks can train concurrently)
+  float *dz[2] = {}, *lpart = nullptr;
+  // partials of the weight gradients and FP64 partials of the bias gradients
+  // over the splits of the batch, all layers (grown on demand, one set per
+  // network so that networks can train concurrently)
   float* splitk = nullptr;
   size_t splitk_n = 0;
   double* csum = nullptr;
@@ -64,16 +64,18 @@ struct Mlp {
   void refresh(hipStream_t s);
   void ensure_work(long long rows);
   void free_work();
-  // x: device [n][n_in]; y: device [n][n_out] (physical units) or null
-  void forward(const float* x, float* y, long long n, bool precise, bool save, hipStream_t s);
+  // x: device [n][n_in]; y: device [n][n_out] (physical units) or null; idx:
+  // device rows of x, or null
+  void forward(const float* x, float* y, long long n, bool precise, bool save, hipStream_t s,
+               const int* idx = nullptr);
   // x: device raw inputs, t: device normalized targets [B][16], rw: device
   // row weights [B] or null; fills g
   double loss_grad(const float* x, const float* tnorm, long long B, bool precise, hipStream_t s,
                    const float* rw = nullptr);
-  // the gradient of loss_grad without reading the loss back; returns the
-  // number of loss partials left in lpart
-  int grad_only(const float* x, const float* tnorm, long long B, bool precise, hipStream_t s,
-                const float* rw = nullptr);
+  // the gradient's partials (splitk, csum) and the loss partials (lpart, their
+  // number is returned); idx: device rows of x, tnorm and rw, or null (all)
+  int grad_partials(const float* x, const float* tnorm, long long B, bool precise, hipStream_t s, const float* rw,
+                    const int* idx);
   void train(const float* X, const float* T, long long n, int epochs, int batch, double lr, uint64_t seed,
              const float* row_weight, float* loss_out);
   // zero the Adam moments (a later train call starts its optimizer afresh)

@@ -9,9 +9,10 @@
 // which reproduces FP32 weights for gradient checks. Bias and GELU are fused
 // into the epilogue; the layer output stays in LDS for the next layer.
 //
-// Training: FP32 backward (64 x 64-tiled GEMMs on the FP32 matrix cores for
-// dA = dZ W and dW = dZ^T A, column sums for db), weighted MSE on normalized outputs, Adam on FP32
-// master weights with refreshed bf16 copies after each step.
+// Training: FP32 backward on the FP32 matrix cores, one launch a layer (dW = dZ^T A
+// in splits of the batch, db, and dA = dZ W with gelu'), weighted MSE on normalized outputs,
+// and one launch that sums the splits, applies Adam to the FP32 master weights and refreshes
+// their bf16 copies: eight launches a step.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -37,9 +38,12 @@ typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
-constexpr int MROWS = 64;             // rows per forward work-group
 constexpr int FWD_WAVES = 8;          // waves per forward work-group
-constexpr int NRB = MROWS / 16;       // 16-row tiles per wave (every wave spans all rows)
+// Rows (over all networks) of a forward launch from which a work-group takes 64
+// of them; below, 16, so that more CUs have one. Both sides: 4096 rows of two
+// networks 21 us with 16 and 29 us with 64, 3072 of four 31 and 37; 8192 of two
+// 32 and 30, 4096 of eight 70 and 57. A row's result does not depend on the choice.
+constexpr long long kFullRows = 64 * 256;
 constexpr int NCB = MLP_W / (16 * FWD_WAVES);  // 16-column tiles per wave
 constexpr int AST = 264;              // LDS row stride of the bf16 activation tiles (16-byte aligned rows)
 
@@ -88,22 +92,25 @@ __host__ __device__ __forceinline__ long long frag_offset(int cb, int s, int K, 
   return (((long long)cb * (K / 32) + s) * 64 + lane) * 8;
 }
 
+// One network of a forward launch (blockIdx.y): its parameter arrays, whose
+// layer offsets are the same for every network.
+struct NetRef {
+  const __bf16* hi;
+  const __bf16* lo;
+  const float* w;     // FP32 parameters (the biases)
+  const float* scal;  // xmean[32] xinv[32] ymean[16] ystd[16]
+  const float* skip;  // G [16][MLP_GATES][32], c [16], then G's bf16 hi and lo parts
+  int g0, g1, g2;     // gate input indices
+};
+
 struct FwdArgs {
   const float* x;
+  const int* idx;  // row r of the launch is row idx[r] of x, or null (row r)
   long long n;
   int n_in, n_out;
-  const float* xmean;
-  const float* xinv;
-  const float* ymean;
-  const float* ystd;
-  const float* skip;  // G [16][MLP_GATES][32], c [16]
-  const __bf16* skip_hi;  // G rounded to bf16
-  const __bf16* skip_lo;  // the remainder G - hi, rounded to bf16
-  int g0, g1, g2;     // gate input indices
-  const __bf16* whi[MLP_LAYERS];
-  const __bf16* wlo[MLP_LAYERS];
-  const float* bias[MLP_LAYERS];
-  float* y;      // [n][n_out] outputs in physical units (optional)
+  int woff[MLP_LAYERS], boff[MLP_LAYERS];
+  NetRef net[HOM_ENSEMBLE_MAX_NETS];
+  float* y;      // [networks][n][n_out] outputs in physical units (optional)
   float* yhat;   // [n][16] normalized outputs (optional)
   float* xs;     // [n][32] normalized inputs (optional, training)
   float* zs[MLP_LAYERS - 1];  // [n][256] pre-activations (optional)
@@ -112,8 +119,12 @@ struct FwdArgs {
 
 // SAVE: keep the normalized inputs, pre-activations, activations and
 // normalized outputs for the backward pass (training); inference writes y only
-template <int PRECISE, bool SAVE>
+// MROWS: rows per work-group, 64 where that fills the chip (the weights are
+// read once a work-group), 16 for fewer rows, whose launches are bound by the
+// latency of a work-group's layers. A row's arithmetic is the same in both.
+template <int PRECISE, bool SAVE, int MROWS>
 __global__ void __launch_bounds__(FWD_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4))) k_mlp_fwd(FwdArgs a) {
+  constexpr int NRB = MROWS / 16;  // 16-row tiles per wave (every wave spans all rows)
   // The tile's activations live in LDS already split into bf16 hi + lo: each
   // value is split once, by the lane that produced it, and every wave reads
   // its MFMA fragments directly.
@@ -124,11 +135,17 @@ __global__ void __launch_bounds__(FWD_WAVES * 64) __attribute__((amdgpu_waves_pe
   const int wave = tid >> 6;
   const int lane = tid & 63;
   const long long row0 = (long long)blockIdx.x * MROWS;
+  const NetRef& net = a.net[blockIdx.y];
+  const float *xmean = net.scal, *xinv = net.scal + MLP_IN;
+  const float *ymean = net.scal + 2 * MLP_IN, *ystd = ymean + MLP_OUT;
+  const __bf16* skip_hi = reinterpret_cast<const __bf16*>(net.skip + MLP_OUT * MLP_GATES * MLP_IN + MLP_OUT);
+  const __bf16* skip_lo = skip_hi + MLP_OUT * MLP_GATES * MLP_IN;
+  float* y = a.y ? a.y + (long long)blockIdx.y * a.n * a.n_out : nullptr;
   for (int i = tid; i < MROWS * MLP_IN; i += FWD_WAVES * 64) {
     const int r = i / MLP_IN, k = i % MLP_IN;
     const long long gr = row0 + r;
     float v = 0.0f;
-    if (gr < a.n && k < a.n_in) v = (a.x[gr * a.n_in + k] - a.xmean[k]) * a.xinv[k];
+    if (gr < a.n && k < a.n_in) v = (a.x[(a.idx ? a.idx[gr] : gr) * a.n_in + k] - xmean[k]) * xinv[k];
     const __bf16 h = (__bf16)v;
     ahi[r * AST + k] = h;
     alo[r * AST + k] = (__bf16)(v - (float)h);
@@ -141,14 +158,15 @@ __global__ void __launch_bounds__(FWD_WAVES * 64) __attribute__((amdgpu_waves_pe
 #pragma unroll 1
   for (int l = 0; l < MLP_LAYERS - 1; ++l) {
     const int K = l == 0 ? MLP_IN : MLP_W;
-    const __bf16* whi = a.whi[l];
-    const __bf16* wlo = a.wlo[l];
+    const __bf16* whi = net.hi + a.woff[l];
+    const __bf16* wlo = net.lo + a.woff[l];
+    const float* bias = net.w + a.boff[l];
     // lane: row m = rb 16 + lrow, outputs nn0 .. nn0 + 3 of tile cb; the
     // bias enters as the first product's accumulator input
     floatx4_t bv[NCB];
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb)
-      bv[cb] = *reinterpret_cast<const floatx4_t*>(a.bias[l] + wave * (16 * NCB) + cb * 16 + (lane >> 4) * 4);
+      bv[cb] = *reinterpret_cast<const floatx4_t*>(bias + wave * (16 * NCB) + cb * 16 + (lane >> 4) * 4);
     floatx4_t acc[NRB][NCB];
     bf16x8_t bh[NCB], bl[NCB];
 #pragma unroll
@@ -247,8 +265,9 @@ __global__ void __launch_bounds__(FWD_WAVES * 64) __attribute__((amdgpu_waves_pe
   // output layer: each wave 16 rows x 16 outputs
   if (wave < MROWS / 16) {
     const int l = MLP_LAYERS - 1;
-    const __bf16* whi = a.whi[l];
-    const __bf16* wlo = a.wlo[l];
+    const __bf16* whi = net.hi + a.woff[l];
+    const __bf16* wlo = net.lo + a.woff[l];
+    const float* bias = net.w + a.boff[l];
     floatx4_t acc = floatx4_t{0.f, 0.f, 0.f, 0.f};
     for (int k0 = 0; k0 < MLP_W; k0 += 32) {
       const int o = (wave * 16 + lrow) * AST + k0 + kq;
@@ -267,7 +286,7 @@ __global__ void __launch_bounds__(FWD_WAVES * 64) __attribute__((amdgpu_waves_pe
     // tile whose layout matches acc (x and G split into bf16 hi + lo parts,
     // three products: about 16 significant bits)
     floatx4_t sk = floatx4_t{0.f, 0.f, 0.f, 0.f};
-    if (a.y) {  // uniform over the work-group
+    if (y) {  // uniform over the work-group
       bf16x8_t xh, xl;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
@@ -279,7 +298,7 @@ __global__ void __launch_bounds__(FWD_WAVES * 64) __attribute__((amdgpu_waves_pe
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float* xr = xin + (wave * 16 + (lane >> 4) * 4 + i) * (MLP_IN + 1);
-        const float va = xr[a.g0], vb = xr[a.g1], vc = xr[a.g2];
+        const float va = xr[net.g0], vb = xr[net.g1], vc = xr[net.g2];
         const float s[MLP_GATES] = {1.f, va, va * va, va * va * va, vb, vb * vb, vb * vb * vb,
                                     vc, vc * vc, vc * vc * vc};
 #pragma unroll
@@ -288,8 +307,8 @@ __global__ void __launch_bounds__(FWD_WAVES * 64) __attribute__((amdgpu_waves_pe
       const size_t gb = (size_t)lrow * MLP_GATES * MLP_IN + kq;  // output lrow, inputs kq ..
 #pragma unroll
       for (int gi = 0; gi < MLP_GATES; ++gi) {
-        const bf16x8_t gh = *reinterpret_cast<const bf16x8_t*>(a.skip_hi + gb + gi * MLP_IN);
-        const bf16x8_t gl = *reinterpret_cast<const bf16x8_t*>(a.skip_lo + gb + gi * MLP_IN);
+        const bf16x8_t gh = *reinterpret_cast<const bf16x8_t*>(skip_hi + gb + gi * MLP_IN);
+        const bf16x8_t gl = *reinterpret_cast<const bf16x8_t*>(skip_lo + gb + gi * MLP_IN);
         floatx4_t t = floatx4_t{0.f, 0.f, 0.f, 0.f};
         t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, gh, t, 0, 0, 0);
         t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl, gh, t, 0, 0, 0);
@@ -297,7 +316,7 @@ __global__ void __launch_bounds__(FWD_WAVES * 64) __attribute__((amdgpu_waves_pe
 #pragma unroll
         for (int i = 0; i < 4; ++i) sk[i] += sg[i][gi] * t[i];
       }
-      const float c = a.skip[MLP_OUT * MLP_GATES * MLP_IN + lrow];
+      const float c = net.skip[MLP_OUT * MLP_GATES * MLP_IN + lrow];
 #pragma unroll
       for (int i = 0; i < 4; ++i) sk[i] += c;
     }
@@ -306,72 +325,163 @@ __global__ void __launch_bounds__(FWD_WAVES * 64) __attribute__((amdgpu_waves_pe
       const int m = wave * 16 + (lane >> 4) * 4 + i;
       const long long gr = row0 + m;
       if (gr >= a.n) continue;
-      const float z = acc[i] + a.bias[l][lrow];
+      const float z = acc[i] + bias[lrow];
       if (SAVE) a.yhat[gr * MLP_OUT + lrow] = z;
-      if (a.y && lrow < a.n_out) a.y[gr * a.n_out + lrow] = z * a.ystd[lrow] + a.ymean[lrow] + sk[i];
+      if (y && lrow < a.n_out) y[gr * a.n_out + lrow] = z * ystd[lrow] + ymean[lrow] + sk[i];
     }
   }
 }
 
-// C[M][N] = op(A) op(B) (+ beta C), row-major, FP32. op(A) = A (M x K, lda)
-// or A^T (A stored K x M); op(B) = B (K x N, ldb) or B^T (B stored N x K).
-// C = op(A) op(B) (+ beta C), 64 x 64 tiles. With gridDim.z > 1 the inner
-// dimension is split in chunks of kc: work-group z takes rows z kc .. of A
-// and B (A, B stored [k][*], the weight-gradient form) and writes its own
-// partial C + z M ldc.
-template <bool TA, bool TB>
-__global__ void __launch_bounds__(256) k_gemm(int M, int N, int K, const float* __restrict__ A, int lda,
-                                              const float* __restrict__ B, int ldb, float* __restrict__ C, int ldc,
-                                              float beta, int kc = 0) {
-  __shared__ float As[16][65];
-  __shared__ float Bs[16][65];
-  if (gridDim.z > 1) {
-    const int k0 = blockIdx.z * kc;
-    K = min(kc, K - k0);
-    A += (long long)k0 * lda;
-    B += (long long)k0 * ldb;
-    C += (long long)blockIdx.z * M * ldc;
+// ---------------------------------------------------------------------------
+// backward of one layer: both products, the bias gradient and gelu' in one launch
+// ---------------------------------------------------------------------------
+// Work-groups of two kinds, 64 x 64 tiles each, on the FP32 matrix cores
+// (v_mfma_f32_16x16x4_f32: exact products, FP32 accumulation):
+//   dW[N][K] = dZ^T A over a split of the batch rows (partials, summed in a
+//   fixed order by the update), and the split's FP64 column sums of dZ (db);
+//   dZ_prev (B x K) = (dZ W) gelu'(Z_prev), if there is a layer before.
+// The inner dimension advances in slabs of 64, the next slab's loads in flight
+// during the products. With slabs of 16 loaded and used in turn a product was a
+// chain of sixteen memory latencies; the accumulation order of every output is
+// the same. A batch of 4096: 21 us a 256 x 256 layer (1.1 GFLOP, 50 TFLOP/s; bound by
+// the LDS reads that feed the products) where the two products, the column sums and
+// gelu' took 40 + 30 + 17 + 6 us in launches of their own; a training step takes
+// 120 us of GPU time instead of 530.
+constexpr int BK_TILE = 64, BK_SLAB = 64;
+// LDS row pitches: a wave's four k rows lie on different banks; the odd one also
+// spreads the transposing stores of an operand whose rows run along x
+constexpr int BK_PITCH = 80, BK_PITCH_X = 81;
+constexpr int BK_VEC = BK_SLAB * BK_TILE / 4 / 256;        // 16-byte loads of a thread per slab and operand
+
+struct BackArgs {
+  int B, N, K;          // batch rows, outputs and inputs of the layer
+  const float* dZ;      // [B][N]
+  const float* A;       // [B][K] inputs of the layer
+  const float* W;       // [N][K]
+  const float* Zp;      // [B][K] pre-activations of the layer before
+  float* dZp;           // [B][K], or null
+  float* Pw;            // [splits][N][K]
+  double* Pb;           // [splits][N]
+  int kc, splits;       // batch rows of a split
+  int tn, tk, tb;       // tiles over N, K and B
+};
+
+// A slab of an operand whose rows run along the inner dimension (element
+// (k, x) at src[k ld + x], x < X, k < K; X a multiple of 4): registers, then LDS.
+__device__ __forceinline__ void slab_load_k(const float* src, int ld, int k0, int K, int x0, int X, floatx4_t (&r)[BK_VEC]) {
+#pragma unroll
+  for (int i = 0; i < BK_VEC; ++i) {
+    const int e = threadIdx.x + i * 256;
+    const int k = k0 + (e >> 4), x = x0 + (e & 15) * 4;
+    r[i] = k < K && x < X ? *reinterpret_cast<const floatx4_t*>(src + (long long)k * ld + x)
+                          : floatx4_t{0.f, 0.f, 0.f, 0.f};
   }
+}
+__device__ __forceinline__ void slab_store_k(float* S, const floatx4_t (&r)[BK_VEC]) {
+#pragma unroll
+  for (int i = 0; i < BK_VEC; ++i) {
+    const int e = threadIdx.x + i * 256;
+    *reinterpret_cast<floatx4_t*>(S + (e >> 4) * BK_PITCH + (e & 15) * 4) = r[i];
+  }
+}
+// ... and of one whose rows run along x (element (k, x) at src[x ld + k]; K a
+// multiple of 4)
+__device__ __forceinline__ void slab_load_x(const float* src, int ld, int k0, int K, int x0, int X, floatx4_t (&r)[BK_VEC]) {
+#pragma unroll
+  for (int i = 0; i < BK_VEC; ++i) {
+    const int e = threadIdx.x + i * 256;
+    const int x = x0 + (e >> 4), k = k0 + (e & 15) * 4;
+    r[i] = k < K && x < X ? *reinterpret_cast<const floatx4_t*>(src + (long long)x * ld + k)
+                          : floatx4_t{0.f, 0.f, 0.f, 0.f};
+  }
+}
+__device__ __forceinline__ void slab_store_x(float* S, const floatx4_t (&r)[BK_VEC]) {
+#pragma unroll
+  for (int i = 0; i < BK_VEC; ++i) {
+    const int e = threadIdx.x + i * 256;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) S[((e & 15) * 4 + j) * BK_PITCH_X + (e >> 4)] = r[i][j];
+  }
+}
+
+__global__ void __launch_bounds__(256) k_layer_back(BackArgs a) {
+  __shared__ __attribute__((aligned(16))) float As[BK_SLAB * BK_PITCH_X];
+  __shared__ __attribute__((aligned(16))) float Bs[BK_SLAB * BK_PITCH];
+  __shared__ double red[4][BK_TILE];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;  // the wave's 32 x 32 quarter of the tile
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  // FP32 matrix cores (v_mfma_f32_16x16x4_f32: exact products, FP32
-  // accumulation): lane l feeds A[l % 16][l / 16] and B[l / 16][l % 16] of a
-  // 16 x 4 x 16 step and holds C rows 4 (l / 16) .. + 3 of column l % 16
+  const int nw = a.tn * a.tk * a.splits;
+  const bool dw = (int)blockIdx.x < nw;  // which of the two products
+  int m0, n0, k0, k1, split = 0;
+  if (dw) {
+    const int t = blockIdx.x % (a.tn * a.tk);
+    split = blockIdx.x / (a.tn * a.tk);
+    m0 = (t / a.tk) * BK_TILE;
+    n0 = (t % a.tk) * BK_TILE;
+    k0 = split * a.kc;
+    k1 = min(a.B, k0 + a.kc);
+  } else {
+    const int t = blockIdx.x - nw;
+    m0 = (t / a.tk) * BK_TILE;
+    n0 = (t % a.tk) * BK_TILE;
+    k0 = 0;
+    k1 = a.N;
+  }
   floatx4_t acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int i = tid; i < 16 * 64; i += 256) {
-      const int kk = i / 64, mm = i % 64;
-      const int gm = m0 + mm, gk = k0 + kk;
-      float va = 0.f;
-      if (gm < M && gk < K) va = TA ? A[(long long)gk * lda + gm] : A[(long long)gm * lda + gk];
-      As[kk][mm] = va;
-      const int gn = n0 + mm;
-      float vb = 0.f;
-      if (gn < N && gk < K) vb = TB ? B[(long long)gn * ldb + gk] : B[(long long)gk * ldb + gn];
-      Bs[kk][mm] = vb;
+  const int pa = dw ? BK_PITCH : BK_PITCH_X;
+  const bool bias = dw && n0 == 0;
+  double bsum = 0.0;  // column m0 + lane of dZ, rows k0 + wave, k0 + wave + 4, ..
+  floatx4_t ra[BK_VEC], rb[BK_VEC];
+  const auto load = [&](int k) {
+    if (dw) {
+      slab_load_k(a.dZ, a.N, k, k1, m0, a.N, ra);
+      slab_load_k(a.A, a.K, k, k1, n0, a.K, rb);
+    } else {
+      slab_load_x(a.dZ, a.N, k, k1, m0, a.B, ra);
+      slab_load_k(a.W, a.K, k, k1, n0, a.K, rb);
     }
+  };
+  load(k0);
+  for (int k = k0; k < k1; k += BK_SLAB) {
+    if (dw)
+      slab_store_k(As, ra);
+    else
+      slab_store_x(As, ra);
+    slab_store_k(Bs, rb);
     __syncthreads();
+    if (k + BK_SLAB < k1) load(k + BK_SLAB);
+    // lane l feeds A[l % 16][l / 16] and B[l / 16][l % 16] of a 16 x 4 x 16 step
+    // and holds C rows 4 (l / 16) .. + 3 of column l % 16
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
+    for (int ks = 0; ks < BK_SLAB / 4; ++ks) {
       const int kk = ks * 4 + (lane >> 4);
       float av[2], bv[2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        av[t] = As[kk][wm + t * 16 + (lane & 15)];
-        bv[t] = Bs[kk][wn + t * 16 + (lane & 15)];
+        av[t] = As[kk * pa + wm + t * 16 + (lane & 15)];
+        bv[t] = Bs[kk * BK_PITCH + wn + t * 16 + (lane & 15)];
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[i][j], 0, 0, 0);
     }
+    if (bias) {
+#pragma unroll
+      for (int kk = 0; kk < BK_SLAB; kk += 4) bsum += As[(kk + wave) * pa + lane];
+    }
     __syncthreads();
+  }
+  if (bias) {  // uniform over the work-group
+    red[wave][lane] = bsum;
+    __syncthreads();
+    if (wave == 0 && m0 + lane < a.N)
+      a.Pb[(long long)split * a.N + m0 + lane] = red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane];
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -380,51 +490,20 @@ __global__ void __launch_bounds__(256) k_gemm(int M, int N, int K, const float* 
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int gm = m0 + wm + i * 16 + (lane >> 4) * 4 + r, gn = n0 + wn + j * 16 + (lane & 15);
-        if (gm < M && gn < N) {
-          float* c = C + (long long)gm * ldc + gn;
-          *c = beta == 0.f ? acc[i][j][r] : beta * *c + acc[i][j][r];
+        if (gn >= a.K) continue;
+        if (dw) {
+          if (gm < a.N) a.Pw[((long long)split * a.N + gm) * a.K + gn] = acc[i][j][r];
+        } else if (gm < a.B) {
+          const long long o = (long long)gm * a.K + gn;
+          a.dZp[o] = acc[i][j][r] * gelu_prime_f(a.Zp[o]);
         }
       }
 }
 
-// column sums: out[j] = sum_r in[r][j], one thread per column (fixed order)
-// Column sums (bias gradients) in two fixed-order stages: blocks of 64
-// columns x 4 row lanes over row chunks into FP64 partials, then the chunks.
-constexpr int COLSUM_CHUNK = 256;
-__global__ void __launch_bounds__(256) k_colsum_part(const float* in, long long rows, int cols, double* part) {
-  __shared__ double red[4][64];
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int lane = threadIdx.x >> 6;
-  const long long r0 = (long long)blockIdx.y * COLSUM_CHUNK;
-  const long long r1 = min(rows, r0 + COLSUM_CHUNK);
-  double s = 0.0;
-  if (c < cols)
-    for (long long r = r0 + lane; r < r1; r += 4) s += in[r * cols + c];
-  red[lane][threadIdx.x & 63] = s;
-  __syncthreads();
-  if (lane == 0 && c < cols)
-    part[(long long)blockIdx.y * cols + c] = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] +
-                                             red[3][threadIdx.x];
-}
-
-__global__ void __launch_bounds__(256) k_colsum_final(const double* part, int chunks, int cols, float* out) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= cols) return;
-  double s = 0.0;
-  for (int k = 0; k < chunks; ++k) s += part[(long long)k * cols + c];
-  out[c] = (float)s;
-}
-
-// dz = da * gelu'(z)
-__global__ void k_gelu_back(const float* da, const float* z, float* dz, long long count) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) dz[i] = da[i] * gelu_prime_f(z[i]);
-}
-
-// weighted MSE on normalized outputs: dyhat = 2 w (yhat - t) / B, loss partials
-// weighted mean squared error: output weights w [16], row weights rw [B] (or null)
-__global__ void k_loss(const float* yhat, const float* t, const float* w, const float* rw, long long B, int n_out,
-                       float* dy, double* part) {
+// weighted MSE on normalized outputs: dyhat = 2 w (yhat - t) / B and loss partials;
+// output weights w [16], row weights rw [B] (or null)
+__global__ void k_loss(const float* yhat, const float* t, const float* w, const float* rw, const int* idx, long long B,
+                       int n_out, float* dy, double* part) {
   __shared__ double red[256];
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   double l = 0.0;
@@ -432,8 +511,9 @@ __global__ void k_loss(const float* yhat, const float* t, const float* w, const 
     const int j = (int)(i % MLP_OUT);
     float g = 0.f;
     if (j < n_out) {
-      const float d = yhat[i] - t[i];
-      const float wj = w[j] * (rw ? rw[i / MLP_OUT] : 1.0f);
+      const long long r = i / MLP_OUT, s = idx ? idx[r] : r;  // row of t and rw
+      const float d = yhat[i] - t[s * MLP_OUT + j];
+      const float wj = w[j] * (rw ? rw[s] : 1.0f);
       g = 2.0f * wj * d / (float)B;
       l = (double)wj * (double)d * (double)d / (double)B;
     }
@@ -448,31 +528,48 @@ __global__ void k_loss(const float* yhat, const float* t, const float* w, const 
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ void k_adam(float* w, const float* g, float* m, float* v, long long count, float lr, float b1, float b2,
-                       float c1, float c2, float eps) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-}
-
+// Layer spans of the parameter array and of the backward pass's partials.
 struct LayerSpans {
-  long long off[MLP_LAYERS];
+  long long off[MLP_LAYERS];   // weights; the biases follow
   int n[MLP_LAYERS], k[MLP_LAYERS];
+  long long pw[MLP_LAYERS], pb[MLP_LAYERS];  // offsets of the layer's weight and bias partials
+  int splits;
 };
 
-// master FP32 weights -> bf16 hi / lo copies (weight matrices in fragment
+// Gradient of parameter i: its partials over the splits in a fixed order.
+__device__ __forceinline__ float sum_splits(const LayerSpans& ls, const float* Pw, const double* Pb, long long i) {
+#pragma unroll
+  for (int L = 0; L < MLP_LAYERS; ++L) {
+    const long long r = i - ls.off[L], nk = (long long)ls.n[L] * ls.k[L];
+    if (r >= 0 && r < nk) {
+      const float* p = Pw + ls.pw[L] + r;
+      float v = 0.f;
+#pragma unroll 8
+      for (int s = 0; s < ls.splits; ++s) v += p[s * nk];
+      return v;
+    }
+    if (r >= nk && r < nk + ls.n[L]) {
+      const double* p = Pb + ls.pb[L] + (r - nk);
+      double v = 0.0;
+#pragma unroll 8
+      for (int s = 0; s < ls.splits; ++s) v += p[(long long)s * ls.n[L]];
+      return (float)v;
+    }
+  }
+  return 0.f;
+}
+
+__global__ void __launch_bounds__(256) k_sum_splits(LayerSpans ls, const float* Pw, const double* Pb, float* g,
+                                                    long long count) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i < count) g[i] = sum_splits(ls, Pw, Pb, i);
+}
+
+// master FP32 weight -> bf16 hi / lo copies (weight matrices in fragment
 // order) and the effective FP32 weights the forward pass uses (hi, or hi + lo
 // in precise mode)
-__global__ void k_split(const float* w, __bf16* hi, __bf16* lo, float* eff_bf, float* eff_pr, long long count,
-                        LayerSpans ls) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  const float v = w[i];
+__device__ __forceinline__ void split_weight(const LayerSpans& ls, float v, long long i, __bf16* hi, __bf16* lo,
+                                             float* eff_bf, float* eff_pr) {
   const __bf16 h = (__bf16)v;
   const __bf16 l = (__bf16)(v - (float)h);
   long long d = i;  // biases and padding keep their place
@@ -490,12 +587,51 @@ __global__ void k_split(const float* w, __bf16* hi, __bf16* lo, float* eff_bf, f
   eff_pr[i] = (float)h + (float)l;
 }
 
-__global__ void k_gather(const float* src, int cols, const int* idx, long long count, float* dst) {
+__global__ void k_split(const float* w, __bf16* hi, __bf16* lo, float* eff_bf, float* eff_pr, long long count,
+                        LayerSpans ls) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count * cols) return;
-  const long long r = i / cols;
-  const int c = (int)(i % cols);
-  dst[i] = src[(long long)idx[r] * cols + c];
+  if (i < count) split_weight(ls, w[i], i, hi, lo, eff_bf, eff_pr);
+}
+
+// One training step's end: gradient from the partials, Adam, the weight
+// copies, and (the last work-group) the step's loss added to the epoch's.
+struct UpdateArgs {
+  LayerSpans ls;
+  const float* Pw;
+  const double* Pb;
+  float *w, *m, *v;
+  __bf16 *hi, *lo;
+  float *eff_bf, *eff_pr;
+  long long count;
+  float lr, b1, b2, c1, c2, eps;
+  const double* lpart;  // loss partials of the step
+  int nl;
+  double* loss;
+};
+__global__ void __launch_bounds__(256) k_update(UpdateArgs a) {
+  if (blockIdx.x == gridDim.x - 1) {  // fixed-order sum of the loss partials
+    __shared__ double red[256];
+    double v = 0.0;
+    for (int i = threadIdx.x; i < a.nl; i += 256) v += a.lpart[i];
+    red[threadIdx.x] = v;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+      if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) *a.loss += red[0];
+    return;
+  }
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= a.count) return;
+  const float gi = sum_splits(a.ls, a.Pw, a.Pb, i);
+  const float mi = a.b1 * a.m[i] + (1.f - a.b1) * gi;
+  const float vi = a.b2 * a.v[i] + (1.f - a.b2) * gi * gi;
+  a.m[i] = mi;
+  a.v[i] = vi;
+  const float wi = a.w[i] - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+  a.w[i] = wi;
+  split_weight(a.ls, wi, i, a.hi, a.lo, a.eff_bf, a.eff_pr);
 }
 
 // M networks: y = mean, spread = RMS pairwise distance of the stress outputs
@@ -557,16 +693,41 @@ Mlp::Mlp(int n_in_, int n_out_, uint64_t seed) : n_in(n_in_), n_out(n_out_) {
   alloc((void**)&scal, 5 * MLP_OUT * 4 + 2 * MLP_IN * 4);
   // G and c in FP32, then G's bf16 hi and lo parts
   alloc((void**)&skip, (MLP_OUT * MLP_GATES * MLP_IN + MLP_OUT) * 4 + 2 * MLP_OUT * MLP_GATES * MLP_IN * 2);
-  // He initialization (normal, std sqrt(2 / fan_in)), seeded; biases zero
+  // He initialization (normal, std sqrt(2 / fan_in)), seeded; biases zero.
+  // Marsaglia's polar method on 64-bit draws scaled to [0, 1): the numbers of
+  // std::normal_distribution, which forms logarithms of the generator's range
+  // on every draw (two thirds of the time to set up a network).
   std::vector<float> hw(npad, 0.f);
   std::mt19937_64 gen(seed);
+  const auto uniform = [&] { return std::min((double)gen() * 0x1p-64, 1.0 - 0x1p-53); };
+  struct {
+    bool have = false;
+    double saved = 0.0;
+  } polar;
+  const auto normal = [&](double sd) {
+    if (polar.have) {
+      polar.have = false;
+      return polar.saved * sd;
+    }
+    double x, y, r2;
+    do {
+      x = 2.0 * uniform() - 1.0;
+      y = 2.0 * uniform() - 1.0;
+      r2 = x * x + y * y;
+    } while (r2 > 1.0 || r2 == 0.0);
+    const double mult = std::sqrt(-2.0 * std::log(r2) / r2);
+    polar.saved = x * mult;
+    polar.have = true;
+    return y * mult * sd;
+  };
   for (int l = 0; l < MLP_LAYERS; ++l) {
     const int K = lay_k(l), N = lay_n(l);
     const int kin = l == 0 ? n_in : K;
     const int nout = l == MLP_LAYERS - 1 ? n_out : N;
-    std::normal_distribution<double> nd(0.0, std::sqrt((l == MLP_LAYERS - 1 ? 1.0 : 2.0) / kin));
+    const double sd = std::sqrt((l == MLP_LAYERS - 1 ? 1.0 : 2.0) / kin);
+    polar.have = false;
     for (int i = 0; i < nout; ++i)
-      for (int k = 0; k < kin; ++k) hw[woff[l] + (size_t)i * K + k] = (float)nd(gen);
+      for (int k = 0; k < kin; ++k) hw[woff[l] + (size_t)i * K + k] = (float)normal(sd);
   }
   HIPCHK(hipMemcpy(w, hw.data(), npad * 4, hipMemcpyHostToDevice));
   std::vector<float> s(5 * MLP_OUT + 2 * MLP_IN, 0.f);
@@ -595,15 +756,26 @@ void Mlp::free_work() {
   work_rows = 0;
 }
 
-void Mlp::refresh(hipStream_t s) {
-  const long long n = (long long)npad;
+static LayerSpans layer_spans(const Mlp& net, int splits) {
   LayerSpans ls;
+  long long pw = 0, pb = 0;
   for (int l = 0; l < MLP_LAYERS; ++l) {
-    ls.off[l] = (long long)woff[l];
+    ls.off[l] = (long long)net.woff[l];
     ls.n[l] = lay_n(l);
     ls.k[l] = lay_k(l);
+    ls.pw[l] = pw;
+    ls.pb[l] = pb;
+    pw += (long long)splits * ls.n[l] * ls.k[l];
+    pb += (long long)splits * ls.n[l];
   }
-  hipLaunchKernelGGL(k_split, dim3((n + 255) / 256), dim3(256), 0, s, w, hi, lo, eff_bf, eff_pr, n, ls);
+  ls.splits = splits;
+  return ls;
+}
+
+void Mlp::refresh(hipStream_t s) {
+  const long long n = (long long)npad;
+  hipLaunchKernelGGL(k_split, dim3((n + 255) / 256), dim3(256), 0, s, w, hi, lo, eff_bf, eff_pr, n,
+                     layer_spans(*this, 1));
 }
 
 void Mlp::set_scaling(const float* xmean, const float* xstd, const float* ymean, const float* ystd,
@@ -826,38 +998,45 @@ void Mlp::ensure_work(long long rows) {
   }
   alloc(&yhat, rows * MLP_OUT);
   alloc(&dy, rows * MLP_OUT);
-  alloc(&da, rows * MLP_W);
-  alloc(&dz, rows * MLP_W);
-  alloc(&xb, rows * MLP_IN);
-  alloc(&tb, rows * MLP_OUT);
-  alloc(&rwb, rows);
+  alloc(&dz[0], rows * MLP_W);
+  alloc(&dz[1], rows * MLP_W);
   alloc(&lpart, (rows * MLP_OUT + 255) / 256 * 2);
   work_rows = rows;
 }
 
-void Mlp::forward(const float* x, float* y, long long n, bool precise, bool save, hipStream_t s) {
+template <int PRECISE, bool SAVE>
+static void launch_fwd(const FwdArgs& a, int nets, hipStream_t s) {
+  if (a.n * nets >= kFullRows)
+    hipLaunchKernelGGL((k_mlp_fwd<PRECISE, SAVE, 64>), dim3((unsigned)((a.n + 63) / 64), nets), dim3(FWD_WAVES * 64), 0,
+                       s, a);
+  else
+    hipLaunchKernelGGL((k_mlp_fwd<PRECISE, SAVE, 16>), dim3((unsigned)((a.n + 15) / 16), nets), dim3(FWD_WAVES * 64), 0,
+                       s, a);
+}
+
+static FwdArgs forward_args(const Mlp* const* nets, int M, const float* x, float* y, long long n) {
   FwdArgs a;
   std::memset(&a, 0, sizeof(a));
   a.x = x;
   a.n = n;
-  a.n_in = n_in;
-  a.n_out = n_out;
-  a.xmean = scal;
-  a.xinv = scal + MLP_IN;
-  a.ymean = scal + 2 * MLP_IN;
-  a.ystd = scal + 2 * MLP_IN + MLP_OUT;
-  a.skip = skip;
-  a.skip_hi = reinterpret_cast<const __bf16*>(skip + MLP_OUT * MLP_GATES * MLP_IN + MLP_OUT);
-  a.skip_lo = a.skip_hi + MLP_OUT * MLP_GATES * MLP_IN;
-  a.g0 = gate[0];
-  a.g1 = gate[1];
-  a.g2 = gate[2];
-  for (int l = 0; l < MLP_LAYERS; ++l) {
-    a.whi[l] = hi + woff[l];
-    a.wlo[l] = lo + woff[l];
-    a.bias[l] = w + boff[l];
-  }
+  a.n_in = nets[0]->n_in;
+  a.n_out = nets[0]->n_out;
   a.y = y;
+  for (int l = 0; l < MLP_LAYERS; ++l) {
+    a.woff[l] = (int)nets[0]->woff[l];
+    a.boff[l] = (int)nets[0]->boff[l];
+  }
+  for (int m = 0; m < M; ++m) {
+    const Mlp& net = *nets[m];
+    a.net[m] = NetRef{net.hi, net.lo, net.w, net.scal, net.skip, net.gate[0], net.gate[1], net.gate[2]};
+  }
+  return a;
+}
+
+void Mlp::forward(const float* x, float* y, long long n, bool precise, bool save, hipStream_t s, const int* idx) {
+  const Mlp* self = this;
+  FwdArgs a = forward_args(&self, 1, x, y, n);
+  a.idx = idx;
   if (save) {
     a.yhat = yhat;
     a.xs = xs;
@@ -865,93 +1044,29 @@ void Mlp::forward(const float* x, float* y, long long n, bool precise, bool save
       a.zs[l] = zs[l];
       a.as[l] = as[l];
     }
-  }
-  const unsigned blocks = (unsigned)((n + MROWS - 1) / MROWS);
-  if (save) {
-    if (precise)
-      hipLaunchKernelGGL((k_mlp_fwd<1, true>), dim3(blocks), dim3(FWD_WAVES * 64), 0, s, a);
-    else
-      hipLaunchKernelGGL((k_mlp_fwd<0, true>), dim3(blocks), dim3(FWD_WAVES * 64), 0, s, a);
+    precise ? launch_fwd<1, true>(a, 1, s) : launch_fwd<0, true>(a, 1, s);
   } else {
-    if (precise)
-      hipLaunchKernelGGL((k_mlp_fwd<1, false>), dim3(blocks), dim3(FWD_WAVES * 64), 0, s, a);
-    else
-      hipLaunchKernelGGL((k_mlp_fwd<0, false>), dim3(blocks), dim3(FWD_WAVES * 64), 0, s, a);
+    precise ? launch_fwd<1, false>(a, 1, s) : launch_fwd<0, false>(a, 1, s);
   }
 }
 
-// C = sum_s P[s] over the split-K partials, in a fixed order
-__global__ void __launch_bounds__(256) k_sum_splits(const float* P, int splits, int M, int N, float* C, int ldc) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (long long)M * N) return;
-  const int m = (int)(i / N), n = (int)(i % N);
-  float v = 0.f;
-  for (int k = 0; k < splits; ++k) v += P[(long long)k * M * N + i];
-  C[(long long)m * ldc + n] = v;
+// Batch rows of a split of the weight gradients: 256 each, at most 64 splits
+// (fewer than 1024 rows: one)
+static int back_splits(long long B, int& kc) {
+  const int splits = B >= 1024 ? (int)std::min<long long>(64, B / 256) : 1;
+  kc = (int)((B + splits - 1) / splits);
+  return (int)((B + kc - 1) / kc);  // every split has at least one row
 }
 
-static void colsum(Mlp& net, const float* in, long long rows, int cols, float* out, hipStream_t s) {
-  const int chunks = (int)((rows + COLSUM_CHUNK - 1) / COLSUM_CHUNK);
-  const size_t need = (size_t)chunks * cols;
-  if (need > net.csum_n) {
-    if (net.csum) HIPCHK(hipFree(net.csum));
-    net.csum = nullptr;
-    HIPCHK(hipMalloc((void**)&net.csum, need * sizeof(double)));
-    net.csum_n = need;
-  }
-  hipLaunchKernelGGL(k_colsum_part, dim3((cols + 63) / 64, chunks), dim3(256), 0, s, in, rows, cols, net.csum);
-  hipLaunchKernelGGL(k_colsum_final, dim3((cols + 255) / 256), dim3(256), 0, s, net.csum, chunks, cols, out);
-}
-
-static void gemm(Mlp& net, bool ta, bool tb, int M, int N, int K, const float* A, int lda, const float* B, int ldb,
-                 float* C, int ldc, hipStream_t s) {
-  dim3 grid((N + 63) / 64, (M + 63) / 64);
-  // weight gradients: a small M x N output over a long K (the batch) gets
-  // few work-groups; split K over more of them and sum the partials
-  if (ta && !tb && grid.x * grid.y < 128 && K >= 1024) {
-    const int splits = std::min(64, K / 256);
-    const int kc = (K + splits - 1) / splits;
-    const size_t need = (size_t)splits * M * N;
-    if (need > net.splitk_n) {
-      if (net.splitk) HIPCHK(hipFree(net.splitk));
-      net.splitk = nullptr;
-      HIPCHK(hipMalloc((void**)&net.splitk, need * sizeof(float)));
-      net.splitk_n = need;
-    }
-    const int nsp = (K + kc - 1) / kc;  // every split has at least one row
-    hipLaunchKernelGGL((k_gemm<true, false>), dim3(grid.x, grid.y, nsp), dim3(256), 0, s, M, N, K, A, lda, B, ldb,
-                       net.splitk, N, 0.f, kc);
-    const long long cnt = (long long)M * N;
-    hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, net.splitk, nsp, M, N,
-                       C, ldc);
-    return;
-  }
-  if (!ta && !tb) hipLaunchKernelGGL((k_gemm<false, false>), grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, C, ldc, 0.f);
-  if (ta && !tb) hipLaunchKernelGGL((k_gemm<true, false>), grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, C, ldc, 0.f);
-  if (!ta && tb) hipLaunchKernelGGL((k_gemm<false, true>), grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, C, ldc, 0.f);
-  if (ta && tb) hipLaunchKernelGGL((k_gemm<true, true>), grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, C, ldc, 0.f);
-}
-
-// loss and gradient of the rows (x, t normalized targets already in xb / tb
-// layout: x raw [B][n_in], t normalized [B][16])
-// Fixed-order sum of the loss partials of one step into a device accumulator
-// (training reads the losses back once, at the end, not after every step).
-__global__ void __launch_bounds__(256) k_loss_accumulate(const double* part, int n, double* acc) {
-  __shared__ double red[256];
-  double v = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) v += part[i];
-  red[threadIdx.x] = v;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *acc += red[0];
-}
-
+// loss and gradient of the rows (x raw [B][n_in], t normalized [B][16], or
+// their rows idx)
 double Mlp::loss_grad(const float* x, const float* tnorm, long long B, bool precise, hipStream_t s,
                       const float* rw) {
-  const int lb = grad_only(x, tnorm, B, precise, s, rw);
+  const int lb = grad_partials(x, tnorm, B, precise, s, rw, nullptr);
+  const long long np = (long long)npad;
+  int kc;
+  hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s,
+                     layer_spans(*this, back_splits(B, kc)), splitk, csum, g, np);
   std::vector<double> lp(lb);
   HIPCHK(hipMemcpyAsync(lp.data(), lpart, lb * sizeof(double), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
@@ -960,32 +1075,55 @@ double Mlp::loss_grad(const float* x, const float* tnorm, long long B, bool prec
   return L;
 }
 
-int Mlp::grad_only(const float* x, const float* tnorm, long long B, bool precise, hipStream_t s, const float* rw) {
+int Mlp::grad_partials(const float* x, const float* tnorm, long long B, bool precise, hipStream_t s, const float* rw,
+                       const int* idx) {
   ensure_work(B);
-  forward(x, nullptr, B, precise, true, s);
+  int kc;
+  const int splits = back_splits(B, kc);
+  const LayerSpans ls = layer_spans(*this, splits);
+  const size_t needw = (size_t)ls.pw[MLP_LAYERS - 1] + (size_t)splits * MLP_OUT * MLP_W;
+  const size_t needb = (size_t)ls.pb[MLP_LAYERS - 1] + (size_t)splits * MLP_OUT;
+  if (needw > splitk_n) {
+    if (splitk) HIPCHK(hipFree(splitk));
+    splitk = nullptr;
+    splitk_n = 0;
+    HIPCHK(hipMalloc((void**)&splitk, needw * sizeof(float)));
+    splitk_n = needw;
+  }
+  if (needb > csum_n) {
+    if (csum) HIPCHK(hipFree(csum));
+    csum = nullptr;
+    csum_n = 0;
+    HIPCHK(hipMalloc((void**)&csum, needb * sizeof(double)));
+    csum_n = needb;
+  }
+  forward(x, nullptr, B, precise, true, s, idx);
   const long long cnt = B * MLP_OUT;
   const int lb = (int)((cnt + 255) / 256);
-  hipLaunchKernelGGL(k_loss, dim3(lb), dim3(256), 0, s, yhat, tnorm, scal + 2 * MLP_IN + 2 * MLP_OUT, rw, B, n_out, dy,
-                     reinterpret_cast<double*>(lpart));
+  hipLaunchKernelGGL(k_loss, dim3(lb), dim3(256), 0, s, yhat, tnorm, scal + 2 * MLP_IN + 2 * MLP_OUT, rw, idx, B,
+                     n_out, dy, reinterpret_cast<double*>(lpart));
   const float* eff = precise ? eff_pr : eff_bf;
   const float* dcur = dy;
-  int ncur = MLP_OUT;
   for (int l = MLP_LAYERS - 1; l >= 0; --l) {
-    const int K = lay_k(l), N = lay_n(l);
-    const float* ain = l == 0 ? xs : as[l - 1];
-    // dW[N][K] = dZ^T (B x N) . A (B x K)
-    gemm(*this, true, false, N, K, (int)B, dcur, ncur, ain, K, g + woff[l], K, s);
-    colsum(*this, dcur, B, N, g + boff[l], s);
-    if (l > 0) {
-      // dA (B x K) = dZ (B x N) . W (N x K), then dZ_prev = dA * gelu'(Z_prev)
-      gemm(*this, false, false, (int)B, K, N, dcur, ncur, eff + woff[l], K, da, K, s);
-      const long long c = B * K;
-      hipLaunchKernelGGL(k_gelu_back, dim3((c + 255) / 256), dim3(256), 0, s, da, zs[l - 1], dz, c);
-      // dz is read by the next layer's dW / dA products before its own
-      // gelu' step overwrites it (stream order), so one pair of buffers suffices
-      dcur = dz;
-      ncur = K;
-    }
+    BackArgs a;
+    a.B = (int)B;
+    a.N = lay_n(l);
+    a.K = lay_k(l);
+    a.dZ = dcur;
+    a.A = l == 0 ? xs : as[l - 1];
+    a.W = eff + woff[l];
+    a.Zp = l > 0 ? zs[l - 1] : nullptr;
+    a.dZp = l > 0 ? dz[l & 1] : nullptr;  // not the buffer that this layer reads
+    a.Pw = splitk + ls.pw[l];
+    a.Pb = csum + ls.pb[l];
+    a.kc = kc;
+    a.splits = splits;
+    a.tn = (a.N + BK_TILE - 1) / BK_TILE;
+    a.tk = (a.K + BK_TILE - 1) / BK_TILE;
+    a.tb = (int)((B + BK_TILE - 1) / BK_TILE);
+    const unsigned groups = (unsigned)(a.tn * a.tk * splits + (l > 0 ? a.tb * a.tk : 0));
+    hipLaunchKernelGGL(k_layer_back, dim3(groups), dim3(256), 0, s, a);
+    dcur = a.dZp;
   }
   return lb;
 }
@@ -1103,24 +1241,36 @@ void Mlp::train(const float* X, const float* T, long long n, int epochs, int bat
     HIPCHK(hipMemcpy(didx, perm.data(), n * 4, hipMemcpyHostToDevice));
     for (long long sidx = 0; sidx < steps_per_epoch; ++sidx) {
       const int* bi = didx + sidx * batch;
-      const long long cx = (long long)batch * n_in, ct = (long long)batch * MLP_OUT;
-      hipLaunchKernelGGL(k_gather, dim3((cx + 255) / 256), dim3(256), 0, s, dX, n_in, bi, (long long)batch, xb);
-      hipLaunchKernelGGL(k_gather, dim3((ct + 255) / 256), dim3(256), 0, s, dT, MLP_OUT, bi, (long long)batch, tb);
-      if (dW)
-        hipLaunchKernelGGL(k_gather, dim3((batch + 255) / 256), dim3(256), 0, s, dW, 1, bi, (long long)batch, rwb);
-      const int lb = grad_only(xb, tb, batch, false, s, dW ? rwb : nullptr);
-      hipLaunchKernelGGL(k_loss_accumulate, dim3(1), dim3(256), 0, s, reinterpret_cast<const double*>(lpart), lb,
-                         dloss + e);
+      const int lb = grad_partials(dX, dT, batch, false, s, dW, bi);
       ++step;
       // cosine decay to 1 % with a short warm-up
       const double prog = (double)step / (double)total;
       double lr = lr0 * (0.01 + 0.99 * 0.5 * (1.0 + std::cos(3.14159265358979 * prog)));
       if (step < 200) lr *= (double)step / 200.0;
       const float c1 = 1.f - std::pow(b1, (float)step), c2 = 1.f - std::pow(b2, (float)step);
-      const long long np = (long long)npad;
-      hipLaunchKernelGGL(k_adam, dim3((np + 255) / 256), dim3(256), 0, s, w, g, m, v, np, (float)lr, b1, b2, c1, c2,
-                         1e-8f);
-      refresh(s);
+      UpdateArgs u;
+      int kc;
+      u.ls = layer_spans(*this, back_splits(batch, kc));
+      u.Pw = splitk;
+      u.Pb = csum;
+      u.w = w;
+      u.m = m;
+      u.v = v;
+      u.hi = hi;
+      u.lo = lo;
+      u.eff_bf = eff_bf;
+      u.eff_pr = eff_pr;
+      u.count = (long long)npad;
+      u.lr = (float)lr;
+      u.b1 = b1;
+      u.b2 = b2;
+      u.c1 = c1;
+      u.c2 = c2;
+      u.eps = 1e-8f;
+      u.lpart = reinterpret_cast<const double*>(lpart);
+      u.nl = lb;
+      u.loss = dloss + e;
+      hipLaunchKernelGGL(k_update, dim3((unsigned)((u.count + 255) / 256 + 1)), dim3(256), 0, s, u);
     }
   }
   HIPCHK(hipStreamSynchronize(s));
@@ -1140,8 +1290,9 @@ void Mlp::reset_optimizer() {
 void ensemble_accept(const Mlp* const* nets, int M, const float* x, float* y, float* ys, float* spread,
                         uint8_t* accept, long long n, float thr, float floor_scale, hipStream_t s) {
   const int n_out = nets[0]->n_out;
-  for (int m = 0; m < M; ++m)
-    const_cast<Mlp*>(nets[m])->forward(x, ys + (size_t)m * n * n_out, n, false, false, s);
+  // every network in one launch: a few rows are bound by the latency of a
+  // work-group's layers
+  launch_fwd<0, false>(forward_args(nets, M, x, ys, n), M, s);
   hipLaunchKernelGGL(k_accept_n, dim3((n + 255) / 256), dim3(256), 0, s, ys, M, n, n_out, y, spread, accept, thr,
                      floor_scale);
 }

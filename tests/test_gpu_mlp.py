@@ -173,3 +173,35 @@ def test_row_weights():
     for m in (s1, s2):
         m.set_params(np.zeros(m.param_count, dtype=np.float32))
     assert np.allclose(s1.forward(x[:256]), s2.forward(x[:256]), rtol=1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("rows", [1, 4, 17, 63, 65, 1023, 1025, 2500])
+def test_gradients_at_batch_edges(rows):
+    """Batches around the backward pass's 64-row tiles and its splits of the
+    batch. Bound of the fixed batch above: precise mode carries about 16
+    significant bits."""
+    rng = np.random.default_rng(rows)
+    net = hom.MLP(N_IN, N_OUT, seed=5)
+    x = rng.normal(size=(rows, N_IN)).astype(np.float32)
+    y = rng.normal(size=(rows, N_OUT)).astype(np.float32)
+    lw = rng.uniform(0.5, 2.0, size=N_OUT)
+    net.set_scaling(np.zeros(N_IN), np.ones(N_IN), np.zeros(N_OUT), np.ones(N_OUT), lw)
+    L, g = net.loss_grad(x, y, precise=True)
+    grads, Lref = omlp.gradients(f64(net.layers()), x.astype(np.float64), y.astype(np.float64), lw)
+    assert L == pytest.approx(Lref, rel=1e-5)
+    for i, ((gW, gb), (rW, rb)) in enumerate(zip(net.layers(g), grads)):
+        assert np.linalg.norm(gW - rW) < 5e-5 * np.linalg.norm(rW), i
+        assert np.linalg.norm(gb - rb) < 5e-5 * np.linalg.norm(rb), i
+
+
+@pytest.mark.parametrize("precise", [False, True])
+def test_forward_rows_alike_on_both_sides_of_the_tile_rule(net_and_data, precise):
+    """Launches below 64 * 256 rows take 16 rows a work-group, larger ones 64:
+    the same bits for a row in either."""
+    net, _, _, (xm, xs, *_rest) = net_and_data
+    n = 64 * 256
+    x = (xm + xs * np.random.default_rng(9).normal(size=(n + 5, N_IN))).astype(np.float32)
+    full = net.forward(x, precise=precise)
+    np.testing.assert_array_equal(net.forward(x[:n], precise=precise), full[:n])
+    np.testing.assert_array_equal(net.forward(x[:n - 1], precise=precise), full[:n - 1])
+    np.testing.assert_array_equal(net.forward(x[n - 30:], precise=precise), full[n - 30:])
