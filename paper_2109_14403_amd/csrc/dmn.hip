@@ -18,6 +18,7 @@
 #include <cstring>
 #include <random>
 #include <string>
+#include <type_traits>
 #include <unordered_map>
 #include <utility>
 
@@ -733,10 +734,19 @@ void Dmn::train(long long n, const double* C1, const double* C2, const double* C
 // node 2^S + t (S = min(K, 6)), i.e. 2^R leaves whose data stay in its
 // registers. The S levels above are combined across lanes with shuffles: the
 // depth-d node j (heap 2^d + j) belongs to lane j 2^(S-d), its right child to
-// lane j 2^(S-d) + 2^(S-d-1). Per-node data in global memory (the jumps, the
-// elimination factors G, d0 and the last Newton step) are touched only by the
-// owning lane, so a point needs neither LDS nor a barrier and many points
-// share a CU.
+// lane j 2^(S-d) + 2^(S-d-1). Per-node data (the jumps, the elimination factors
+// G, d0 and the last Newton step) are touched only by the owning lane: those of
+// the 2^S - 1 nodes above depth S are in LDS during the call, those of the
+// lane's own subtree in memory, 64 lanes to a line.
+//
+// A wave's time is a chain of latencies (four rounds of one wave per SIMD at
+// 4096 points of depth 8; vector instructions fill half of it). With the nodes'
+// fields of a lane side by side in memory (64 lines an access) and every level
+// reading its node when it got there, a call of 4096 points of depth 8 took
+// 1.55 ms and one of 300 points 0.34 ms; now, with the upper nodes in LDS, the
+// lane's own factors loaded ahead of the shuffle levels and the leaf states held
+// in registers, 1.14 and 0.29 ms. Two waves per SIMD at half the registers,
+// without the LDS: 1.67 ms, bound by 8 GB of traffic.
 //
 // One bottom-up sweep forms the residual (weighted stress sums and the
 // traction mismatch N^T (c2 s1 - c1 s2) of every laminate) and, in the same
@@ -752,18 +762,34 @@ namespace {
 
 constexpr int ON_MAX_K = 8;
 constexpr int ON_LANES = 64;  // one wave per point
+constexpr int ON_WAVES = 1;   // of a SIMD, with all of its registers
 constexpr int ON_SHUF = 6;    // levels combined across the lanes (2^6 = 64)
 // per point: sigma 6, coupling, dissipation, dsde 36, dsdt 6, dDde 6, dDdt,
 // residual, iterations, status
 constexpr int ON_OUT = 64;
 constexpr int O_DSDT = 44, O_DDDE = 50, O_DDDT = 56, O_RES = 57, O_IT = 58, O_ST = 59;
 constexpr int ON_SCR = 24;  // per internal node: G (18), d0 (3), last Newton step (3)
-constexpr int ON_NODE = 8;  // per heap node: unit direction (3), c1, subtree weight
+constexpr int ON_NODE = 5;  // per heap node: unit direction (3), c1, subtree weight
 constexpr int ON_LP = 16;   // per leaf: d sigma / d theta (6), d D / d eps (6), d D / d theta
+
+// A node's or leaf's place in the arrays over them, laid out [group][field][stride]:
+// the 64 lanes of a wave, each at the same node of its own subtree, touch
+// consecutive doubles, and the fields of one group lie at constant distances. Nodes
+// above depth S are group 0 in heap order; node k of the level r below depth S is
+// group 2^r + k, leaf k of a lane's subtree group k, the index the lane.
+struct Slot {
+  int grp, idx;
+};
+// A node above depth S: its scratch, jump and table entry are in LDS while the
+// kernel runs, [field][ON_LANES].
+struct Top {
+  int idx;
+};
+constexpr int TOP_JUMP = ON_SCR, TOP_TABLE = ON_SCR + 3, TOP_FIELDS = TOP_TABLE + ON_NODE;
 
 struct OnArgs {
   int K, nleaf, S;
-  const double* node;     // [2 nleaf][ON_NODE], heap index (leaves: weight in slot 4)
+  const double* node;     // [group][ON_NODE][stride] of the network, then the leaf weights
   const ProbInc* inc;     // [distinct (theta, dt) of the call]
   const ProbInc* inc_pm;  // [distinct][2]: theta + h_theta, theta - h_theta (all four tangents)
   const int* inc_ix;      // [point] index into inc
@@ -773,17 +799,17 @@ struct OnArgs {
   double* state;          // [point][nstate][nleaf / 2]
   int nstate;
   double* hist;           // [point][HIST_SLOTS][nleaf / 2]
-  double* epsn;           // [point][nleaf][6]
-  double* a;              // [point][nleaf][3] jumps (heap index)
-  double* scr;            // [point][nleaf][ON_SCR]
-  double* lp;             // [point][nleaf][ON_LP] leaf partials (what = 1)
+  double* epsn;           // [point][group][6][stride]
+  double* a;              // [point][group][3][stride] jumps
+  double* scr;            // [point][group][ON_SCR][stride]
+  double* lp;             // [point][group][ON_LP][stride] leaf partials (what = 1)
   // predictor (pred = 1): jump change of the last committed increment, the
   // jumps at the start of this call and whether the point's last call
   // committed; the last committed macro strain and its change (kept with the
   // predictor off too)
   int pred;
-  double* dah;            // [point][nleaf][3]
-  double* a0;             // [point][nleaf][3]
+  double* dah;            // [point][group][3][stride]
+  double* a0;             // [point][group][3][stride]
   double* Ep;             // [point][12]: E of the last commit (6), its change (6)
   int* committed;         // [point]
   const double* E;        // [point][6] Mandel
@@ -792,18 +818,62 @@ struct OnArgs {
   int maxit, maxbt;
 };
 
-// node table of a network: unit directions, c1 and subtree weights (heap index)
-__global__ void k_dmn_node_table(const double* p, int nleaf, double* node) {
+// The arguments with the sizes known where there are register levels (then
+// K = ON_SHUF + R).
+template <int R_>
+struct OnView : OnArgs {
+  static constexpr int R = R_;
+  double* top;  // LDS, [TOP_FIELDS][ON_LANES]
+  __device__ int levels() const { return R > 0 ? ON_SHUF : S; }
+  __device__ int leaves() const { return R > 0 ? ON_LANES << R : nleaf; }
+  __device__ int stride() const { return R > 0 ? ON_LANES : nleaf; }
+  // An offset worked out where it is used: kept over the sweeps, the addresses
+  // of every node's fields fill the registers.
+  static __device__ unsigned here(unsigned off) {
+    asm volatile("" : "+v"(off));
+    return off;
+  }
+  // first field of a slot of point pt; the next lie stride() apart
+  __device__ double* at(double* base, int fields, int pt, Slot s) const {
+    return base + (long long)pt * leaves() * fields + here(s.grp * fields * stride() + s.idx);
+  }
+  __device__ const double* table(Slot s) const { return node + here(s.grp * ON_NODE * stride() + s.idx); }
+  __device__ double leaf_weight(Slot l) const { return node[(unsigned)(ON_NODE * leaves() + l.grp * stride() + l.idx)]; }
+  // scratch, jump and table entry of a node, and the distance of their fields
+  __device__ double* scratch(int pt, Slot s) const { return at(scr, ON_SCR, pt, s); }
+  __device__ double* scratch(int, Top t) const { return top + t.idx; }
+  __device__ double* jump(int pt, Slot s) const { return at(a, 3, pt, s); }
+  __device__ double* jump(int, Top t) const { return top + TOP_JUMP * ON_LANES + t.idx; }
+  __device__ const double* table(Top t) const { return top + TOP_TABLE * ON_LANES + t.idx; }
+  __device__ int stride(Slot) const { return stride(); }
+  __device__ static constexpr int stride(Top) { return ON_LANES; }
+  // the same node in the arrays
+  static __device__ Slot slot(Slot s) { return s; }
+  static __device__ Slot slot(Top t) { return Slot{0, t.idx}; }
+  // index of a leaf among those of its phase
+  __device__ unsigned phase_index(Slot l) const { return here(R > 0 ? (l.grp >> 1) * ON_LANES + l.idx : l.idx >> 1); }
+};
+
+// node table of a network: unit directions, c1 and subtree weights
+__global__ void k_dmn_node_table(const double* p, int nleaf, int S, double* node) {
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
   const double* v = p + 3 * (nleaf - 1);
-  for (int l = 0; l < nleaf; ++l) node[ON_NODE * (nleaf + l) + 4] = fmax(v[l], 0.0);
+  const int stride = nleaf < ON_LANES ? nleaf : ON_LANES;
+  const auto weight = [&](int h) {  // place of a heap node's weight
+    const int d = 31 - __builtin_clz(h), r = d - S, j = h - (1 << d);
+    const int in = r < 0 ? 0 : j & ((1 << r) - 1), lane = r < 0 ? h : j >> r;
+    if (h >= nleaf) return ON_NODE * nleaf + in * stride + lane;
+    return ((r < 0 ? 0 : (1 << r) + in) * ON_NODE + 4) * stride + lane;
+  };
+  for (int l = 0; l < nleaf; ++l) node[weight(nleaf + l)] = fmax(v[l], 0.0);
   for (int h = nleaf - 1; h >= 1; --h) {
-    double* nh = node + ON_NODE * h;
-    const double wl = node[ON_NODE * (2 * h) + 4], wr = node[ON_NODE * (2 * h + 1) + 4], sw = wl + wr;
-    double len;
+    const double wl = node[weight(2 * h)], wr = node[weight(2 * h + 1)], sw = wl + wr;
+    double nh[3], len;
     unit(p + 3 * param_of(h, nleaf), nh, len);
-    nh[3] = sw > 0.0 ? wl / sw : 0.5;
-    nh[4] = sw;
+    double* f = node + weight(h);
+    for (int k = 0; k < 3; ++k) f[(k - 4) * stride] = nh[k];
+    f[-stride] = sw > 0.0 ? wl / sw : 0.5;
+    f[0] = sw;
   }
 }
 
@@ -857,23 +927,17 @@ __device__ __forceinline__ void nt_apply(const double* n, const double* v, doubl
   r[1] = n[1] * v[1] + SQ2H * (n[2] * v[3] + n[0] * v[5]);
   r[2] = n[2] * v[2] + SQ2H * (n[1] * v[3] + n[0] * v[4]);
 }
-__device__ __forceinline__ double* node_scr(const OnArgs& g, int pt, int h) {
-  return g.scr + ((long long)pt * g.nleaf + h) * ON_SCR;
-}
-__device__ __forceinline__ double* node_jump(const OnArgs& g, int pt, int h) {
-  return g.a + ((long long)pt * g.nleaf + h) * 3;
-}
-
 // Laminate h from its children A (phase 1 side) and B: residual contribution
 // (PLAIN: from the plain sums), elimination factors into the node's scratch,
 // condensed tangent and stresses into P. P may be A itself: every entry of P
 // is written after the last read of the same entry of A.
-template <bool PLAIN, class CA, class CB>
-__device__ __forceinline__ void combine(const OnArgs& g, int pt, int h, const CA& A, const CB& B, NodeV& P,
+template <bool PLAIN, class G, class H, class CA, class CB>
+__device__ __forceinline__ void combine(const G& g, int pt, H h, const CA& A, const CB& B, NodeV& P,
                                         double& gg) {
-  const double* nt = g.node + ON_NODE * h;
-  const double n[3] = {nt[0], nt[1], nt[2]};
-  const double c1 = nt[3], c2 = 1.0 - c1, wsub = nt[4];
+  const int st = g.stride(h);
+  const double* nt = g.table(h);
+  const double n[3] = {nt[0], nt[st], nt[2 * st]};
+  const double c1 = nt[3 * st], c2 = 1.0 - c1, wsub = nt[4 * st];
   const double s0 = SQ2H * n[0], s1 = SQ2H * n[1], s2 = SQ2H * n[2];
   // X = (c2 K1 - c1 K2) N and M = N^T (c2^2 K1 + c1^2 K2) N, column by column
   double X[6][3], M[3][3];
@@ -922,12 +986,12 @@ __device__ __forceinline__ void combine(const OnArgs& g, int pt, int h, const CA
   // a subtree without weight on one side has no say in its jump: it stays
   double Mi[3][3];
   const bool ok = (c1 * c2 * wsub > 0.0) && inv3(M, Mi);
-  double* sc = node_scr(g, pt, h);
+  double* sc = g.scratch(pt, h);
   double d0[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     d0[k] = ok ? -(Mi[k][0] * r[0] + Mi[k][1] * r[1] + Mi[k][2] * r[2]) : 0.0;
-    sc[18 + k] = d0[k];
+    sc[(18 + k) * st] = d0[k];
   }
 #pragma unroll
   for (int i = 0; i < 6; ++i) P.sp[i] = p1[i] + p2[i] + X[i][0] * d0[0] + X[i][1] * d0[1] + X[i][2] * d0[2];
@@ -938,7 +1002,7 @@ __device__ __forceinline__ void combine(const OnArgs& g, int pt, int h, const CA
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       gq[k] = ok ? -(Mi[k][0] * X[q][0] + Mi[k][1] * X[q][1] + Mi[k][2] * X[q][2]) : 0.0;
-      sc[6 * k + q] = gq[k];
+      sc[(6 * k + q) * st] = gq[k];
     }
 #pragma unroll
     for (int i = 0; i <= q; ++i)
@@ -948,12 +1012,14 @@ __device__ __forceinline__ void combine(const OnArgs& g, int pt, int h, const CA
 }
 
 // children strains of laminate h: eps1 = eps + c2 N a, eps2 = eps - c1 N a
-__device__ __forceinline__ void split(const OnArgs& g, int h, const double* jump, const double* e, double* el,
-                                      double* er) {
-  const double* nt = g.node + ON_NODE * h;
-  const double c1 = nt[3], c2 = 1.0 - c1;
+template <class G, class H>
+__device__ __forceinline__ void split(const G& g, H h, const double* jump, const double* e, double* el, double* er) {
+  const int st = g.stride(h);
+  const double* nt = g.table(h);
+  const double n[3] = {nt[0], nt[st], nt[2 * st]};
+  const double c1 = nt[3 * st], c2 = 1.0 - c1;
   double jn[6];
-  n_apply(nt, jump, jn);
+  n_apply(n, jump, jn);
 #pragma unroll
   for (int c = 0; c < 6; ++c) {
     el[c] = e[c] + c2 * jn[c];
@@ -961,76 +1027,124 @@ __device__ __forceinline__ void split(const OnArgs& g, int h, const double* jump
   }
 }
 
+// ... at the node's current jump
+template <class G, class H>
+__device__ __forceinline__ void split_jump(const G& g, int pt, H h, const double* e, double* el, double* er) {
+  const int st = g.stride(h);
+  const double* ah = g.jump(pt, h);
+  const double jump[3] = {ah[0], ah[st], ah[2 * st]};
+  split(g, h, jump, e, el, er);
+}
+
 // Newton step of node h from the strain change of the node: da = d0 + G deps
 // (kept in the scratch; added to the jump if `update`), and the children's
 // strain changes
-__device__ __forceinline__ void node_step(const OnArgs& g, int pt, int h, const double* de, bool update, double* dl,
-                                          double* dr) {
-  double* sc = node_scr(g, pt, h);
+struct StepData {
+  double G[18], d0[3];
+};
+template <class G, class H>
+__device__ __forceinline__ void load_step(const G& g, int pt, H h, StepData& d) {
+  const double* sc = g.scratch(pt, h);
+  const int st = g.stride(h);
+#pragma unroll
+  for (int k = 0; k < 18; ++k) d.G[k] = sc[k * st];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) d.d0[k] = sc[(18 + k) * st];
+}
+template <class G, class H>
+__device__ __forceinline__ void node_step(const G& g, int pt, H h, const StepData& d, const double* de, bool update,
+                                          double* dl, double* dr) {
+  double* sc = g.scratch(pt, h);
+  const int st = g.stride(h);
   double da[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    double x = sc[18 + k];
+    double x = d.d0[k];
 #pragma unroll
-    for (int i = 0; i < 6; ++i) x += sc[6 * k + i] * de[i];
+    for (int i = 0; i < 6; ++i) x += d.G[6 * k + i] * de[i];
     da[k] = x;
-    sc[21 + k] = x;
+    sc[(21 + k) * st] = x;
   }
   if (update) {
-    double* ah = node_jump(g, pt, h);
+    double* ah = g.jump(pt, h);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) ah[k] += da[k];
+    for (int k = 0; k < 3; ++k) ah[k * st] += da[k];
   }
   split(g, h, da, de, dl, dr);
 }
 
-// the register levels of a lane: the subtree of LV levels below node h
-template <int LV>
+// phase of a leaf, known where it is reached: 0 at even leaves, 1 at odd ones
+template <int P>
+using PhaseOf = std::integral_constant<int, P>;
+
+// the register levels of a lane: the subtree of LV levels below its node n of
+// the level R - LV. The halves of a subtree run through the same code, one
+// after the other: unrolled, four copies of the leaf law and their live values
+// took 560 registers a lane.
+template <int LV, class G>
 struct RegTree {
-  // strains from the jumps, leaves by leaf(l, eps, LeafV&), combination upwards
+  static constexpr int LEVEL = G::R - LV;
+  using Half = RegTree<LV - 1, G>;
+  static __device__ __forceinline__ Slot node(int n, int lane) { return Slot{(1 << LEVEL) + n, lane}; }
+  // strains from the jumps, leaves by leaf(phase, slot, eps, LeafV&), combination upwards
   template <bool PLAIN, class LeafFn>
-  static __device__ __forceinline__ void up(const OnArgs& g, int pt, int h, const double* e, NodeV& out, double& gg,
-                                            LeafFn& leaf) {
+  static __device__ __forceinline__ void up(const G& g, int pt, int n, int lane, const double* e, NodeV& out,
+                                            double& gg, LeafFn& leaf) {
     double el[6], er[6];
-    split(g, h, node_jump(g, pt, h), e, el, er);
+    split_jump(g, pt, node(n, lane), e, el, er);
     if constexpr (LV == 1) {
       LeafV A, B;
-      leaf(2 * h - g.nleaf, el, A);
-      leaf(2 * h + 1 - g.nleaf, er, B);
-      combine<PLAIN>(g, pt, h, A, B, out, gg);
+      leaf(PhaseOf<0>{}, Slot{2 * n, lane}, el, A);
+      leaf(PhaseOf<1>{}, Slot{2 * n + 1, lane}, er, B);
+      combine<PLAIN>(g, pt, node(n, lane), A, B, out, gg);
     } else {
       NodeV B;
-      B.K = out.K + 21 * ON_LANES;  // the next slot
-      RegTree<LV - 1>::template up<PLAIN>(g, pt, 2 * h, el, out, gg, leaf);
-      RegTree<LV - 1>::template up<PLAIN>(g, pt, 2 * h + 1, er, B, gg, leaf);
-      combine<PLAIN>(g, pt, h, out, B, out, gg);
+#pragma unroll 1
+      for (int k = 0; k < 2; ++k) {
+        if (k == 1) {
+#pragma unroll
+          for (int c = 0; c < 6; ++c) {
+            el[c] = er[c];
+            out.s[c] = B.s[c];
+            out.sp[c] = B.sp[c];
+          }
+        }
+        B.K = out.K + k * 21 * ON_LANES;  // the second half's tangent in the next slot
+        Half::template up<PLAIN>(g, pt, 2 * n + k, lane, el, B, gg, leaf);
+      }
+      combine<PLAIN>(g, pt, node(n, lane), out, B, out, gg);
     }
   }
-  // leaf strains from the jumps: fn(l, eps)
+  // leaf strains from the jumps: fn(phase, slot, eps)
   template <class Fn>
-  static __device__ __forceinline__ void down(const OnArgs& g, int pt, int h, const double* e, Fn& fn) {
+  static __device__ __forceinline__ void down(const G& g, int pt, int n, int lane, const double* e, Fn& fn) {
     double el[6], er[6];
-    split(g, h, node_jump(g, pt, h), e, el, er);
+    split_jump(g, pt, node(n, lane), e, el, er);
     if constexpr (LV == 1) {
-      fn(2 * h - g.nleaf, el);
-      fn(2 * h + 1 - g.nleaf, er);
+      fn(PhaseOf<0>{}, Slot{2 * n, lane}, el);
+      fn(PhaseOf<1>{}, Slot{2 * n + 1, lane}, er);
     } else {
-      RegTree<LV - 1>::down(g, pt, 2 * h, el, fn);
-      RegTree<LV - 1>::down(g, pt, 2 * h + 1, er, fn);
+#pragma unroll 1
+      for (int k = 0; k < 2; ++k) {
+        if (k == 1)
+#pragma unroll
+          for (int c = 0; c < 6; ++c) el[c] = er[c];
+        Half::down(g, pt, 2 * n + k, lane, el, fn);
+      }
     }
   }
-  // Newton steps from the node's strain change; leaf strain changes: fn(l, deps)
+  // Newton steps from the node's strain change; leaf strain changes: fn(slot, deps)
   template <class Fn>
-  static __device__ __forceinline__ void expand(const OnArgs& g, int pt, int h, const double* de, bool update,
-                                                Fn& fn) {
+  static __device__ __forceinline__ void expand(const G& g, int pt, int n, int lane, const StepData* d,
+                                                const double* de, bool update, Fn& fn) {
     double dl[6], dr[6];
-    node_step(g, pt, h, de, update, dl, dr);
+    node_step(g, pt, node(n, lane), d[(1 << LEVEL) + n - 1], de, update, dl, dr);
     if constexpr (LV == 1) {
-      fn(2 * h - g.nleaf, dl);
-      fn(2 * h + 1 - g.nleaf, dr);
+      fn(Slot{2 * n, lane}, dl);
+      fn(Slot{2 * n + 1, lane}, dr);
     } else {
-      RegTree<LV - 1>::expand(g, pt, 2 * h, dl, update, fn);
-      RegTree<LV - 1>::expand(g, pt, 2 * h + 1, dr, update, fn);
+      Half::expand(g, pt, 2 * n, lane, d, dl, update, fn);
+      Half::expand(g, pt, 2 * n + 1, lane, d, dr, update, fn);
     }
   }
 };
@@ -1047,14 +1161,15 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // root strain (E, or 0 for a change) to the lane's depth-S node: shuffle levels,
 // each owner splits its node with `jump(h, jn)`
-template <class JumpFn>
-__device__ __forceinline__ void shuffle_down(const OnArgs& g, int lane, double* e, JumpFn& jump) {
-  const bool act = lane < (1 << g.S);
-  for (int d = 0; d < g.S; ++d) {
-    const int sh = g.S - d, half = 1 << (sh - 1);
+template <class G, class JumpFn>
+__device__ __forceinline__ void shuffle_down(const G& g, int lane, double* e, JumpFn& jump) {
+  const int S = g.levels();
+  const bool act = lane < (1 << S);
+  for (int d = 0; d < S; ++d) {
+    const int sh = S - d, half = 1 << (sh - 1);
     const int pos = lane & ((1 << sh) - 1);
     double er[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (act && pos == 0) jump((1 << d) + (lane >> sh), e, er);
+    if (act && pos == 0) jump(Top{(1 << d) + (lane >> sh)}, e, er);
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
       const double t = shup(er[c], half);
@@ -1066,11 +1181,12 @@ __device__ __forceinline__ void shuffle_down(const OnArgs& g, int lane, double* 
 // the lane's depth-S node value up to the root (lane 0), combining at every
 // shuffle level: stress sums by shuffles, tangents read from the right
 // child's LDS slot
-template <bool PLAIN>
-__device__ __forceinline__ void shuffle_up(const OnArgs& g, int pt, int lane, NodeV& cur, double& gg) {
-  const bool act = lane < (1 << g.S);
-  for (int d = g.S - 1; d >= 0; --d) {
-    const int sh = g.S - d, half = 1 << (sh - 1);
+template <bool PLAIN, class G>
+__device__ __forceinline__ void shuffle_up(const G& g, int pt, int lane, NodeV& cur, double& gg) {
+  const int S = g.levels();
+  const bool act = lane < (1 << S);
+  for (int d = S - 1; d >= 0; --d) {
+    const int sh = S - d, half = 1 << (sh - 1);
     __syncthreads();  // the children's tangents are in their lanes' slots
     NodeV rb;
     rb.K = cur.K + half;
@@ -1079,89 +1195,102 @@ __device__ __forceinline__ void shuffle_up(const OnArgs& g, int pt, int lane, No
       rb.s[c] = PLAIN ? shdown(cur.s[c], half) : 0.0;
       rb.sp[c] = shdown(cur.sp[c], half);
     }
-    if (act && (lane & ((1 << sh) - 1)) == 0) combine<PLAIN>(g, pt, (1 << d) + (lane >> sh), cur, rb, cur, gg);
+    if (act && (lane & ((1 << sh) - 1)) == 0) combine<PLAIN>(g, pt, Top{(1 << d) + (lane >> sh)}, cur, rb, cur, gg);
   }
 }
 
 // Strains of every leaf at the current jumps (leaves by `leaf`), residual
 // and elimination of the whole tree; root values on lane 0. root.K names the
 // lane's first LDS slot.
-template <int R, bool PLAIN, class LeafFn>
-__device__ __forceinline__ void eval_pass(const OnArgs& g, int pt, int lane, LeafFn& leaf, NodeV& root,
-                                          double& gg) {
+template <bool PLAIN, class G, class LeafFn>
+__device__ __forceinline__ void eval_pass(const G& g, int pt, int lane, LeafFn& leaf, NodeV& root, double& gg) {
   __syncthreads();  // the slots of the previous sweep have been read
   double e[6];
 #pragma unroll
   for (int c = 0; c < 6; ++c) e[c] = lane == 0 ? g.E[6 * pt + c] : 0.0;
-  auto jump = [&](int h, double* ev, double* er) {
+  auto jump = [&](Top h, double* ev, double* er) {
     double el[6];
-    split(g, h, node_jump(g, pt, h), ev, el, er);
+    split_jump(g, pt, h, ev, el, er);
 #pragma unroll
     for (int c = 0; c < 6; ++c) ev[c] = el[c];
   };
   shuffle_down(g, lane, e, jump);
-  if constexpr (R == 0) {
+  if constexpr (G::R == 0) {
     LeafV L{};
-    if (lane < g.nleaf) leaf(lane, e, L);
+    if (lane < g.leaves()) {
+      if (lane & 1)
+        leaf(PhaseOf<1>{}, Slot{0, lane}, e, L);
+      else
+        leaf(PhaseOf<0>{}, Slot{0, lane}, e, L);
+    }
     to_node(L, root);
   } else {
-    RegTree<R>::template up<PLAIN>(g, pt, (1 << g.S) + lane, e, root, gg, leaf);
+    RegTree<G::R, G>::template up<PLAIN>(g, pt, 0, lane, e, root, gg, leaf);
   }
   shuffle_up<PLAIN>(g, pt, lane, root, gg);
 }
 
-// leaf strains at the current jumps: fn(l, eps)
-template <int R, class Fn>
-__device__ __forceinline__ void strains_pass(const OnArgs& g, int pt, int lane, Fn& fn) {
+// leaf strains at the current jumps: fn(phase, slot, eps)
+template <class G, class Fn>
+__device__ __forceinline__ void strains_pass(const G& g, int pt, int lane, Fn& fn) {
   double e[6];
 #pragma unroll
   for (int c = 0; c < 6; ++c) e[c] = lane == 0 ? g.E[6 * pt + c] : 0.0;
-  auto jump = [&](int h, double* ev, double* er) {
+  auto jump = [&](Top h, double* ev, double* er) {
     double el[6];
-    split(g, h, node_jump(g, pt, h), ev, el, er);
+    split_jump(g, pt, h, ev, el, er);
 #pragma unroll
     for (int c = 0; c < 6; ++c) ev[c] = el[c];
   };
   shuffle_down(g, lane, e, jump);
-  if constexpr (R == 0) {
-    if (lane < g.nleaf) fn(lane, e);
+  if constexpr (G::R == 0) {
+    if (lane < g.leaves()) {
+      if (lane & 1)
+        fn(PhaseOf<1>{}, Slot{0, lane}, e);
+      else
+        fn(PhaseOf<0>{}, Slot{0, lane}, e);
+    }
   } else {
-    RegTree<R>::down(g, pt, (1 << g.S) + lane, e, fn);
+    RegTree<G::R, G>::down(g, pt, 0, lane, e, fn);
   }
 }
 
 // Newton steps of all jumps for a zero root strain change (after eval_pass);
-// the leaf strain changes: fn(l, deps)
-template <int R, class Fn>
-__device__ __forceinline__ void expand_pass(const OnArgs& g, int pt, int lane, bool update, Fn& fn) {
+// the leaf strain changes: fn(slot, deps)
+template <class G, class Fn>
+__device__ __forceinline__ void expand_pass(const G& g, int pt, int lane, bool update, Fn& fn) {
   double de[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  auto step = [&](int h, double* dv, double* dr) {
+  // the lane's own nodes from memory, on their way during the levels above
+  StepData own[1 << G::R];
+#pragma unroll
+  for (int n = 1; n < (1 << G::R); ++n) load_step(g, pt, Slot{n, lane}, own[n - 1]);
+  auto step = [&](Top h, double* dv, double* dr) {
     double dl[6];
-    node_step(g, pt, h, dv, update, dl, dr);
+    StepData d;
+    load_step(g, pt, h, d);
+    node_step(g, pt, h, d, dv, update, dl, dr);
 #pragma unroll
     for (int c = 0; c < 6; ++c) dv[c] = dl[c];
   };
   shuffle_down(g, lane, de, step);
-  if constexpr (R == 0) {
-    if (lane < g.nleaf) fn(lane, de);
+  if constexpr (G::R == 0) {
+    if (lane < g.leaves()) fn(Slot{0, lane}, de);
   } else {
-    RegTree<R>::expand(g, pt, (1 << g.S) + lane, de, update, fn);
+    RegTree<G::R, G>::expand(g, pt, 0, lane, own, de, update, fn);
   }
 }
 
-// every internal node the lane owns: fn(h)
-template <int R, class Fn>
-__device__ __forceinline__ void for_owned(const OnArgs& g, int lane, Fn& fn) {
-  if (lane >= (1 << g.S)) return;
-  for (int d = 0; d < g.S; ++d) {
-    const int sh = g.S - d;
-    if ((lane & ((1 << sh) - 1)) == 0) fn((1 << d) + (lane >> sh));
+// every internal node the lane owns: fn(slot)
+template <class G, class Fn>
+__device__ __forceinline__ void for_owned(const G& g, int lane, Fn& fn) {
+  const int S = g.levels();
+  if (lane >= (1 << S)) return;
+  for (int d = 0; d < S; ++d) {
+    const int sh = S - d;
+    if ((lane & ((1 << sh) - 1)) == 0) fn(Top{(1 << d) + (lane >> sh)});
   }
-  const int h0 = (1 << g.S) + lane;
 #pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int k = 0; k < (1 << r); ++k) fn((h0 << r) + k);
+  for (int n = 1; n < (1 << G::R); ++n) fn(Slot{n, lane});
 }
 
 // effective stress and the full 6 x 6 tangent of the root
@@ -1184,18 +1313,32 @@ __device__ __forceinline__ double residual_norm(const OnArgs& g, int lane, const
   return __shfl(r, 0, ON_LANES);
 }
 
+// State of step n, history sums and last plastic increment of a lane's PA66
+// leaves, in registers for all sweeps of the call.
+template <int N>
+struct PaLeaves {
+  double st[N][7], hs[N][7], dp[N];
+};
+
 // leaf law: stress and compressed tangent 3K P1 + ca P2 + cb N N
-__device__ void leaf_eval(const OnArgs& g, const ProbInc& in, int pt, int l, const double* e, double* sg,
-                          double& K3, double& ca, double& cb, double* nd) {
-  const int phase = l & 1;
-  const PhaseInc& pi = in.ph[phase];
-  if (phase == g.pa_phase) {
-    const int q = l >> 1;
-    const long long ss = g.nleaf >> 1;
-    const double* st = g.state + (long long)pt * g.nstate * ss + q;
-    double* hs = g.hist + (long long)pt * HIST_SLOTS * ss + q;
+template <int PA, int PHASE, int N>
+__device__ __forceinline__ void leaf_eval(const ProbInc& in, PaLeaves<N>& pl, Slot l, const double* e, double* sg,
+                                          double& K3, double& ca, double& cb, double* nd) {
+  const PhaseInc& pi = in.ph[PHASE];
+  if constexpr (PHASE == PA) {
+    const bool second = N > 1 && l.grp >> 1;
+    double st[7], hs[7], dp = second ? pl.dp[N - 1] : pl.dp[0];
+#pragma unroll
+    for (int c = 0; c < 7; ++c) {
+      st[c] = second ? pl.st[N - 1][c] : pl.st[0][c];
+      hs[c] = second ? pl.hs[N - 1][c] : pl.hs[0][c];
+    }
     PaOut o;
-    pa66_point(in, e, st, ss, nullptr, nullptr, o, nullptr, nullptr, hs, hs + 7 * ss);
+    pa66_point(in, e, st, 1, nullptr, nullptr, o, nullptr, nullptr, hs, &dp);
+    if (second)
+      pl.dp[N - 1] = dp;
+    else
+      pl.dp[0] = dp;
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
       sg[c] = o.sig[c];
@@ -1221,16 +1364,16 @@ __device__ void leaf_eval(const OnArgs& g, const ProbInc& in, int pt, int l, con
 // point partials of leaf l at its converged strain e, from state n:
 // d sigma / d theta, d D / d eps, d D / d theta (closed form for the
 // thermoelastic phase, central differences of the PA66 update)
-__device__ void leaf_partials(const OnArgs& g, const ProbInc& in, int pt, int l, const double* e, double* st_,
-                              double* gd, double& hd) {
-  const int phase = l & 1;
-  const double* enp = g.epsn + ((long long)g.nleaf * pt + l) * 6;
+template <int PA, int PHASE, class G>
+__device__ __forceinline__ void leaf_partials(const G& g, const ProbInc& in, int pt, Slot l, const double* e,
+                                              double* st_, double* gd, double& hd) {
+  const double* enp = g.at(g.epsn, 6, pt, l);
   double en[6];
 #pragma unroll
-  for (int c = 0; c < 6; ++c) en[c] = enp[c];
-  if (phase == g.pa_phase) {
-    const long long ss = g.nleaf >> 1;
-    const int q = l >> 1;
+  for (int c = 0; c < 6; ++c) en[c] = enp[c * g.stride()];
+  if constexpr (PHASE == PA) {
+    const long long ss = g.leaves() >> 1;
+    const unsigned q = g.phase_index(l);
     const double* st = g.state + (long long)pt * g.nstate * ss + q;
     const double* hs = g.hist + (long long)pt * HIST_SLOTS * ss + q;
     double sp[6], Dp = 0.0;
@@ -1258,7 +1401,7 @@ __device__ void leaf_partials(const OnArgs& g, const ProbInc& in, int pt, int l,
       }
     }
   } else {
-    const PhaseInc& pi = in.ph[phase];
+    const PhaseInc& pi = in.ph[PHASE];
     const double ca = pi.K3 * pi.alpha0;
     const double trd = (e[0] - en[0]) + (e[1] - en[1]) + (e[2] - en[2]);
 #pragma unroll
@@ -1270,32 +1413,46 @@ __device__ void leaf_partials(const OnArgs& g, const ProbInc& in, int pt, int l,
   }
 }
 
-template <int R>
-__global__ void __launch_bounds__(ON_LANES) k_dmn_online(OnArgs g) {
+// R register levels, PA the phase with the PA66 law (-1: none), T: all four tangents
+template <int R, int PA, bool T>
+__global__ void __launch_bounds__(ON_LANES, ON_WAVES) k_dmn_online(OnView<R> g) {
   // condensed tangents: one slot per register level (at least one), lane-interleaved
   __shared__ double kslot[(R > 0 ? R : 1) * 21 * ON_LANES];
+  __shared__ double top[TOP_FIELDS * ON_LANES];
+  g.top = top;
   const int pt = blockIdx.x;
   const int lane = threadIdx.x;
-  const int nleaf = g.nleaf;
+  const int st = g.stride();
+  if (lane >= 1 && lane < g.leaves()) {  // node `lane` of those above depth S
+    const double* nt = g.table(Slot{0, lane});
+    const double* ah = g.jump(pt, Slot{0, lane});
+#pragma unroll
+    for (int f = 0; f < ON_NODE; ++f) top[(TOP_TABLE + f) * ON_LANES + lane] = nt[f * st];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) top[(TOP_JUMP + k) * ON_LANES + lane] = ah[k * st];
+  }
+  __syncthreads();
   constexpr int LPT = 1 << R;  // leaves per lane
   const int ix = g.inc_ix[pt];
   const ProbInc& in = g.inc[ix];
-  const bool leaves = lane * LPT < nleaf;
+  const bool leaves = lane * LPT < g.leaves();
   // branch history sums of this lane's PA66 leaves for this increment
-  if (leaves && g.pa_phase >= 0) {
-    const long long ss = nleaf >> 1;
+  constexpr int NPA = R > 0 ? LPT / 2 : 1;
+  PaLeaves<NPA> pl;
+  if (PA >= 0 && leaves && (R > 0 || (lane & 1) == PA)) {
+    const long long ss = g.leaves() >> 1;
 #pragma unroll
-    for (int i = 0; i < LPT; ++i) {
-      const int l = lane * LPT + i;
-      if ((l & 1) != g.pa_phase) continue;
-      const int q = l >> 1;
-      double hd[6], hs;
-      pa66_history(in, g.state + (long long)pt * g.nstate * ss + q, ss, hd, hs);
+    for (int i = 0; i < NPA; ++i) {
+      const unsigned q = g.phase_index(Slot{2 * i, lane});
+      const double* state = g.state + (long long)pt * g.nstate * ss + q;
+      pa66_history(in, state, ss, pl.hs[i], pl.hs[i][6]);
       double* h = g.hist + (long long)pt * HIST_SLOTS * ss + q;
 #pragma unroll
-      for (int c = 0; c < 6; ++c) h[c * ss] = hd[c];
-      h[6 * ss] = hs;
-      h[7 * ss] = -1.0;
+      for (int c = 0; c < 7; ++c) {
+        pl.st[i][c] = state[c * ss];
+        h[c * ss] = pl.hs[i][c];
+      }
+      pl.dp[i] = -1.0;
     }
   }
   // predictor: start from the committed jumps plus s times their last change,
@@ -1310,54 +1467,57 @@ __global__ void __launch_bounds__(ON_LANES) k_dmn_online(OnArgs g) {
       pp += ep[6 + c] * ep[6 + c];
     }
     if (g.committed[pt] && pp > 0.0 && isfinite(ee)) pred_s = fmin(2.0, fmax(0.0, ee / pp));
-    auto start = [&](int h) {
-      double* ah = node_jump(g, pt, h);
-      double* a0 = g.a0 + ((long long)pt * nleaf + h) * 3;
-      const double* dh = g.dah + ((long long)pt * nleaf + h) * 3;
+    auto start = [&](auto h) {
+      double* ah = g.jump(pt, h);
+      const int sh = g.stride(h);
+      double* a0 = g.at(g.a0, 3, pt, g.slot(h));
+      const double* dh = g.at(g.dah, 3, pt, g.slot(h));
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        a0[k] = ah[k];
-        ah[k] += pred_s * dh[k];
+        a0[k * st] = ah[k * sh];
+        ah[k * sh] += pred_s * dh[k * st];
       }
     };
-    for_owned<R>(g, lane, start);
+    for_owned(g, lane, start);
   }
-  auto wleaf = [&](int l) { return g.node[ON_NODE * (nleaf + l) + 4]; };
-  auto law = [&](int l, const double* e, LeafV& L) {
+  auto law = [&](auto ph, Slot l, const double* e, LeafV& L) {
     double sg[6];
-    leaf_eval(g, in, pt, l, e, sg, L.K3, L.ca, L.cb, L.nd);
-    L.w = wleaf(l);
+    leaf_eval<PA, decltype(ph)::value>(in, pl, l, e, sg, L.K3, L.ca, L.cb, L.nd);
+    L.w = g.leaf_weight(l);
 #pragma unroll
     for (int c = 0; c < 6; ++c) L.s[c] = L.w * sg[c];
   };
   NodeV root;
   root.K = kslot + lane;
-  double gg = 0.0;
-  eval_pass<R, true>(g, pt, lane, law, root, gg);
-  double res = residual_norm(g, lane, root, gg);
-  auto nothing = [](int, const double*) {};
-  int it = 0;
-  for (it = 1; it <= g.maxit; ++it) {
-    expand_pass<R>(g, pt, lane, true, nothing);
-    const double res_old = res;
-    gg = 0.0;
-    eval_pass<R, true>(g, pt, lane, law, root, gg);
+  auto nothing = [](Slot, const double*) {};
+  // sweeps: the start's, then after a Newton step (it counts them) and after
+  // each cut back of a step that did not lower the residual (1, gamma, gamma^2, ..)
+  int it = 0, cuts = 0;
+  double res, res_old = 0.0;
+  for (;;) {
+    double gg = 0.0;
+    eval_pass<true>(g, pt, lane, law, root, gg);
     res = residual_norm(g, lane, root, gg);
-    for (int i = 0; i < g.maxbt; ++i) {  // backtracking: steps 1, gamma, gamma^2, ...
-      if (res < res_old) break;
-      const double cut = pow(g.gamma, (double)i) * (1.0 - g.gamma);
-      auto back = [&](int h) {
-        double* ah = node_jump(g, pt, h);
-        const double* sc = node_scr(g, pt, h);
+    if (it > 0) {
+      if (!(res < res_old) && cuts < g.maxbt) {
+        const double cut = pow(g.gamma, (double)cuts) * (1.0 - g.gamma);
+        auto back = [&](auto h) {
+          double* ah = g.jump(pt, h);
+          const double* sc = g.scratch(pt, h);
+          const int sh = g.stride(h);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) ah[k] -= cut * sc[21 + k];
-      };
-      for_owned<R>(g, lane, back);
-      gg = 0.0;
-      eval_pass<R, true>(g, pt, lane, law, root, gg);
-      res = residual_norm(g, lane, root, gg);
+          for (int k = 0; k < 3; ++k) ah[k * sh] -= cut * sc[(21 + k) * sh];
+        };
+        for_owned(g, lane, back);
+        ++cuts;
+        continue;
+      }
+      if (res < g.tol) break;
     }
-    if (res < g.tol) break;
+    if (++it > g.maxit) break;
+    expand_pass(g, pt, lane, true, nothing);
+    res_old = res;
+    cuts = 0;
   }
   const bool conv = res < g.tol;
   const bool commit = conv && !g.trial;
@@ -1365,101 +1525,100 @@ __global__ void __launch_bounds__(ON_LANES) k_dmn_online(OnArgs g) {
   // effective stress and tangent: the root of the last sweep
   double* o = g.out + (long long)pt * ON_OUT;
   if (lane == 0) put_root(o, root);
-  if (g.what) {
-    auto partials = [&](int l, const double* e) {
+  if constexpr (T) {
+    auto partials = [&](auto ph, Slot l, const double* e) {
       double st_[6], gd[6], hd;
-      leaf_partials(g, in, pt, l, e, st_, gd, hd);
-      double* lp = g.lp + ((long long)pt * nleaf + l) * ON_LP;
+      leaf_partials<PA, decltype(ph)::value>(g, in, pt, l, e, st_, gd, hd);
+      double* lp = g.at(g.lp, ON_LP, pt, l);
 #pragma unroll
       for (int c = 0; c < 6; ++c) {
-        lp[c] = st_[c];
-        lp[6 + c] = gd[c];
+        lp[c * st] = st_[c];
+        lp[(6 + c) * st] = gd[c];
       }
-      lp[12] = hd;
+      lp[12 * st] = hd;
     };
-    strains_pass<R>(g, pt, lane, partials);
-    // d<sigma>/dtheta: the jumps equilibrate the leaf sources w dsigma/dtheta
-    auto src_theta = [&](int l, const double* e, LeafV& L) {
-      const double* lp = g.lp + ((long long)pt * nleaf + l) * ON_LP;
-      double sg[6];
-      leaf_eval(g, in, pt, l, e, sg, L.K3, L.ca, L.cb, L.nd);
-      L.w = wleaf(l);
-#pragma unroll
-      for (int c = 0; c < 6; ++c) L.s[c] = L.w * lp[c];
-    };
-    NodeV rt;
-    rt.K = kslot + lane;
-    double unused = 0.0;
-    eval_pass<R, false>(g, pt, lane, src_theta, rt, unused);
-    if (lane == 0)
-#pragma unroll
-      for (int c = 0; c < 6; ++c) o[O_DSDT + c] = rt.sp[c];
-    // d<D>/dtheta = sum_l w_l (dD/dtheta_l + dD/deps_l . d eps_l / d theta)
-    double dT = 0.0;
-    auto heat = [&](int l, const double* de) {
-      const double* lp = g.lp + ((long long)pt * nleaf + l) * ON_LP;
-      double x = lp[12];
-#pragma unroll
-      for (int c = 0; c < 6; ++c) x += lp[6 + c] * de[c];
-      dT += wleaf(l) * x;
-    };
-    expand_pass<R>(g, pt, lane, false, heat);
-    dT = wave_sum(dT);
-    if (lane == 0) o[O_DDDT] = dT;
-    // d<D>/dE = sum_l w_l (d eps_l / dE)^T dD/deps_l: the condensed value of
+    strains_pass(g, pt, lane, partials);
+    // k = 0, d<sigma>/dtheta: the jumps equilibrate the leaf sources w dsigma/dtheta;
+    // k = 1, d<D>/dE = sum_l w_l (d eps_l / dE)^T dD/deps_l: the condensed value of
     // the leaf sources w dD/deps (the localization is symmetric in this sense)
-    auto src_coup = [&](int l, const double* e, LeafV& L) {
-      const double* lp = g.lp + ((long long)pt * nleaf + l) * ON_LP;
-      double sg[6];
-      leaf_eval(g, in, pt, l, e, sg, L.K3, L.ca, L.cb, L.nd);
-      L.w = wleaf(l);
+#pragma unroll 1
+    for (int k = 0; k < 2; ++k) {
+      auto source = [&](auto ph, Slot l, const double* e, LeafV& L) {
+        const double* lp = g.at(g.lp, ON_LP, pt, l) + 6 * k * st;
+        double sg[6];
+        leaf_eval<PA, decltype(ph)::value>(in, pl, l, e, sg, L.K3, L.ca, L.cb, L.nd);
+        L.w = g.leaf_weight(l);
 #pragma unroll
-      for (int c = 0; c < 6; ++c) L.s[c] = L.w * lp[6 + c];
-    };
-    eval_pass<R, false>(g, pt, lane, src_coup, rt, unused);
-    if (lane == 0)
+        for (int c = 0; c < 6; ++c) L.s[c] = L.w * lp[c * st];
+      };
+      NodeV rt;
+      rt.K = kslot + lane;
+      double unused = 0.0;
+      eval_pass<false>(g, pt, lane, source, rt, unused);
+      if (lane == 0)
 #pragma unroll
-      for (int c = 0; c < 6; ++c) o[O_DDDE + c] = rt.sp[c];
+        for (int c = 0; c < 6; ++c) o[(k == 0 ? O_DSDT : O_DDDE) + c] = rt.sp[c];
+      if (k == 1) break;
+      // d<D>/dtheta = sum_l w_l (dD/dtheta_l + dD/deps_l . d eps_l / d theta)
+      double dT = 0.0;
+      auto heat = [&](Slot l, const double* de) {
+        const double* lp = g.at(g.lp, ON_LP, pt, l);
+        double x = lp[12 * st];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) x += lp[(6 + c) * st] * de[c];
+        dT += g.leaf_weight(l) * x;
+      };
+      expand_pass(g, pt, lane, false, heat);
+      dT = wave_sum(dT);
+      if (lane == 0) o[O_DDDT] = dT;
+    }
+  }
+  __syncthreads();  // the jumps above depth S go back: the next call starts from them
+  if (lane >= 1 && lane < g.leaves()) {
+    double* ah = g.jump(pt, Slot{0, lane});
+#pragma unroll
+    for (int k = 0; k < 3; ++k) ah[k * st] = top[(TOP_JUMP + k) * ON_LANES + lane];
   }
   // coupling term and dissipation of every leaf; commit if converged
   double D = 0.0, Dd = 0.0;
-  auto fin = [&](int l, const double* e) {
-    const int phase = l & 1;
-    double* en = g.epsn + ((long long)pt * nleaf + l) * 6;
-    double Dl = 0.0, Ddl = 0.0;
-    if (phase == g.pa_phase) {
-      const long long ss = nleaf >> 1;
-      const int q = l >> 1;
-      double* st = g.state + (long long)pt * g.nstate * ss + q;
-      double* hs = g.hist + (long long)pt * HIST_SLOTS * ss + q;
-      double enl[6];
+  auto fin = [&](auto ph, Slot l, const double* e) {
+    constexpr int PHASE = decltype(ph)::value;
+    double* enp = g.at(g.epsn, 6, pt, l);
+    double en[6];
 #pragma unroll
-      for (int c = 0; c < 6; ++c) enl[c] = en[c];
+    for (int c = 0; c < 6; ++c) en[c] = enp[c * st];
+    double Dl = 0.0, Ddl = 0.0;
+    if constexpr (PHASE == PA) {
+      const long long ss = g.leaves() >> 1;
+      const unsigned q = g.phase_index(l);
+      double* state = g.state + (long long)pt * g.nstate * ss + q;
+      double* hs = g.hist + (long long)pt * HIST_SLOTS * ss + q;
       PaOut po;
-      pa66_point(in, e, st, ss, commit ? st : nullptr, enl, po, &Ddl, &Dl, hs, nullptr);
+      pa66_point(in, e, state, ss, commit ? state : nullptr, en, po, &Ddl, &Dl, hs, nullptr);
     } else {
-      const PhaseInc& pi = in.ph[phase];
+      const PhaseInc& pi = in.ph[PHASE];
       const double trd = (e[0] - en[0]) + (e[1] - en[1]) + (e[2] - en[2]);
       Dl = -in.theta * pi.K3 * pi.alpha0 * trd / in.dt;
     }
-    const double w = wleaf(l);
+    const double w = g.leaf_weight(l);
     D += w * Dl;
     Dd += w * Ddl;
     if (commit)
 #pragma unroll
-      for (int c = 0; c < 6; ++c) en[c] = e[c];
+      for (int c = 0; c < 6; ++c) enp[c * st] = e[c];
   };
-  strains_pass<R>(g, pt, lane, fin);
+  strains_pass(g, pt, lane, fin);
   if (g.pred) {
     if (commit) {
-      auto change = [&](int h) {
-        const double* ah = node_jump(g, pt, h);
-        const double* a0 = g.a0 + ((long long)pt * nleaf + h) * 3;
-        double* dh = g.dah + ((long long)pt * nleaf + h) * 3;
+      auto change = [&](auto h) {
+        const double* ah = g.jump(pt, h);
+        const int sh = g.stride(h);
+        const double* a0 = g.at(g.a0, 3, pt, g.slot(h));
+        double* dh = g.at(g.dah, 3, pt, g.slot(h));
 #pragma unroll
-        for (int k = 0; k < 3; ++k) dh[k] = ah[k] - a0[k];
+        for (int k = 0; k < 3; ++k) dh[k * st] = ah[k * sh] - a0[k * st];
       };
-      for_owned<R>(g, lane, change);
+      for_owned(g, lane, change);
     }
     if (lane == 0) g.committed[pt] = commit ? 1 : 0;
   }
@@ -1484,6 +1643,39 @@ __global__ void __launch_bounds__(ON_LANES) k_dmn_online(OnArgs g) {
   }
 }
 
+}  // namespace
+
+namespace {
+template <int R, int PA>
+void launch_online_tangents(const OnArgs& g, hipStream_t s, int n) {
+  OnView<R> v;
+  static_cast<OnArgs&>(v) = g;
+  v.top = nullptr;
+  if (g.what)
+    hipLaunchKernelGGL((k_dmn_online<R, PA, true>), dim3(n), dim3(ON_LANES), 0, s, v);
+  else
+    hipLaunchKernelGGL((k_dmn_online<R, PA, false>), dim3(n), dim3(ON_LANES), 0, s, v);
+}
+template <int R>
+void launch_online_phase(const OnArgs& g, hipStream_t s, int n) {
+  if (g.pa_phase == 0)
+    launch_online_tangents<R, 0>(g, s, n);
+  else if (g.pa_phase == 1)
+    launch_online_tangents<R, 1>(g, s, n);
+  else
+    launch_online_tangents<R, -1>(g, s, n);
+}
+void launch_online_levels(const OnArgs& g, hipStream_t s, int n) {
+  static_assert(ON_MAX_K - ON_SHUF <= 2, "at most two register levels per lane");
+  switch (g.K - g.S) {  // register levels below the shuffle levels
+    case 0:
+      return launch_online_phase<0>(g, s, n);
+    case 1:
+      return launch_online_phase<1>(g, s, n);
+    default:
+      return launch_online_phase<2>(g, s, n);
+  }
+}
 }  // namespace
 
 struct PairHash {
@@ -1539,8 +1731,9 @@ DmnOnline* dmn_online_create(const Dmn& net, const hom_law* laws, int npoints, d
   const size_t half = (size_t)o->nleaf / 2;
   o->p = dalloc_into<double>(o->allocs, net.nparam);
   hip_check(hipMemcpy(o->p, net.p, net.nparam * sizeof(double), hipMemcpyDeviceToDevice), "hipMemcpy");
-  o->node = dalloc_into<double>(o->allocs, (size_t)2 * o->nleaf * ON_NODE);
-  hipLaunchKernelGGL(k_dmn_node_table, dim3(1), dim3(1), 0, nullptr, o->p, o->nleaf, o->node);
+  o->node = dalloc_into<double>(o->allocs, (size_t)o->nleaf * (ON_NODE + 1));
+  hipLaunchKernelGGL(k_dmn_node_table, dim3(1), dim3(1), 0, nullptr, o->p, o->nleaf, std::min(o->K, ON_SHUF),
+                     o->node);
   hip_check(hipGetLastError(), "k_dmn_node_table");
   if (o->nstate) {
     o->state = dalloc_into<double>(o->allocs, (size_t)npoints * o->nstate * half);
@@ -1660,18 +1853,7 @@ void dmn_online_step(DmnOnline* o, const double* strain, const double* theta, co
   g.gamma = 0.5;
   g.maxit = o->maxit;
   g.maxbt = 8;
-  static_assert(ON_MAX_K - ON_SHUF <= 2, "at most two register levels per lane");
-  switch (o->K - g.S) {  // register levels below the shuffle levels
-    case 0:
-      hipLaunchKernelGGL(k_dmn_online<0>, dim3(n), dim3(ON_LANES), 0, nullptr, g);
-      break;
-    case 1:
-      hipLaunchKernelGGL(k_dmn_online<1>, dim3(n), dim3(ON_LANES), 0, nullptr, g);
-      break;
-    default:
-      hipLaunchKernelGGL(k_dmn_online<2>, dim3(n), dim3(ON_LANES), 0, nullptr, g);
-      break;
-  }
+  launch_online_levels(g, nullptr, n);
   hip_check(hipGetLastError(), "k_dmn_online");
   hip_check(hipMemcpy(o->out_h, o->out, (size_t)ON_OUT * n * sizeof(double), hipMemcpyDeviceToHost), "hipMemcpy");
   for (int i = 0; i < n; ++i) {

@@ -348,3 +348,33 @@ def test_gradients_at_the_depth_limits(K, count):
     assert np.abs(D - ref).max() <= 1e-10 * np.abs(ref).max()
     assert abs(Jg - J) <= 1e-10 * J
     assert em <= 1e-7 and ev <= 1e-7
+
+
+@pytest.mark.parametrize("law1,law2", [("pa66", "e_glass"), ("e_glass", "pa66"), ("e_glass", "e_glass")])
+@pytest.mark.parametrize("K", [1, 4, 6, 7, 8])
+def test_online_for_each_phase_and_depth(K, law1, law2):
+    """Every place of the PA66 law (even leaves, odd leaves, none) at every
+    number of levels per lane: three increments and a trial step with all
+    tangents against the oracle, at the tolerances of the comparison above."""
+    rng = np.random.default_rng(400 + K)
+    m, v = random_params(K, rng)
+    laws = [getattr(W, n)() for n in (law1, law2)]
+    gpu = hom.DmnOnline(_net(K, m, v), *laws, 2, tol=1e-10)
+    ref = oracle_online(m, v, *laws, 2, 1e-10)
+    dirs = np.array([[1, 0, 0, 0, 0, 0.4], [0.3, -0.2, 1, 0, 0.5, 0]], dtype=float)
+    for k in range(1, 4):
+        gpu.step(dirs * 0.006 * k, 310.0, 2.0)
+        for i in range(2):
+            ref[i].step(dirs[i] * 0.006 * k, 310.0, 2.0)
+    out = gpu.step(dirs * 0.022, 310.0, 2.0, what=1, trial=True)
+    for i in range(2):
+        o, g = ref[i].step(dirs[i] * 0.022, 310.0, 2.0, all_tangents=True), out[i]
+        assert g["status"] == hom.HOM_OK
+        dsde_o = o["dsde"] * WM[None, :] / WM[:, None]
+        assert np.abs(g["stress"] - o["stress"]).max() <= 1e-8 * np.abs(o["stress"]).max()
+        assert np.abs(g["dsde"] - dsde_o).max() <= 1e-7 * np.abs(dsde_o).max()
+        assert abs(g["coupling"] - o["coupling"]) <= 1e-7 * max(abs(o["coupling"]), 1e-9)
+        assert np.abs(g["dsdt"] - o["dsdt"] / WM).max() <= 1e-6 * np.abs(o["dsdt"]).max()
+        assert np.abs(g["dDde"] - o["dDde"] * WM).max() <= 1e-6 * np.abs(o["dDde"]).max()
+        assert abs(g["dDdt"] - o["dDdt"]) <= 1e-6 * abs(o["dDdt"])
+    gpu.close()
