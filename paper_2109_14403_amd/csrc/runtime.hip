@@ -869,12 +869,15 @@ class BatchT : public BatchImpl {
     return basic ? (long long)lim.max_newton + 2 : (long long)(lim.max_newton + 1) * (lim.max_krylov + 2);
   }
 
-  int chunk_size(const Group<T>& G) const {
+  int chunk_size(const Group<T>& G, int variant) const {
     if (opts.chunk > 0) return opts.chunk;
-    // large grids: four iterations per host check (each check is a host round
-    // trip of ~1 % of an iteration; after convergence the rest of a chunk's
-    // launches return at once); small ones: 16
-    return (G.nvox * G.nprob >= (1LL << 22)) ? 4 : 16;
+    // A check costs 10 to 15 us; after convergence the rest of a chunk's launches
+    // return at once, 2 us each. Large grids: four iterations a check (about 1 %
+    // of them). Small ones: 16, near the best for the 30 to 150 iterations of
+    // an increment's mechanics (chunks of 4 and of 8 queued ahead on a progress
+    // word in host memory were 0 to 7 % slower). Conduction without a change of
+    // the gradient is over after one evaluation: four (16: 70 to 100 us more).
+    return variant == 1 || G.nvox * G.nprob >= (1LL << 22) ? 4 : 16;
   }
 
   void run_chunk(Group<T>& G, int variant, bool basic, int k) {
@@ -902,7 +905,7 @@ class BatchT : public BatchImpl {
     hipStream_t stream = G.stream;  // this group's lane
     // timed per kernel (profiling): one iteration per check, so that no launch
     // follows convergence and every timed launch did work
-    const int k = prof.on ? 1 : chunk_size(G);
+    const int k = prof.on ? 1 : chunk_size(G, variant);
     Ctl* ctl = variant == 1 ? G.ctl_t : G.ctl_m;
     long long done_its = 0;
     for (;;) {
