@@ -131,8 +131,8 @@ struct Pipe {
   int green;                // Green enum
   int div;                  // problems that share one set of phases and tangents: 1, or the columns of
                             // a tangent call that are solved together (problem = cell * div + column)
-  int xblocks;              // > 0: Newton-CG iteration; the x pass left xblocks partial sums a
-                            // problem, and the passes below drive the solver's state
+  int xblocks;              // > 0: Newton-CG or fused fixed-point iteration; the x pass left xblocks
+                            // partial sums a problem, and the passes below drive the solver's state
   int zblocks;              // work-groups a problem of the pass that applies the Green operator
   Limits lim;
 };

@@ -73,6 +73,27 @@ LaunchInfo xmid_c(const Pipe<T>& a, hipStream_t s, bool dry) {
   return li;
 }
 
+template <typename T, int C, int N, int NL>
+LaunchInfo xbasic_c(const Pipe<T>& a, hipStream_t s, bool dry) {
+  LaunchInfo li;
+  li.threads = x_threads<N, NL, C>();
+  li.blocks = a.nprob * ((a.ny * a.nz + NL - 1) / NL);
+  li.lds = (size_t)xmid_lds_elems<N, NL, C>() * sizeof(c2<T>);
+  {
+    static bool attr = false;
+    if (!attr && li.lds > 65536) {
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_xbasic<T, C, N, NL>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      (void)hipGetLastError();
+      attr = true;
+    }
+  }
+  if (!dry) {
+    hipLaunchKernelGGL((k_xbasic<T, C, N, NL>), dim3(li.blocks), dim3(li.threads), li.lds, s, a);
+  }
+  return li;
+}
+
 template <typename T, int C, int N, int TX, int V>
 LaunchInfo ypass_c(const Pipe<T>& a, int inverse, hipStream_t s, bool dry) {
   constexpr int G = N / Plan<N, V>::M;
@@ -197,6 +218,14 @@ LaunchInfo xmid_launch(const Pipe<T>& a, hipStream_t s, bool dry) {
 }
 
 template <typename T, int N>
+LaunchInfo xbasic_launch(const Pipe<T>& a, hipStream_t s, bool dry) {
+  constexpr int NL = x_lines(N, sizeof(T) == 8, true), FEW = xmid_lines_few(N, sizeof(T) == 8);
+  if (xmid_lines(N, sizeof(T) == 8, (long long)a.nprob * a.ny * a.nz) == FEW)
+    return a.C == 6 ? xbasic_c<T, 6, N, FEW>(a, s, dry) : xbasic_c<T, 3, N, FEW>(a, s, dry);
+  return a.C == 6 ? xbasic_c<T, 6, N, NL>(a, s, dry) : xbasic_c<T, 3, N, NL>(a, s, dry);
+}
+
+template <typename T, int N>
 LaunchInfo ypass_launch(const Pipe<T>& a, int sched, int inverse, hipStream_t s, bool dry) {
   const int tx = schedule_tile(sched);
   if (schedule_plan(sched) == 1)
@@ -216,6 +245,7 @@ LaunchInfo zgreen_launch(const Pipe<T>& a, int sched, hipStream_t s, bool dry) {
   template LaunchInfo xfwd_launch<T, HOM_N>(const Pipe<T>&, hipStream_t, bool);             \
   template LaunchInfo xinv_launch<T, HOM_N>(const Pipe<T>&, hipStream_t, bool);             \
   template LaunchInfo xmid_launch<T, HOM_N>(const Pipe<T>&, hipStream_t, bool);             \
+  template LaunchInfo xbasic_launch<T, HOM_N>(const Pipe<T>&, hipStream_t, bool);           \
   template LaunchInfo yzplane_launch<T, HOM_N>(const Pipe<T>&, hipStream_t, bool);          \
   template LaunchInfo ypass_launch<T, HOM_N>(const Pipe<T>&, int, int, hipStream_t, bool);  \
   template LaunchInfo zgreen_launch<T, HOM_N>(const Pipe<T>&, int, hipStream_t, bool);

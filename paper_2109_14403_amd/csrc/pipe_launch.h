@@ -44,8 +44,9 @@ constexpr int x_lines(int n, bool fp64, bool mid) {
 // (in brackets the work-groups they made before): FP64 32 x 16^2 (16) 1.12, 24^3
 // (36) 1.19, 32^3 (64) 1.06, 96 x 24 x 48 (72) 1.14, 128 x 32 x 32 (128) 1.08, 48^3
 // (144) 1.03 times as fast; FP32 24^3 (18) 1.06, 32^3 (64) 1.05, 96 x 24 x 48 (72)
-// 1.10, but 128 x 32 x 32 (128) 0.98 and 48^3 (144) 0.99. The forward and inverse
-// passes of the fixed-point scheme gain nothing (16^3: 0.97).
+// 1.10, but 128 x 32 x 32 (128) 0.98 and 48^3 (144) 0.99. The fixed-point scheme's
+// middle pass: 16^3 1.05, 32^3 FP64 1.03, FP32 1.06, 24 x 16 x 32 FP32 1.14 (its
+// separate forward and inverse passes: 16^3 0.97, left as they are).
 constexpr int xmid_lines_few(int n, bool fp64) {
   return x_lines(n, fp64, true) < 4 ? 1 : x_lines(n, fp64, true) / 4;
 }
@@ -96,6 +97,8 @@ LaunchInfo xinv_launch(const Pipe<T>& a, hipStream_t s, bool dry);
 template <typename T, int N>
 LaunchInfo xmid_launch(const Pipe<T>& a, hipStream_t s, bool dry);
 template <typename T, int N>
+LaunchInfo xbasic_launch(const Pipe<T>& a, hipStream_t s, bool dry);
+template <typename T, int N>
 LaunchInfo ypass_launch(const Pipe<T>& a, int sched, int inverse, hipStream_t s, bool dry);
 template <typename T, int N>
 LaunchInfo zgreen_launch(const Pipe<T>& a, int sched, hipStream_t s, bool dry);
@@ -108,6 +111,8 @@ template <typename T>
 LaunchInfo run_xinv(const Pipe<T>& a, hipStream_t s, bool dry = false);
 template <typename T>
 LaunchInfo run_xmid(const Pipe<T>& a, hipStream_t s, bool dry = false);
+template <typename T>
+LaunchInfo run_xbasic(const Pipe<T>& a, hipStream_t s, bool dry = false);
 template <typename T>
 LaunchInfo run_ypass(const Pipe<T>& a, int sched, int inverse, hipStream_t s, bool dry = false);
 template <typename T>

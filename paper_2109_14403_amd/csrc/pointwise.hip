@@ -628,21 +628,7 @@ __global__ void __launch_bounds__(RED_THREADS) k_reduce_a(Ctl* ctl, const double
   if (c.mode != M_BASIC) return;
   sum_parts<2>(part, maxblk, nblk, prob, s, red);
   if (threadIdx.x != 0) return;
-  c.pipelines += 1;
-  const double dd = s[0], xx = s[1];
-  const double err = xx > 0.0 ? sqrt(dd / xx) : 0.0;
-  c.res = err;
-  c.newton_it += 1;
-  if (!isfinite(err)) {
-    c.mode = M_FAIL;
-    c.status = -4;
-  } else if (err <= lim.tol) {
-    c.mode = M_DONE;
-    c.status = 1;
-  } else if (c.newton_it >= lim.max_newton) {
-    c.mode = M_FAIL;
-    c.status = -3;
-  }
+  basic_transition(c, s[0], s[1], lim);
 }
 
 constexpr int RED_STAGE_THREADS = 256;

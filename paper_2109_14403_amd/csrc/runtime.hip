@@ -228,6 +228,10 @@ LaunchInfo run_xmid(const Pipe<T>& a, hipStream_t s, bool dry) {
   HOM_DISPATCH(a.nx, (xmid_launch<T, NN>(a, s, dry)))
 }
 template <typename T>
+LaunchInfo run_xbasic(const Pipe<T>& a, hipStream_t s, bool dry) {
+  HOM_DISPATCH(a.nx, (xbasic_launch<T, NN>(a, s, dry)))
+}
+template <typename T>
 LaunchInfo run_ypass(const Pipe<T>& a, int sched, int inverse, hipStream_t s, bool dry) {
   HOM_DISPATCH(a.ny, (ypass_launch<T, NN>(a, sched, inverse, s, dry)))
 }
@@ -793,7 +797,8 @@ class BatchT : public BatchImpl {
     LaunchInfo lx = run_xfwd<T>(a, stream, true);
     LaunchInfo li = run_xinv<T>(a, stream, true);
     LaunchInfo lm = run_xmid<T>(a, stream, true);
-    if (!launch_ok(lx) || !launch_ok(li) || !launch_ok(lm)) fail(HOM_E_UNSUPPORTED, "x-pass does not fit the work-group limits");
+    LaunchInfo lb = run_xbasic<T>(a, stream, true);
+    if (!launch_ok(lb) || !launch_ok(lx) || !launch_ok(li) || !launch_ok(lm)) fail(HOM_E_UNSUPPORTED, "x-pass does not fit the work-group limits");
   }
 
   Limits limits(int phys) const {
@@ -820,23 +825,29 @@ class BatchT : public BatchImpl {
     const int C = phys == 0 ? 6 : 3;
     Limits lim = limits(phys);
     if (variant >= 2) lim.linear = 1;
-    if (!basic) {  // the y and z passes drive the Newton-CG state
+    // fixed point without internal variables: one x pass an iteration
+    const bool fused = basic && (phys == 1 || !G.state);
+    if (!basic || fused) {  // the y and z passes drive the solver's state
       a.xblocks = G.xmblocks;
       const int tx = schedule_tile(G.txz[phys]);
       a.zblocks = G.ny * ((G.P + tx - 1) / tx);
       a.lim = lim;
     }
     Ctl* ctl = phys == 0 ? G.ctl_m : G.ctl_t;
-    prof.begin(K_EVAL, stream);
-    if (variant >= 2) {
-      q.s0 = variant == 3 || G.div > 1 ? G.dsdt : nullptr;  // columns solved together: of the last one
-      launch_eval_linear<T>(q, stream);
-    } else {
-      launch_eval<T>(q, C, stream);
+    if (!fused) {
+      prof.begin(K_EVAL, stream);
+      if (variant >= 2) {
+        q.s0 = variant == 3 || G.div > 1 ? G.dsdt : nullptr;  // columns solved together: of the last one
+        launch_eval_linear<T>(q, stream);
+      } else {
+        launch_eval<T>(q, C, stream);
+      }
+      prof.end(stream);
     }
-    prof.end(stream);
-    prof.begin(basic ? K_XFWD : K_XMID, stream);
-    if (basic)
+    prof.begin(basic && !fused ? K_XFWD : K_XMID, stream);
+    if (fused)
+      run_xbasic<T>(a, stream);
+    else if (basic)
       run_xfwd<T>(a, stream);
     else
       run_xmid<T>(a, stream);
@@ -856,7 +867,7 @@ class BatchT : public BatchImpl {
       run_ypass<T>(a, G.txy[phys], 1, stream);
       prof.end(stream);
     }
-    if (!basic) return;
+    if (!basic || fused) return;
     prof.begin(K_XINV, stream);
     run_xinv<T>(a, stream);
     prof.end(stream);

@@ -56,3 +56,39 @@ def test_batch_of_large_planes_equals_single_cells(shape, count, precision):
             err = np.abs(r[i][k] - g[k]).max() / np.abs(g[k]).max()
             print(f"{shape} problem {i} precision {precision} {k}: {err:.2e}", flush=True)
             assert err <= 2 * TOL[precision]
+
+
+# The fixed-point scheme contracts by (k - 1) / (k + 1) for a stiffness contrast
+# k = 23: the strain is off by at most tol (k + 1) / 2 where it stops, the stress
+# by k times as much, relative to the effective one.
+BASIC = 23 * 12
+BASIC_TOL = {hom.FP64: 1e-10, hom.FP32: 1e-6}
+
+
+@pytest.mark.parametrize("precision", [hom.FP64, hom.FP32])
+@pytest.mark.parametrize("shape", [(16, 16, 16), (24, 16, 32), (16, 48, 64), (96, 16, 24), (128, 16, 16), (48, 48, 48),
+                                   (16, 16, 256)])
+def test_fixed_point_increment_matches_oracle(shape, precision):
+    """The x pass of the fixed-point scheme (plane pass and separate passes,
+    few and many lines): an increment with a temperature gradient, twice, alone
+    and in a batch whose problems end after different numbers of iterations."""
+    rng = np.random.default_rng(sum(shape) + 7 * precision)
+    img = (rng.random(shape) < 0.3).astype(np.uint8)
+    laws = [W.small_sphere_matrix(), W.small_sphere_inclusion()]
+    strain = np.array([4e-3, -1e-3, 2e-3, 1e-3, -2e-3, 3e-3])
+    grad = [1.0, -0.5, 0.25]
+    tol = BASIC_TOL[precision]
+    opts = dict(scheme=hom.SCHEME_BASIC, precision=precision, tol=tol)
+    o = solver.Cell(img, laws).solve_increment(strain, 323.0, grad, 2.0, tol=1e-11)
+    with hom.Context(img, laws, **opts) as ctx:
+        for _ in range(2):
+            g = ctx.solve_increment(strain, 323.0, grad, 2.0)
+            for k in ("stress", "heat_flux"):
+                err = np.abs(g[k] - o[k]).max() / np.abs(o[k]).max()
+                print(f"{shape} precision {precision} {k}: {err:.2e}", flush=True)
+                assert err <= BASIC * tol
+    with hom.Batch([img, np.zeros_like(img), img], laws, **opts) as b:
+        r = b.solve_increment([strain, strain, 3 * strain], [323.0] * 3, [grad] * 3, [2.0] * 3)
+    assert r[1]["newton_iters"] < r[0]["newton_iters"]
+    err = np.abs(r[0]["stress"] - o["stress"]).max() / np.abs(o["stress"]).max()
+    assert err <= BASIC * tol
