@@ -18,6 +18,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <future>
 #include <mutex>
 #include <random>
 #include <type_traits>
@@ -591,6 +592,19 @@ __global__ void k_split(const float* w, __bf16* hi, __bf16* lo, float* eff_bf, f
                         LayerSpans ls) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < count) split_weight(ls, w[i], i, hi, lo, eff_bf, eff_pr);
+}
+
+// Targets as the loss sees them, (t - mean) / std in FP64 (networks with a
+// skip subtract it on the host).
+struct TargetScale {
+  double mean[MLP_OUT], std[MLP_OUT];
+};
+__global__ void k_normalize_targets(const float* t, long long n, int n_out, TargetScale ts, float* out) {
+  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n * MLP_OUT) return;
+  const long long r = i / MLP_OUT;
+  const int j = (int)(i % MLP_OUT);
+  out[i] = j < n_out ? (float)(((double)t[r * n_out + j] - ts.mean[j]) / ts.std[j]) : 0.f;
 }
 
 // One training step's end: gradient from the partials, Adam, the weight
@@ -1193,25 +1207,55 @@ void Mlp::train(const float* X, const float* T, long long n, int epochs, int bat
     hipStream_t s;
     ~StreamGuard() { (void)hipStreamDestroy(s); }
   } sguard{s};
-  float *dX = nullptr, *dT = nullptr, *dW = nullptr;
-  int* didx = nullptr;
-  HIPCHK(hipMalloc((void**)&dX, n * n_in * 4));
-  HIPCHK(hipMalloc((void**)&dT, n * MLP_OUT * 4));
-  HIPCHK(hipMalloc((void**)&didx, n * 4));
-  if (row_weight) HIPCHK(hipMalloc((void**)&dW, n * 4));
+  // The first epoch's order is drawn while the rows are copied, the targets are
+  // normalized on the device and the arrays are one allocation: 16384 rows in two
+  // epochs of 4096 a batch 1.55 -> 1.38 ms (1 ms of it the steps' kernels).
+  std::mt19937_64 gen(seed);
+  std::vector<int> perm(n);
+  const auto draw_order = [&] {
+    for (long long i = 0; i < n; ++i) perm[i] = (int)i;
+    std::shuffle(perm.begin(), perm.end(), gen);
+  };
+  std::future<void> first_order;
+  if (epochs > 0) first_order = std::async(std::launch::async, draw_order);
+  // one allocation for the call's arrays: each one's bytes rounded up to 256
+  const auto bytes = [](long long b) { return (b + 255) / 256 * 256; };
+  const long long bx = bytes(n * n_in * 4), bt = bytes(n * MLP_OUT * 4), bi_ = bytes(n * 4),
+                  bw = row_weight ? bytes(n * 4) : 0, bl = bytes(std::max(epochs, 1) * (long long)sizeof(double));
+  const bool raw = hskip.empty();  // targets normalized on the device
+  const long long br = raw ? bytes(n * n_out * 4) : 0;
+  char* base = nullptr;
+  HIPCHK(hipMalloc((void**)&base, bx + bt + bi_ + bw + bl + br));
   struct Guard {  // destroyed before sguard: waits for the stream, then frees
     hipStream_t s;
-    std::vector<void*> p;
+    void* p;
     ~Guard() {
       (void)hipStreamSynchronize(s);
-      for (void* q : p)
-        if (q) (void)hipFree(q);
+      (void)hipFree(p);
     }
-  } guard{s, {dX, dT, didx, dW}};
-  std::vector<float> tn((size_t)n * MLP_OUT);
-  normalized_targets(X, T, n, tn.data());
+  } guard{s, base};
+  float* dX = reinterpret_cast<float*>(base);
+  float* dT = reinterpret_cast<float*>(base + bx);
+  int* didx = reinterpret_cast<int*>(base + bx + bt);
+  float* dW = row_weight ? reinterpret_cast<float*>(base + bx + bt + bi_) : nullptr;
+  double* dloss = reinterpret_cast<double*>(base + bx + bt + bi_ + bw);  // per-epoch loss sums
   HIPCHK(hipMemcpy(dX, X, n * n_in * 4, hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(dT, tn.data(), tn.size() * 4, hipMemcpyHostToDevice));
+  if (raw) {
+    float* draw = reinterpret_cast<float*>(base + bx + bt + bi_ + bw + bl);
+    HIPCHK(hipMemcpy(draw, T, n * n_out * 4, hipMemcpyHostToDevice));
+    TargetScale ts;
+    for (int j = 0; j < MLP_OUT; ++j) {
+      ts.mean[j] = j < n_out ? hy_mean[j] : 0.0;
+      ts.std[j] = j < n_out ? hy_std[j] : 1.0;
+    }
+    hipLaunchKernelGGL(k_normalize_targets, dim3((unsigned)((n * MLP_OUT + 255) / 256)), dim3(256), 0, s, draw, n,
+                       n_out, ts, dT);
+    HIPCHK(hipGetLastError());
+  } else {
+    std::vector<float> tn((size_t)n * MLP_OUT);
+    normalized_targets(X, T, n, tn.data());
+    HIPCHK(hipMemcpy(dT, tn.data(), tn.size() * 4, hipMemcpyHostToDevice));
+  }
   if (row_weight) {  // scaled to mean 1, so the learning rate keeps its meaning
     double sum = 0.0;
     for (long long r = 0; r < n; ++r) sum += row_weight[r];
@@ -1221,12 +1265,7 @@ void Mlp::train(const float* X, const float* T, long long n, int epochs, int bat
     HIPCHK(hipMemcpy(dW, rw.data(), n * 4, hipMemcpyHostToDevice));
   }
   ensure_work(batch);
-  std::mt19937_64 gen(seed);
-  std::vector<int> perm(n);
   const long long steps_per_epoch = n / batch;
-  double* dloss = nullptr;  // per-epoch loss sums on the device
-  HIPCHK(hipMalloc((void**)&dloss, std::max(epochs, 1) * sizeof(double)));
-  guard.p.push_back(dloss);
   HIPCHK(hipMemsetAsync(dloss, 0, std::max(epochs, 1) * sizeof(double), s));
   // the clears of freshly allocated work buffers ran on the null stream, which
   // this non-blocking stream does not wait for
@@ -1235,8 +1274,10 @@ void Mlp::train(const float* X, const float* T, long long n, int epochs, int bat
   long long step = 0;
   const float b1 = 0.9f, b2 = 0.999f;
   for (int e = 0; e < epochs; ++e) {
-    for (long long i = 0; i < n; ++i) perm[i] = (int)i;
-    std::shuffle(perm.begin(), perm.end(), gen);
+    if (e == 0)
+      first_order.get();
+    else
+      draw_order();
     HIPCHK(hipStreamSynchronize(s));  // the last epoch's gathers have read didx
     HIPCHK(hipMemcpy(didx, perm.data(), n * 4, hipMemcpyHostToDevice));
     for (long long sidx = 0; sidx < steps_per_epoch; ++sidx) {

@@ -205,3 +205,19 @@ def test_forward_rows_alike_on_both_sides_of_the_tile_rule(net_and_data, precise
     np.testing.assert_array_equal(net.forward(x[:n], precise=precise), full[:n])
     np.testing.assert_array_equal(net.forward(x[:n - 1], precise=precise), full[:n - 1])
     np.testing.assert_array_equal(net.forward(x[n - 30:], precise=precise), full[n - 30:])
+
+
+@pytest.mark.parametrize("rows,n_out", [(256, 10), (777, 3), (1000, 16)])
+def test_targets_normalized_on_the_device_and_on_the_host_are_the_same(rows, n_out):
+    """A network with a skip normalizes its targets on the host, one without on
+    the device: with a skip of zeros the same training, bit for bit."""
+    rng = np.random.default_rng(rows)
+    x = rng.normal(size=(rows, 6)).astype(np.float32)
+    y = (rng.normal(size=(rows, n_out)) * 10.0 ** rng.integers(-3, 4, n_out)).astype(np.float32)
+    nets = [hom.MLP(6, n_out, seed=4) for _ in range(2)]
+    for net in nets:
+        net.set_scaling(x.mean(0), x.std(0), y.mean(0), y.std(0))
+    nets[1].set_skip((0, 1, 2), np.zeros((n_out, 10, 6)), np.zeros(n_out))
+    losses = [net.train(x, y, epochs=2, batch=128, lr=2e-3, seed=5) for net in nets]
+    np.testing.assert_array_equal(losses[0], losses[1])
+    np.testing.assert_array_equal(nets[0].get_params(), nets[1].get_params())
