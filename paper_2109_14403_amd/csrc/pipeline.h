@@ -821,7 +821,8 @@ __global__ void __launch_bounds__((PlaneCfg<T, C, NY, NZ>::THREADS)) k_yzplane(P
   const int prob = blockIdx.x / bpp;
   const int kx = blockIdx.x - prob * bpp;
   Ctl& ctl = a.ctl[prob];
-  if (!pipeline_mode(ctl.mode)) return;
+  const int mode = ctl.mode;
+  if (!pipeline_mode(mode)) return;
   const int tid = threadIdx.x;
   double norm = 0.0;
   c2<T>* base = a.spec + ((long long)prob * P + min(kx, P - 1)) * (NY * NZ * C);
@@ -887,7 +888,9 @@ __global__ void __launch_bounds__((PlaneCfg<T, C, NY, NZ>::THREADS)) k_yzplane(P
       if (kx != 0 && 2 * kx != a.nx) norm *= 2.0;
     }
   }
-  if (drive) {
+  if (drive && mode == M_BASIC) {  // no norm and nothing to wait for (16^3 in FP64 6.3 us, 8.0 with the ticket)
+    if (kx == P) cg_step_length(a, prob);
+  } else if (drive) {
     if (kx == P) cg_step_length(a, prob);
     double s[1] = {norm};
     block_sum<1>(s, red);
@@ -1320,7 +1323,7 @@ __global__ void __launch_bounds__((x_threads<N, NL, C>()))
 // Bound like the middle pass above. In the place of the evaluation, a forward
 // pass, an inverse pass and a reduction kernel (the end of an iteration is found
 // by the next one's z or plane pass): elastic increments of 16^3 in FP64 3.54 ->
-// 2.51 ms, 32^3 FP64 5.56 -> 4.05, FP32 3.13 -> 2.18, 64^3 FP32 5.34 -> 4.00,
+// 2.16 ms, 32^3 FP64 5.56 -> 4.05, FP32 3.13 -> 2.18, 64^3 FP32 5.34 -> 4.00,
 // 128^3 FP32 16.2 -> 12.7 ms. Laws with internal variables keep the pointwise
 // evaluation: theirs takes 130 registers and reads the state.
 template <typename T, int C, int N, int NL>
