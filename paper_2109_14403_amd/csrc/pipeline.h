@@ -461,10 +461,10 @@ __device__ __forceinline__ void block_parts(const Pipe<T>& a, int prob, int q0, 
 }
 
 // End of a fixed-point iteration: |Gamma0 sigma|^2 against |x|^2 of the field it
-// gave. Called by one thread.
+// gave (not a number if either is). Called by one thread.
 __device__ __forceinline__ void basic_transition(Ctl& c, double dd, double xx, const Limits& lim) {
   c.pipelines += 1;
-  const double err = xx > 0.0 ? sqrt(dd / xx) : 0.0;
+  const double err = xx == 0.0 ? 0.0 : sqrt(dd / xx);
   c.res = err;
   c.newton_it += 1;
   if (!isfinite(err)) {
@@ -521,7 +521,7 @@ __device__ __forceinline__ void newton_cg_transition(Ctl& c, double vv, const Li
       c.pending = 1;
     }
   } else {
-    const double res = c.fnorm > 0.0 ? sqrt(vv) / c.fnorm : 0.0;
+    const double res = c.fnorm == 0.0 ? 0.0 : sqrt(vv) / c.fnorm;  // not a number if either is
     c.res = res;
     c.newton_it += 1;
     c.pending = 0;
