@@ -306,7 +306,6 @@ __device__ __forceinline__ void x_forward_lines(const Pipe<T>& a, int prob, int 
   const bool fw = tid < G * L;  // a thread of the line transforms
   const int l = tid % L;
   const int t = fw ? tid / L : 0;
-  __builtin_assume(t < G);
   c2<T> r[M];
 #pragma unroll
   for (int m = 0; m < M; ++m) r[m] = fw ? buf[l * SP + t + G * m] : mk(T(0), T(0));
@@ -580,9 +579,6 @@ __global__ void __launch_bounds__((N / Plan<N, V>::M) * TX * C) k_ypass(Pipe<T> 
   for (int i = tid; i < N; i += blockDim.x) tw[i] = a.twy[i];
   const int l = tid % L;
   const int t = tid / L;
-  // the launch has G * L threads: the twiddle indices below need no wrap (with
-  // the range lost, one instantiation mixed up two twiddle loads)
-  __builtin_assume(t < G);
   const int kx = kb * TX + l / C;
   const int c = l % C;
   const bool active = kx < P;
@@ -694,9 +690,6 @@ __global__ void __launch_bounds__((N / Plan<N, V>::M) * TX * C)
   for (int i = tid; i < N; i += nth) tw[i] = a.twz[i];
   const int l = tid % L;
   const int t = tid / L;
-  // the launch has G * L threads: the twiddle indices below need no wrap (with
-  // the range lost, one instantiation mixed up two twiddle loads)
-  __builtin_assume(t < G);
   const int kx = kb * TX + l / C;
   const int c = l % C;
   const bool active = kx < P;
@@ -789,7 +782,6 @@ struct PlaneCfg {
     const bool on = t < GY && l < LY;
     t = on ? t : 0;
     l = on ? l : 0;
-    __builtin_assume(t < GY);
     return on;
   }
   static __device__ __forceinline__ bool z_line(int tid, int i, int& t, int& l) {
@@ -798,7 +790,6 @@ struct PlaneCfg {
     const bool on = t < GZ && l < LZ;
     t = on ? t : 0;
     l = on ? l : 0;
-    __builtin_assume(t < GZ);
     return on;
   }
 };
@@ -1029,7 +1020,6 @@ __device__ __forceinline__ void x_inverse_lines(const Pipe<T>& a, int prob, int 
   const bool fw = NTH == G * L || tid < G * L;  // a thread of the line transforms
   const int l = tid % L;
   const int t = fw ? tid / L : 0;
-  __builtin_assume(t < G);
   const int li = l / NP;
   const int q = l - li * NP;
   c2<T> r[M];
