@@ -520,7 +520,10 @@ __device__ __forceinline__ void newton_cg_transition(Ctl& c, double vv, const Li
       c.pending = 1;
     }
   } else {
-    const double res = c.fnorm == 0.0 ? 0.0 : sqrt(vv) / c.fnorm;  // not a number if either is
+    // relative to the stress field; while that is zero, a prescribed mean stress
+    // is all the residual there is: relative to itself (not a number if either is)
+    const double rn = sqrt(vv), fn = c.fnorm == 0.0 ? rn : c.fnorm;
+    const double res = fn == 0.0 ? 0.0 : rn / fn;
     c.res = res;
     c.newton_it += 1;
     c.pending = 0;
@@ -535,7 +538,7 @@ __device__ __forceinline__ void newton_cg_transition(Ctl& c, double vv, const Li
       c.status = -3;
     } else {
       const double eta = lim.linear ? 0.0 : fmin(0.1, res);
-      const double tgt = fmax(eta * sqrt(vv), 0.5 * lim.tol * c.fnorm);
+      const double tgt = fmax(eta * rn, 0.5 * lim.tol * fn);
       c.cg_target = tgt * tgt;
       c.cg_it = 0;
       c.beta = 0.0;
