@@ -103,7 +103,8 @@ typedef struct {
                           voxels in a group and for conduction, else 16) */
   int32_t use_graph;   /* 1: replay chunks as captured hipGraphs */
   int32_t profile;     /* 1: time every kernel launch with HIP events */
-  int32_t autotune;    /* 1: time the tile choices of the y/z passes at setup */
+  int32_t autotune;    /* 1: time the tile choices of the y/z passes at setup (groups whose planes are
+                          transformed in one pass have none, see hom_batch_schedules) */
   void* stream;        /* hipStream_t to run on; NULL => a stream owned by the context */
   int32_t tangent;     /* 1: keep the per-voxel partials of each converged increment that the
                           temperature and coupling tangents need (hom_algorithmic_tangent,
@@ -284,7 +285,12 @@ int hom_batch_kernel_stats(const hom_batch* b, const char** names, int64_t* laun
  * tile width (kx columns per work-group: 2, 4 or 8) + 16 x FFT plan variant
  * (0 or 1). Writes at most cap groups into out (7 cap values); returns the
  * number of groups, or a negative error code. hom_schedules: the same for a
- * single-problem context. */
+ * single-problem context.
+ * Where a whole plane ny x nz of one kx fits into LDS the y and z transforms
+ * are one pass without such choices (at most 104 KB of 6 (ny + 1) nz complex
+ * values in FP32 and 64 KB in FP64; up to 120 KB if the group has at least 128
+ * planes, n_prob (nx / 2 + 1)). Such a group is not tuned and reports width 4,
+ * plan 0, which it does not run. */
 int hom_batch_schedules(const hom_batch* b, int32_t* out, int32_t cap);
 int hom_schedules(const hom_ctx* ctx, int32_t* out, int32_t cap);
 /* hom_algorithmic_tangent for every problem of a batch; out: n_prob entries. */

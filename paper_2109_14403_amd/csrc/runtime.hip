@@ -725,8 +725,29 @@ class BatchT : public BatchImpl {
     HIPCHK(hipDeviceSynchronize());
   }
 
-  // time the y / z schedules (tile width and FFT plan) on this group's data
-  // and keep the fastest
+  // The y and z passes drive the solver's state, with the partial sums that
+  // takes: all but the fixed-point scheme of laws with internal variables.
+  bool drives_state(const Group<T>& G, int phys) const {
+    return opts.scheme != HOM_SCHEME_BASIC || phys == 1 || !G.state;
+  }
+  // Arguments of the pipeline passes as an iteration runs them.
+  Pipe<T> pass_args(const Group<T>& G, int phys, const Limits& lim) const {
+    const bool basic = opts.scheme == HOM_SCHEME_BASIC, rot = opts.discretization == HOM_DISC_ROTATED;
+    const int green = phys == 0 ? (basic ? G_GAMMA0 : (rot ? G_PROJ_ROT : G_PROJ))
+                                : (basic ? G_GAMMA_TH : (rot ? G_GRADPROJ_ROT : G_GRADPROJ));
+    Pipe<T> a = G.pipe(phys, green);
+    if (drives_state(G, phys)) {
+      a.xblocks = G.xmblocks;
+      const int tx = schedule_tile(G.txz[phys]);
+      a.zblocks = G.ny * ((G.P + tx - 1) / tx);
+      a.lim = lim;
+    }
+    return a;
+  }
+
+  // time the y / z schedules (tile width and FFT plan) of the passes as an
+  // iteration runs them (of a residual evaluation, which moves no state before
+  // the inverse y pass) on this group's data and keep the fastest
   void autotune(Group<T>& G) {
     hipStream_t stream = G.stream;  // this group's lane
     hipEvent_t e0, e1;
@@ -740,7 +761,7 @@ class BatchT : public BatchImpl {
     for (int phys = 0; phys < 2; ++phys) {
       Ctl* ctl = phys == 0 ? G.ctl_m : G.ctl_t;
       HIPCHK(hipMemcpy(ctl, c.data(), sizeof(Ctl) * G.nprob, hipMemcpyHostToDevice));
-      Pipe<T> a = G.pipe(phys, phys == 0 ? G_PROJ : G_GRADPROJ);
+      const Pipe<T> a = pass_args(G, phys, limits(phys));
       for (int pass = 0; pass < 2; ++pass) {
         auto run = [&](int sc) { pass == 0 ? run_ypass<T>(a, sc, 0, stream) : run_zgreen<T>(a, sc, stream); };
         std::vector<int> cand;
@@ -817,22 +838,13 @@ class BatchT : public BatchImpl {
   void iteration(Group<T>& G, int variant, bool basic) {
     hipStream_t stream = G.stream;  // this group's lane
     const int phys = variant == 1 ? 1 : 0;
-    const bool rot = opts.discretization == HOM_DISC_ROTATED;
-    const int green = phys == 0 ? (basic ? G_GAMMA0 : (rot ? G_PROJ_ROT : G_PROJ))
-                                : (basic ? G_GAMMA_TH : (rot ? G_GRADPROJ_ROT : G_GRADPROJ));
-    Pipe<T> a = G.pipe(phys, green);
     Pt<T> q = G.pt(phys);
     const int C = phys == 0 ? 6 : 3;
     Limits lim = limits(phys);
     if (variant >= 2) lim.linear = 1;
+    const Pipe<T> a = pass_args(G, phys, lim);
     // fixed point without internal variables: one x pass an iteration
-    const bool fused = basic && (phys == 1 || !G.state);
-    if (!basic || fused) {  // the y and z passes drive the solver's state
-      a.xblocks = G.xmblocks;
-      const int tx = schedule_tile(G.txz[phys]);
-      a.zblocks = G.ny * ((G.P + tx - 1) / tx);
-      a.lim = lim;
-    }
+    const bool fused = basic && drives_state(G, phys);
     Ctl* ctl = phys == 0 ? G.ctl_m : G.ctl_t;
     if (!fused) {
       prof.begin(K_EVAL, stream);

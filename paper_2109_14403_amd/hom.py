@@ -549,7 +549,8 @@ class Context(_Handle):
         return _stats(self._lib.hom_kernel_stats, self._h)
 
     def schedules(self):
-        """The y / z pass schedules (tile width, FFT plan) the autotuner chose."""
+        """The y / z pass schedules (tile width, FFT plan) the autotuner chose
+        (the default where planes are transformed in one pass, which has none)."""
         return _schedules(self._lib.hom_schedules, self._h)
 
     def set_profiling(self, on: bool):
@@ -650,7 +651,8 @@ class Batch(_Handle):
         return _stats(self._lib.hom_batch_kernel_stats, self._h)
 
     def schedules(self):
-        """The y / z pass schedules (tile width, FFT plan) per grid group."""
+        """The y / z pass schedules (tile width, FFT plan) per grid group (the
+        default where planes are transformed in one pass, which has none)."""
         return _schedules(self._lib.hom_batch_schedules, self._h)
 
 
