@@ -707,41 +707,16 @@ Mlp::Mlp(int n_in_, int n_out_, uint64_t seed) : n_in(n_in_), n_out(n_out_) {
   alloc((void**)&scal, 5 * MLP_OUT * 4 + 2 * MLP_IN * 4);
   // G and c in FP32, then G's bf16 hi and lo parts
   alloc((void**)&skip, (MLP_OUT * MLP_GATES * MLP_IN + MLP_OUT) * 4 + 2 * MLP_OUT * MLP_GATES * MLP_IN * 2);
-  // He initialization (normal, std sqrt(2 / fan_in)), seeded; biases zero.
-  // Marsaglia's polar method on 64-bit draws scaled to [0, 1): the numbers of
-  // std::normal_distribution, which forms logarithms of the generator's range
-  // on every draw (two thirds of the time to set up a network).
+  // He initialization (normal, std sqrt(2 / fan_in)), seeded; biases zero
   std::vector<float> hw(npad, 0.f);
   std::mt19937_64 gen(seed);
-  const auto uniform = [&] { return std::min((double)gen() * 0x1p-64, 1.0 - 0x1p-53); };
-  struct {
-    bool have = false;
-    double saved = 0.0;
-  } polar;
-  const auto normal = [&](double sd) {
-    if (polar.have) {
-      polar.have = false;
-      return polar.saved * sd;
-    }
-    double x, y, r2;
-    do {
-      x = 2.0 * uniform() - 1.0;
-      y = 2.0 * uniform() - 1.0;
-      r2 = x * x + y * y;
-    } while (r2 > 1.0 || r2 == 0.0);
-    const double mult = std::sqrt(-2.0 * std::log(r2) / r2);
-    polar.saved = x * mult;
-    polar.have = true;
-    return y * mult * sd;
-  };
   for (int l = 0; l < MLP_LAYERS; ++l) {
     const int K = lay_k(l), N = lay_n(l);
     const int kin = l == 0 ? n_in : K;
     const int nout = l == MLP_LAYERS - 1 ? n_out : N;
-    const double sd = std::sqrt((l == MLP_LAYERS - 1 ? 1.0 : 2.0) / kin);
-    polar.have = false;
+    std::normal_distribution<double> nd(0.0, std::sqrt((l == MLP_LAYERS - 1 ? 1.0 : 2.0) / kin));
     for (int i = 0; i < nout; ++i)
-      for (int k = 0; k < kin; ++k) hw[woff[l] + (size_t)i * K + k] = (float)normal(sd);
+      for (int k = 0; k < kin; ++k) hw[woff[l] + (size_t)i * K + k] = (float)nd(gen);
   }
   HIPCHK(hipMemcpy(w, hw.data(), npad * 4, hipMemcpyHostToDevice));
   std::vector<float> s(5 * MLP_OUT + 2 * MLP_IN, 0.f);

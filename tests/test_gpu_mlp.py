@@ -221,3 +221,15 @@ def test_targets_normalized_on_the_device_and_on_the_host_are_the_same(rows, n_o
     losses = [net.train(x, y, epochs=2, batch=128, lr=2e-3, seed=5) for net in nets]
     np.testing.assert_array_equal(losses[0], losses[1])
     np.testing.assert_array_equal(nets[0].get_params(), nets[1].get_params())
+
+
+def test_initial_network_of_a_seed():
+    """The initial weights are the draws of std::normal_distribution on
+    std::mt19937_64(seed), layer by layer (first two and last weight of each
+    layer, from a host program that calls the two)."""
+    draws = [(0.259052932, -0.316714764, 0.303462267), (-0.100153431, -0.183836535, 0.0187645033),
+             (0.0159088224, 0.00444698241, -0.196138665), (0.0302440617, 0.0436188132, 0.0804008171),
+             (0.0257088933, -0.0477711968, -0.0274669509)]
+    for (w, b), d in zip(hom.MLP(7, 3, seed=11).layers(), draws):
+        np.testing.assert_array_equal(np.concatenate([w.ravel()[:2], w.ravel()[-1:]]), np.float32(d))
+        assert not b.any()
