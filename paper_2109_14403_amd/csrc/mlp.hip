@@ -1215,17 +1215,9 @@ void Mlp::train(const float* X, const float* T, long long n, int epochs, int bat
   float* dW = row_weight ? reinterpret_cast<float*>(base + bx + bt + bi_) : nullptr;
   double* dloss = reinterpret_cast<double*>(base + bx + bt + bi_ + bw);  // per-epoch loss sums
   HIPCHK(hipMemcpy(dX, X, n * n_in * 4, hipMemcpyHostToDevice));
+  float* draw = reinterpret_cast<float*>(base + bx + bt + bi_ + bw + bl);  // raw targets
   if (raw) {
-    float* draw = reinterpret_cast<float*>(base + bx + bt + bi_ + bw + bl);
     HIPCHK(hipMemcpy(draw, T, n * n_out * 4, hipMemcpyHostToDevice));
-    TargetScale ts;
-    for (int j = 0; j < MLP_OUT; ++j) {
-      ts.mean[j] = j < n_out ? hy_mean[j] : 0.0;
-      ts.std[j] = j < n_out ? hy_std[j] : 1.0;
-    }
-    hipLaunchKernelGGL(k_normalize_targets, dim3((unsigned)((n * MLP_OUT + 255) / 256)), dim3(256), 0, s, draw, n,
-                       n_out, ts, dT);
-    HIPCHK(hipGetLastError());
   } else {
     std::vector<float> tn((size_t)n * MLP_OUT);
     normalized_targets(X, T, n, tn.data());
@@ -1242,9 +1234,19 @@ void Mlp::train(const float* X, const float* T, long long n, int epochs, int bat
   ensure_work(batch);
   const long long steps_per_epoch = n / batch;
   HIPCHK(hipMemsetAsync(dloss, 0, std::max(epochs, 1) * sizeof(double), s));
-  // the clears of freshly allocated work buffers ran on the null stream, which
-  // this non-blocking stream does not wait for
+  // the copies went over the null stream, which this non-blocking stream does
+  // not wait for
   HIPCHK(hipStreamSynchronize(nullptr));
+  if (raw) {
+    TargetScale ts;
+    for (int j = 0; j < MLP_OUT; ++j) {
+      ts.mean[j] = j < n_out ? hy_mean[j] : 0.0;
+      ts.std[j] = j < n_out ? hy_std[j] : 1.0;
+    }
+    hipLaunchKernelGGL(k_normalize_targets, dim3((unsigned)((n * MLP_OUT + 255) / 256)), dim3(256), 0, s, draw, n,
+                       n_out, ts, dT);
+    HIPCHK(hipGetLastError());
+  }
   const long long total = steps_per_epoch * epochs;
   long long step = 0;
   const float b1 = 0.9f, b2 = 0.999f;
@@ -1255,6 +1257,7 @@ void Mlp::train(const float* X, const float* T, long long n, int epochs, int bat
       draw_order();
     HIPCHK(hipStreamSynchronize(s));  // the last epoch's gathers have read didx
     HIPCHK(hipMemcpy(didx, perm.data(), n * 4, hipMemcpyHostToDevice));
+    HIPCHK(hipStreamSynchronize(nullptr));  // ... and the new order is there before the next ones
     for (long long sidx = 0; sidx < steps_per_epoch; ++sidx) {
       const int* bi = didx + sidx * batch;
       const int lb = grad_partials(dX, dT, batch, false, s, dW, bi);
