@@ -233,3 +233,11 @@ def test_initial_network_of_a_seed():
     for (w, b), d in zip(hom.MLP(7, 3, seed=11).layers(), draws):
         np.testing.assert_array_equal(np.concatenate([w.ravel()[:2], w.ravel()[-1:]]), np.float32(d))
         assert not b.any()
+
+
+@pytest.mark.parametrize("rows", [16383, 16384, 20001])
+def test_gradients_of_large_batches(rows):
+    """Both sides of the row rule of the forward pass that keeps activations (16
+    and 64 rows a work-group), and the batch in 64 splits of more than 256
+    rows, the last one shorter. Bounds of the smaller batches above."""
+    test_gradients_at_batch_edges(rows)
