@@ -320,7 +320,6 @@ struct Group {
   // tangents and partials
   std::unique_ptr<Group<T>> columns;
   bool columns_failed = false;  // no memory for it: one column after the other
-  const Group<T>* base = nullptr;
   int div = 1;
   ProbInc* inc_pm_d = nullptr;
   ProbInc* inc_pm_h = nullptr;
@@ -427,7 +426,6 @@ struct Group {
   // Iteration fields for ncol linearized solves a problem of b, with b's
   // grid, phases, tangents and schedules.
   void alloc_columns(const Group<T>& b, int ncol) {
-    base = &b;
     div = ncol;
     nx = b.nx;
     ny = b.ny;
@@ -1253,10 +1251,12 @@ class BatchT : public BatchImpl {
   // the cell's phases and tangents read by all of them. Measured, one column
   // after the other against all together (an increment and its tangents,
   // 7 columns; a stiffness sample, 6): 16^3 FP32 12.0 -> 3.6 ms, 32^3 18.8 -> 6.0,
-  // 48^3 24.5 -> 10.5, 64^3 37.0 -> 21.1, 24^3 FP64 23.2 -> 6.2; sample at 32^3
-  // 12.6 -> 3.1, 64^3 23.2 -> 13.3, 96^3 57.7 -> 40.1, 128^3 112 -> 103 ms. Above
-  // that the passes fill the memory system by themselves, and seven sets of
-  // iteration fields (0.8 KB a voxel in FP32) are not worth it.
+  // 48^3 24.5 -> 10.5, 64^3 37.0 -> 21.1, 24^3 FP64 23.2 -> 6.2. Above 2^21 voxels
+  // the passes fill the memory system by themselves and seven sets of fields
+  // only spread it: the six columns of d sigma / d E at 128^3 FP32 55.3 -> 50.2 ms
+  // and FP64 105.3 -> 104.4, but 256 x 128 x 128 98.2 -> 100.1, 128 x 256 x 256
+  // 193 -> 218, 256^3 397 -> 427. The fields (0.85 KB a voxel in FP32, 1.7 KB in
+  // FP64) are kept for later calls.
   static constexpr int kColumns = 7;
   static constexpr long long kColumnVoxels = 1LL << 21;  // of a group, up to which they do
   bool columns_together(Group<T>& G) {
@@ -1266,6 +1266,8 @@ class BatchT : public BatchImpl {
       G.columns.reset(new Group<T>());
       G.columns->alloc_columns(G, kColumns);
       check_tiles(*G.columns, 0);
+      // predictor: warm starts (one column after the other needs less memory in all)
+      if (G.dx && !G.tcol) G.tcol = G.template dalloc<T>(kColumns * 6 * (size_t)G.nprob * G.vs);
       HIPCHK(hipStreamSynchronize(nullptr));  // the clears, which the lane's stream does not wait for
     } catch (const Error& e) {
       G.columns.reset();
@@ -1288,10 +1290,6 @@ class BatchT : public BatchImpl {
     lim.linear = 1;
     Pt<T> q = L.pt(0);
     q.ncol = ncol;
-    if (G.dx && !G.tcol) {  // predictor: warm starts
-      G.tcol = G.template dalloc<T>(kColumns * field * G.nprob);
-      HIPCHK(hipStreamSynchronize(nullptr));
-    }
     q.x0 = G.tcol;
     for (int c = 0; c < ncol; ++c) q.x0_ok |= G.tcol && G.tcol_ok[c] ? 1 << c : 0;
     for (int j = 0; j < G.nprob; ++j) {
@@ -1362,18 +1360,17 @@ class BatchT : public BatchImpl {
     }
     const double sq2 = std::sqrt(2.0);
     const double w[6] = {1, 1, 1, sq2, sq2, sq2};
-    const bool prof_on = prof.on;
-    prof.on = false;
+    struct ProfilerOff {  // until the call returns, however it does
+      bool& on;
+      const bool was;
+      explicit ProfilerOff(bool& b) : on(b), was(b) { on = false; }
+      ~ProfilerOff() { on = was; }
+    } off(prof.on);
     for (auto& gp : groups) {
       Group<T>& G = *gp;
       hipStream_t stream = G.stream;  // this group's lane
       if (columns_together(G)) {
-        try {
-          tangent_columns(G, what, out);
-        } catch (...) {
-          prof.on = prof_on;
-          throw;
-        }
+        tangent_columns(G, what, out);
         continue;
       }
       const size_t nm = (size_t)G.nprob * G.vs;
@@ -1438,13 +1435,11 @@ class BatchT : public BatchImpl {
         }
       } catch (...) {
         restore();
-        prof.on = prof_on;
         throw;
       }
       restore();
       HIPCHK(hipGetLastError());
     }
-    prof.on = prof_on;
   }
 
   // ---- checkpoint: xn, xt, state, macro history -------------------------
