@@ -150,3 +150,30 @@ def test_predictor_under_mixed_conditions_and_adiabatic_balance():
     it = [sum(r["newton_iters"] + r["krylov_iters"] for r in out[1:]) for out in runs]
     print(f"mixed adiabatic increments 2..5: iterations {it[0]} -> {it[1]}", flush=True)
     assert it[1] < it[0]
+
+
+def test_batch_tangents_with_warm_starts():
+    """The columns of a batch's tangents start from their own problem's last
+    solutions: six columns, then seven, at two increments with loads of their
+    own, equal the single problems' (same iterates, other sums: 1e-9)."""
+    rng = np.random.default_rng(12)
+    imgs = [(rng.random((16, 16, 16)) < 0.3).astype(np.uint8) for _ in range(3)]
+    laws = [W.pa66(), W.e_glass()]
+    opts = dict(precision=hom.FP64, tol=1e-10, predictor=1, tangent=1)
+    strain = rng.normal(size=(3, 6)) * 4e-3
+    args = lambda k, i: (k * strain[i], 300.0 + 5 * i, [1.0, 0.0, -0.5 * i], 1.0 + i)
+    with hom.Batch(imgs, laws, **opts) as b:
+        many = []
+        for k in (1, 2, 3):
+            b.solve_increment(*map(list, zip(*[args(k, i) for i in range(3)])))
+            many.append([b.algorithmic_tangent(what=w) for w in (0, 1)])
+    for i, img in enumerate(imgs):
+        with hom.Context(img, laws, **opts) as ctx:
+            for k in (1, 2, 3):
+                ctx.solve_increment(*args(k, i))
+                for w in (0, 1):
+                    one, got = ctx.algorithmic_tangent(what=w), many[k - 1][w][i]
+                    for key in ("dsde",) + (("dsdt", "dDde", "dDdt") if w else ()):
+                        x, y = np.asarray(got[key]), np.asarray(one[key])
+                        assert np.abs(x - y).max() <= 1e-9 * np.abs(y).max(), (i, k, w, key)
+                    assert abs(got["krylov_iters"] - one["krylov_iters"]) <= one["solves"]
