@@ -37,14 +37,16 @@ enum Mode : int { M_DONE = 0, M_EVAL = 1, M_CG = 2, M_BASIC = 3, M_FAIL = -1 };
 enum Green : int { G_PROJ = 0, G_GAMMA0 = 1, G_GRADPROJ = 2, G_GAMMA_TH = 3, G_PROJ_ROT = 4, G_GRADPROJ_ROT = 5 };
 enum LawKind : int { LAW_TE = 1, LAW_PA66 = 2 };
 
-// Per-problem solver control, owned by the device. The reduce kernels are
-// the only writers of mode transitions.
+// Per-problem solver control, owned by the device. The y and z passes (or the
+// plane pass) move the state of a Newton-CG solve and of a fixed-point solve
+// without internal variables, the reduce kernel that of any other.
 struct Ctl {
   int mode;
   int newton_it;    // residual evaluations done (Newton) / iterations (basic)
   int cg_it;        // CG iterations in the current Newton step
   int cg_bad;       // p . C p of the current CG iteration is not positive and finite
-  int pending;      // x += dx before the next evaluation
+  int pending;      // Newton-CG: x += alpha p before the next evaluation; fixed point in one x
+                    // pass: an application of the operator waits in the spectrum
   int status;       // 0 running, 1 converged, <0 failure code
   int pipelines;    // FFT pipeline applications so far
   int krylov;       // total CG iterations

@@ -26,11 +26,16 @@
 // Newton step is decided by the true residual of its evaluation (|r| by
 // Parseval's theorem, |sigma| from the x pass).
 //
-// The fixed-point scheme has no such recurrence and takes
-//   xfwd   forward transforms along x of the stress / flux field,
-//   xinv   complex-to-real inverse along x, scaled by 1/(nx ny nz), the
-//          update of the strain and FP64 partial sums for the reductions,
-// around the same y and z passes.
+// The fixed-point scheme has no such recurrence. Without internal variables (and
+// for conduction) it takes
+//   xbasic  inverse transforms along x, the update of the strain, the law and
+//           the forward transforms, with the sums that end the iteration before:
+//           the z or plane pass behind it moves the solver's state;
+// with them, around the same y and z passes,
+//   xfwd    forward transforms along x of the stress field,
+//   xinv    complex-to-real inverse along x, scaled by 1/(nx ny nz), the update
+//           of the strain and FP64 partial sums for the reduction that ends the
+//           iteration.
 //
 // CG keeps three fields (x, r, p): the step x += alpha p of iteration k is
 // deferred to the x pass of iteration k + 1 (or to the next constitutive
@@ -1098,7 +1103,7 @@ __global__ void __launch_bounds__((x_threads<N, NL, C>())) k_xinv(Pipe<T> a) {
       }
       T* o = at(db + c * nv, v);
       T out[4];
-      if (mode == M_EVAL) {  // residual field r = -Gamma sigma; norms of r and sigma
+      if (mode == M_EVAL) {  // a single application of the operator: r = -Gamma f
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           out[j] = -g[j];

@@ -817,7 +817,8 @@ class BatchT : public BatchImpl {
     LaunchInfo li = run_xinv<T>(a, stream, true);
     LaunchInfo lm = run_xmid<T>(a, stream, true);
     LaunchInfo lb = run_xbasic<T>(a, stream, true);
-    if (!launch_ok(lb) || !launch_ok(lx) || !launch_ok(li) || !launch_ok(lm)) fail(HOM_E_UNSUPPORTED, "x-pass does not fit the work-group limits");
+    if (!launch_ok(lb) || !launch_ok(lx) || !launch_ok(li) || !launch_ok(lm))
+      fail(HOM_E_UNSUPPORTED, "x-pass does not fit the work-group limits");
   }
 
   Limits limits(int phys) const {
