@@ -600,11 +600,13 @@ struct TargetScale {
   double mean[MLP_OUT], std[MLP_OUT];
 };
 __global__ void k_normalize_targets(const float* t, long long n, int n_out, TargetScale ts, float* out) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n * MLP_OUT) return;
-  const long long r = i / MLP_OUT;
-  const int j = (int)(i % MLP_OUT);
-  out[i] = j < n_out ? (float)(((double)t[r * n_out + j] - ts.mean[j]) / ts.std[j]) : 0.f;
+  // a launch has fewer than 2^32 threads, a training set may have more values
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n * MLP_OUT;
+       i += (long long)gridDim.x * blockDim.x) {
+    const long long r = i / MLP_OUT;
+    const int j = (int)(i % MLP_OUT);
+    out[i] = j < n_out ? (float)(((double)t[r * n_out + j] - ts.mean[j]) / ts.std[j]) : 0.f;
+  }
 }
 
 // One training step's end: gradient from the partials, Adam, the weight
@@ -1243,8 +1245,8 @@ void Mlp::train(const float* X, const float* T, long long n, int epochs, int bat
       ts.mean[j] = j < n_out ? hy_mean[j] : 0.0;
       ts.std[j] = j < n_out ? hy_std[j] : 1.0;
     }
-    hipLaunchKernelGGL(k_normalize_targets, dim3((unsigned)((n * MLP_OUT + 255) / 256)), dim3(256), 0, s, draw, n,
-                       n_out, ts, dT);
+    const unsigned blocks = (unsigned)std::min<long long>((n * MLP_OUT + 255) / 256, 1 << 16);
+    hipLaunchKernelGGL(k_normalize_targets, dim3(blocks), dim3(256), 0, s, draw, n, n_out, ts, dT);
     HIPCHK(hipGetLastError());
   }
   const long long total = steps_per_epoch * epochs;

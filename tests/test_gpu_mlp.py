@@ -241,3 +241,15 @@ def test_gradients_of_large_batches(rows):
     and 64 rows a work-group), and the batch in 64 splits of more than 256
     rows, the last one shorter. Bounds of the smaller batches above."""
     test_gradients_at_batch_edges(rows)
+
+
+def test_targets_of_more_values_than_a_launch_has_threads():
+    """2^28 rows and a few have more than 2^32 padded targets: training takes them.
+    Every row is the same and the steps are too small to change a weight: an epoch
+    has the loss of one batch."""
+    rows, batch = 2**28 + 5, 2**20
+    x = np.full((rows, 1), 0.5, np.float32)
+    net, few = hom.MLP(1, 1, seed=1), hom.MLP(1, 1, seed=1)
+    (loss,) = net.train(x, x, epochs=1, batch=batch, lr=1e-30, seed=0)
+    (first,) = few.train(x[:batch], x[:batch], epochs=1, batch=batch, lr=1e-30, seed=0)
+    assert loss == pytest.approx(first, rel=1e-6)
