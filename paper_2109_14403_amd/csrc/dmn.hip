@@ -306,6 +306,7 @@ struct OffArgs {
   const double* C1;    // [S][36]
   const double* C2;
   const double* Cb;    // [S][36] targets, or null
+  int first;           // number of the launch's first block
   const int* idx;      // [B] sample of each block, or null (block = sample)
   double* Cnode;       // [B][nleaf][36] (heap index 1 .. nleaf - 1) of trees that do not fit into LDS
   double* D;           // [B][36] prediction, or null
@@ -332,9 +333,10 @@ __global__ void __launch_bounds__(OFF_THREADS) k_dmn_sample(OffArgs a) {
   double* wsub = reinterpret_cast<double*>(smem_raw);  // subtree weights, heap order
   double* wbar = wsub + 2 * a.nleaf;
   double* scr = wbar + 2 * a.nleaf + (threadIdx.x >> 3) * SCR8;
-  double* node = NODES ? wbar + 2 * a.nleaf + (OFF_THREADS / 8) * SCR8 : a.Cnode + (long long)blockIdx.x * a.nleaf * 36;
+  double* node = NODES ? wbar + 2 * a.nleaf + (OFF_THREADS / 8) * SCR8
+                       : a.Cnode + (long long)(a.first + blockIdx.x) * a.nleaf * 36;
   __shared__ double den_s, err_s;
-  const int s = blockIdx.x;
+  const int s = a.first + blockIdx.x;
   const int sample = a.idx ? a.idx[s] : s;
   const int nleaf = a.nleaf;
   const int tid = threadIdx.x, nth = blockDim.x;
@@ -487,20 +489,26 @@ U* dalloc_into(std::vector<void*>& allocs, size_t count) {
   return static_cast<U*>(ptr);
 }
 
-void launch_samples(const OffArgs& a, int B, hipStream_t stream) {
+// One launch, or several where one would have 2^32 threads or more (from 2^23
+// samples of depth 7 on), which a launch does not run.
+void launch_samples(OffArgs a, int B, hipStream_t stream) {
   const int threads = std::min(OFF_THREADS, std::max(64, 4 * a.nleaf));  // eight lanes a laminate
   const bool nodes = a.K <= OFF_LDS_K;
   const size_t lds = off_lds(a.nleaf, nodes);
-  if (nodes) {
-    if (lds > 65536)
-      hip_check(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dmn_sample<true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
-                "hipFuncSetAttribute");
-    hipLaunchKernelGGL(k_dmn_sample<true>, dim3(B), dim3(threads), lds, stream, a);
-  } else {
-    hipLaunchKernelGGL(k_dmn_sample<false>, dim3(B), dim3(threads), lds, stream, a);
+  if (nodes && lds > 65536)
+    hip_check(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dmn_sample<true>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
+              "hipFuncSetAttribute");
+  constexpr int kMost = 1 << 22;
+  for (a.first = 0;; a.first += kMost) {
+    const dim3 groups(std::min(B - a.first, kMost));
+    if (nodes)
+      hipLaunchKernelGGL(k_dmn_sample<true>, groups, dim3(threads), lds, stream, a);
+    else
+      hipLaunchKernelGGL(k_dmn_sample<false>, groups, dim3(threads), lds, stream, a);
+    hip_check(hipGetLastError(), "k_dmn_sample");
+    if (B - a.first <= kMost) return;
   }
-  hip_check(hipGetLastError(), "k_dmn_sample");
 }
 // node stiffnesses in memory, for the trees that do not fit into LDS
 size_t node_doubles(int K, long long B) { return K <= OFF_LDS_K ? 1 : (size_t)B * ((size_t)1 << K) * 36; }

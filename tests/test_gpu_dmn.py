@@ -378,3 +378,16 @@ def test_online_for_each_phase_and_depth(K, law1, law2):
         assert np.abs(g["dDde"] - o["dDde"] * WM).max() <= 1e-6 * np.abs(o["dDde"]).max()
         assert abs(g["dDdt"] - o["dDdt"]) <= 1e-6 * abs(o["dDdt"])
     gpu.close()
+
+
+def test_more_samples_than_a_launch_has_work_groups_for():
+    """Depth 7 takes 512 threads a sample: from 2^23 samples on one launch would
+    have 2^32 threads. Every sample's stiffness is that of the sample alone."""
+    n, few = 2**23 + 3, 64
+    C1, C2 = samples(few, np.random.default_rng(2))
+    net = hom.Dmn(7, seed=3)
+    ref = net.homogenize(C1, C2)
+    got = net.homogenize(np.resize(C1, (n, 6, 6)), np.resize(C2, (n, 6, 6)))
+    for lo in (0, 2**22 - few, 2**22, 2**23 - few):  # ends of the launches, in whole rounds of the few
+        assert np.array_equal(got[lo:lo + few], ref), lo
+    assert np.array_equal(got[2**23:], ref[:3])
