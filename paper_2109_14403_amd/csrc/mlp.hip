@@ -40,11 +40,15 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
 constexpr int FWD_WAVES = 8;          // waves per forward work-group
-// Rows (over all networks) of a forward launch from which a work-group takes 64
-// of them; below, 16, so that more CUs have one. Both sides: 4096 rows of two
-// networks 21 us with 16 and 29 us with 64, 3072 of four 31 and 37; 8192 of two
-// 32 and 30, 4096 of eight 70 and 57. A row's result does not depend on the choice.
-constexpr long long kFullRows = 64 * 256;
+// Work-groups of 16 rows (over all networks) up to which a forward launch takes
+// them, so that more CUs have one; beyond, 64 rows each. The line lies where a
+// CU would get one more round of small ones: three a CU fit beside each other
+// (12288 rows 20.4 us with 16 rows and 22.9 with 64, 13312 rows 25.7 and 22.9;
+// of eight networks 38.6 and 42.1, 43.8 and 42.8), in precise mode two (8192
+// rows 20.2 and 27.1, 10240 rows 27.0 and 27.1, 12288 rows 28.6 and 27.2). Rows
+// for another round of large ones make no second line: 20480 rows 31.9 and 36.2,
+// but 24576 37.5 and 37.1. A row's result does not depend on the choice.
+constexpr long long few_groups(bool precise) { return precise ? 640 : 768; }
 constexpr int NCB = MLP_W / (16 * FWD_WAVES);  // 16-column tiles per wave
 constexpr int AST = 264;              // LDS row stride of the bf16 activation tiles (16-byte aligned rows)
 
@@ -997,11 +1001,11 @@ void Mlp::ensure_work(long long rows) {
 
 template <int PRECISE, bool SAVE>
 static void launch_fwd(const FwdArgs& a, int nets, hipStream_t s) {
-  if (a.n * nets >= kFullRows)
-    hipLaunchKernelGGL((k_mlp_fwd<PRECISE, SAVE, 64>), dim3((unsigned)((a.n + 63) / 64), nets), dim3(FWD_WAVES * 64), 0,
-                       s, a);
+  const long long few = (a.n + 15) / 16;
+  if (few * nets <= few_groups(PRECISE))
+    hipLaunchKernelGGL((k_mlp_fwd<PRECISE, SAVE, 16>), dim3((unsigned)few, nets), dim3(FWD_WAVES * 64), 0, s, a);
   else
-    hipLaunchKernelGGL((k_mlp_fwd<PRECISE, SAVE, 16>), dim3((unsigned)((a.n + 15) / 16), nets), dim3(FWD_WAVES * 64), 0,
+    hipLaunchKernelGGL((k_mlp_fwd<PRECISE, SAVE, 64>), dim3((unsigned)((a.n + 63) / 64), nets), dim3(FWD_WAVES * 64), 0,
                        s, a);
 }
 

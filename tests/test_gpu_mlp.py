@@ -253,3 +253,48 @@ def test_targets_of_more_values_than_a_launch_has_threads():
     (loss,) = net.train(x, x, epochs=1, batch=batch, lr=1e-30, seed=0)
     (first,) = few.train(x[:batch], x[:batch], epochs=1, batch=batch, lr=1e-30, seed=0)
     assert loss == pytest.approx(first, rel=1e-6)
+
+
+@pytest.mark.parametrize("precise,groups", [(False, 768), (True, 640)])
+def test_rows_alike_where_the_tiles_change(precise, groups):
+    """Up to `groups` work-groups of 16 rows (over all networks) a forward pass
+    takes those, beyond 64 rows each: the same bits for a row in either."""
+    import torch
+    n = 16 * groups
+    nets = [hom.MLP(N_IN, N_OUT, seed=s) for s in (1, 2)]
+    x = np.random.default_rng(n).normal(size=(n + 1, N_IN)).astype(np.float32)
+    full = nets[0].forward(x, precise=precise)
+    np.testing.assert_array_equal(nets[0].forward(x[:n], precise=precise), full[:n])
+    np.testing.assert_array_equal(nets[0].forward(x[:n - 1], precise=precise), full[:n - 1])
+    if precise:
+        return  # an ensemble is not
+    xd = torch.as_tensor(x[:n // 2 + 1], device="cuda")
+    many = hom.mlp_ensemble_infer(nets, xd, 0.1, 1.0)
+    few = hom.mlp_ensemble_infer(nets, xd[:-1].contiguous(), 0.1, 1.0)
+    for a, b in zip(many, few):
+        np.testing.assert_array_equal(a[:-1].cpu().numpy(), b.cpu().numpy())
+
+
+def test_gradients_where_the_tiles_change():
+    """A batch on 64-row tiles of the forward pass that keeps activations against
+    its two halves on 16-row ones. The weighted mean of the halves' gradients is
+    the batch's; FP32 sums over splits of 256 rows round by 256 eps = 3e-5."""
+    rng = np.random.default_rng(12)
+    n, h = 16 * 768 + 3, 5000
+    net = hom.MLP(N_IN, N_OUT, seed=5)
+    net.set_scaling(np.zeros(N_IN), np.ones(N_IN), np.zeros(N_OUT), np.ones(N_OUT), np.ones(N_OUT))
+    x = rng.normal(size=(n, N_IN)).astype(np.float32)
+    y = rng.normal(size=(n, N_OUT)).astype(np.float32)
+    L, g = net.loss_grad(x, y, precise=False)
+    (L1, g1), (L2, g2) = net.loss_grad(x[:h], y[:h], precise=False), net.loss_grad(x[h:], y[h:], precise=False)
+    assert L == pytest.approx((h * L1 + (n - h) * L2) / n, rel=1e-6)
+    for (gW, gb), (aW, ab), (bW, bb) in zip(net.layers(g), net.layers(g1), net.layers(g2)):
+        for t, a, b in ((gW, aW, bW), (gb, ab, bb)):
+            want = (h * a.astype(np.float64) + (n - h) * b) / n
+            assert np.linalg.norm(t - want) < 5e-5 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("rows", [10240, 10241])
+def test_precise_gradients_where_the_tiles_change(rows):
+    """Bounds of the smaller batches above."""
+    test_gradients_at_batch_edges(rows)
