@@ -346,6 +346,16 @@ struct Group {
     return reinterpret_cast<U*>(p);
   }
 
+  // An array taken after the setup: its clear goes over the null stream, which
+  // the lane's stream does not wait for. Without the wait a tangent call cleared
+  // a part of the stress field that it had just saved there.
+  template <typename U>
+  U* dalloc_late(size_t count) {
+    U* p = dalloc<U>(count);
+    HIPCHK(hipStreamSynchronize(nullptr));
+    return p;
+  }
+
   // streams of this group's work (the batch's own, or a lane of its own that
   // lets groups of different grids run at the same time)
   hipStream_t stream = nullptr;
@@ -1375,7 +1385,7 @@ class BatchT : public BatchImpl {
         continue;
       }
       const size_t nm = (size_t)G.nprob * G.vs;
-      if (!G.fsave) G.fsave = G.template dalloc<T>(6 * nm);
+      if (!G.fsave) G.fsave = G.template dalloc_late<T>(6 * nm);
       HIPCHK(hipMemcpyAsync(G.fsave, G.f, 6 * nm * sizeof(T), hipMemcpyDeviceToDevice, stream));
       auto restore = [&] {
         (void)hipMemcpyAsync(G.xm, G.xnm, 6 * nm * sizeof(T), hipMemcpyDeviceToDevice, stream);
@@ -1388,7 +1398,7 @@ class BatchT : public BatchImpl {
         lim.linear = 1;
         const long long cap = iteration_cap(lim, false);
         Pt<T> q = G.pt(0);
-        if (G.dx && !G.tcol) G.tcol = G.template dalloc<T>(7 * 6 * nm);  // predictor: warm starts
+        if (G.dx && !G.tcol) G.tcol = G.template dalloc_late<T>(7 * 6 * nm);  // predictor: warm starts
         for (int j = 0; j < G.nprob; ++j) {
           hom_tangent& t = out[G.members[j]];
           std::memset(&t, 0, sizeof(t));
