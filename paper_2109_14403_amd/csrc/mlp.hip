@@ -1192,13 +1192,15 @@ void Mlp::train(const float* X, const float* T, long long n, int epochs, int bat
   // normalized on the device and the arrays are one allocation: 16384 rows in two
   // epochs of 4096 a batch 1.55 -> 1.38 ms (1 ms of it the steps' kernels).
   std::mt19937_64 gen(seed);
-  std::vector<int> perm(n);
-  const auto draw_order = [&] {
-    for (long long i = 0; i < n; ++i) perm[i] = (int)i;
-    std::shuffle(perm.begin(), perm.end(), gen);
+  std::vector<int> order[2];  // of even and odd epochs: one is drawn while the other may still be copied
+  for (auto& o : order) o.resize(n);
+  const auto draw_order = [&](int e) {
+    std::vector<int>& o = order[e & 1];
+    for (long long i = 0; i < n; ++i) o[i] = (int)i;
+    std::shuffle(o.begin(), o.end(), gen);
   };
   std::future<void> first_order;
-  if (epochs > 0) first_order = std::async(std::launch::async, draw_order);
+  if (epochs > 0) first_order = std::async(std::launch::async, draw_order, 0);
   // one allocation for the call's arrays: each one's bytes rounded up to 256
   const auto bytes = [](long long b) { return (b + 255) / 256 * 256; };
   const long long bx = bytes(n * n_in * 4), bt = bytes(n * MLP_OUT * 4), bi_ = bytes(n * 4),
@@ -1260,10 +1262,9 @@ void Mlp::train(const float* X, const float* T, long long n, int epochs, int bat
     if (e == 0)
       first_order.get();
     else
-      draw_order();
-    HIPCHK(hipStreamSynchronize(s));  // the last epoch's gathers have read didx
-    HIPCHK(hipMemcpy(didx, perm.data(), n * 4, hipMemcpyHostToDevice));
-    HIPCHK(hipStreamSynchronize(nullptr));  // ... and the new order is there before the next ones
+      draw_order(e);
+    HIPCHK(hipStreamSynchronize(s));  // the last epoch's order has been copied, and read
+    HIPCHK(hipMemcpyAsync(didx, order[e & 1].data(), n * 4, hipMemcpyHostToDevice, s));
     for (long long sidx = 0; sidx < steps_per_epoch; ++sidx) {
       const int* bi = didx + sidx * batch;
       const int lb = grad_partials(dX, dT, batch, false, s, dW, bi);
